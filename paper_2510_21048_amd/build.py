@@ -15,6 +15,11 @@ FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
     # no packed fp32 instructions anywhere (none are needed: the path is integer-only)
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+    # the row tables order their integer keys as doubles, none of them a NaN: min and max need no quieting
+    "-fno-honor-nans",
+    # the event loops branch on wave-uniform values only: left unstructured, both sides of a branch update
+    # the table's registers in place (structured, each side keeps a copy: 1.7x the registers, and spills)
+    "-mllvm", "-structurizecfg-skip-uniform-regions=1",
 ]
 
 

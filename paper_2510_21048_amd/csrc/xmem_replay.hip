@@ -19,10 +19,11 @@
 //               chain is one (trace, pool) pair when the capacity is unbounded
 //               (the pools never interact), else one trace.  The chain walks
 //               the annotated stream in 64-event tiles with a one-tile
-//               prefetch.  Each free block is one packed key (size, address)
-//               held unordered in an LDS table (768 per pool; paged sorted sets
-//               in HBM beyond): best fit (Section 3.4 (iii)) is a masked wavefront
-//               minimum, splits and merges rewrite one slot, a new segment is
+//               prefetch.  Each free block is one packed key (size, address),
+//               held sorted in vector registers (768 per pool; paged sorted sets
+//               in HBM beyond): best fit (Section 3.4 (iii)) is one comparison per
+//               row and a ballot, a split or merge moves the keys between its old
+//               and new place by one, a new segment is
 //               requested only when nothing fits (Section 3.4 (ii), (iv)), and
 //               under a capacity idle segments are released before OOM is
 //               declared (Section 3.4 (v)).  Allocated blocks reach their free
@@ -388,6 +389,13 @@ __device__ __forceinline__ uint64_t wl64(uint64_t val, int lane, uint64_t v) {
   return (int)threadIdx.x == lane ? val : v;
 }
 __device__ __forceinline__ uint64_t ballot(bool p) { return __builtin_amdgcn_ballot_w64(p); }
+// a wave-uniform value that was loaded into vector registers, in scalar ones (conditions on it are
+// then scalar branches)
+__device__ __forceinline__ uint32_t uni(uint32_t v) { return __builtin_amdgcn_readfirstlane(v); }
+__device__ __forceinline__ int32_t uni(int32_t v) { return __builtin_amdgcn_readfirstlane(v); }
+__device__ __forceinline__ uint64_t uni64(uint64_t v) {
+  return (uint64_t)uni((uint32_t)v) | ((uint64_t)uni((uint32_t)(v >> 32)) << 32);
+}
 // Orders this wavefront's memory operations as written (single-wavefront
 // workgroups: the hardware keeps a wavefront's accesses in order).
 __device__ __forceinline__ void wave_order() { __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront"); }
@@ -897,167 +905,193 @@ __device__ __forceinline__ int64_t event_delta(const Gw& w, int64_t base, int64_
   return 0;
 }
 
-// ------------------------------------------------------------------ fast chain: 32-bit packed keys
+// ------------------------------------------------------------------ row tables: sorted keys in registers
 // Every free block is one 64-bit key (size << 32) | address, in units, so the
 // best fit of Section 3.4 (iii) -- the smallest (size, address) with size >= u
-// -- is the smallest key >= (u << 32): a masked wavefront minimum.  A pool's
-// keys sit unordered in the kLdsSlots slots of its LDS table.  Each event
-// makes one pass over the used rows (every row load issued before the first
-// use), then rewrites at most two slots from one lane.  A chain hands itself
-// over when a pool would need more free blocks than its table holds (status
-// kSpill, to the paged chain kernel) or when sizes or addresses reach 2^31
+// -- is the first key >= (u << 32) in key order.  A pool's keys are held sorted
+// in vector registers: with R rows in use, key i sits in lane i / R of row
+// i % R, so that moving a run of keys by one place is a move between rows of
+// the same lane, and only the outermost row crosses lanes (one DPP shift).
+// Sizes stay below kRowLimit, so a key is also a non-negative finite double in
+// the same order, and an insertion is one v_max_f64 and one v_min_f64 per row:
+//   with v inserted, place p holds min(x[p], max(x[p - 1], v)).
+// The slots past the count hold kEmptyKey, above every key.  A chain hands
+// itself over when a pool would need more free blocks than the rows hold (status
+// kSpill, to the paged chain kernel) or when sizes or addresses reach kRowLimit
 // units (status kRetry, to the 64-bit chain kernel); either replays it again.
-constexpr int kLdsRows = 12;  // 6 KB per pool: six replay wavefronts per SIMD (80 VGPRs each)
-constexpr int32_t kLdsSlots = kLdsRows * 64;
-constexpr uint64_t kFastLimit = 1ull << 31;
-static_assert(kStateKeys == kLdsSlots, "a chunk state holds a full LDS table");
+constexpr int kTabRows = 12;
+constexpr int32_t kTabSlots = kTabRows * 64;
+constexpr uint64_t kFastLimit = 1ull << 31;  // the paged chains' sizes and addresses
+constexpr uint32_t kEmptyHi = 0x7fe00000u;   // a finite double above every key
+constexpr uint64_t kEmptyKey = (uint64_t)kEmptyHi << 32;
+constexpr uint64_t kRowLimit = kEmptyHi;
+static_assert(kStateKeys == kTabSlots, "a chunk state holds a full table");
 constexpr uint64_t kNoKey = ~0ull;
 constexpr int kRetry = 0x40;
 constexpr int kSpill = 0x41;
 constexpr int kAbandoned = 0x42;  // a speculative chunk past where its round's walk will stop
 
 __device__ __forceinline__ uint64_t key_of(uint64_t size, uint64_t addr) { return (size << 32) | addr; }
+__device__ __forceinline__ uint64_t key_of32(uint32_t size, uint32_t addr) { return ((uint64_t)size << 32) | addr; }
 __device__ __forceinline__ uint64_t key_size(uint64_t k) { return k >> 32; }
 __device__ __forceinline__ uint64_t key_addr(uint64_t k) { return k & 0xffffffffull; }
+__device__ __forceinline__ uint32_t hi32(uint64_t k) { return (uint32_t)(k >> 32); }
+__device__ __forceinline__ uint32_t lo32(uint64_t k) { return (uint32_t)k; }
 // the same block as an address key (address << 32) | size: ordered by address
 __device__ __forceinline__ uint64_t akey_of(uint64_t size, uint64_t addr) { return (addr << 32) | size; }
 __device__ __forceinline__ uint64_t akey_size(uint64_t k) { return k & 0xffffffffull; }
 __device__ __forceinline__ uint64_t akey_addr(uint64_t k) { return k >> 32; }
 
-struct STab {
-  LMEM uint64_t* l;  // slots [0, kLdsSlots); slots n.. hold kNoKey
-  int32_t n;
+// keys in order as doubles (no key is a NaN: -fno-honor-nans keeps these single instructions)
+__device__ __forceinline__ uint64_t kmin(uint64_t a, uint64_t b) {
+  return __builtin_bit_cast(uint64_t, __builtin_fmin(__builtin_bit_cast(double, a), __builtin_bit_cast(double, b)));
+}
+__device__ __forceinline__ uint64_t kmax(uint64_t a, uint64_t b) {
+  return __builtin_bit_cast(uint64_t, __builtin_fmax(__builtin_bit_cast(double, a), __builtin_bit_cast(double, b)));
+}
+// lane i gets lane i - 1's key (lane 0: zero, below every key) / lane i + 1's (lane 63: kEmptyKey)
+__device__ __forceinline__ uint64_t key_below(uint64_t v) {
+  return ((uint64_t)(uint32_t)__builtin_amdgcn_update_dpp(0, (int)hi32(v), 0x138, 0xf, 0xf, true) << 32) |
+         (uint32_t)__builtin_amdgcn_update_dpp(0, (int)lo32(v), 0x138, 0xf, 0xf, true);
+}
+__device__ __forceinline__ uint64_t key_above(uint64_t v) {
+  return ((uint64_t)(uint32_t)__builtin_amdgcn_update_dpp((int)kEmptyHi, (int)hi32(v), 0x130, 0xf, 0xf, false) << 32) |
+         (uint32_t)__builtin_amdgcn_update_dpp(0, (int)lo32(v), 0x130, 0xf, 0xf, true);
+}
+// lane `lane` (wave-uniform) of v replaced by the wave-uniform val
+extern "C" __device__ int xmem_llvm_writelane(int val, int lane, int v) __asm("llvm.amdgcn.writelane.i32");
+__device__ __forceinline__ uint32_t wl(uint32_t val, uint32_t lane, uint32_t v) {
+  return (uint32_t)xmem_llvm_writelane((int)val, (int)lane, (int)v);
+}
+// the lowest set lane of a mask (lane 63 when there is none)
+__device__ __forceinline__ int first_lane(uint64_t m) { return __builtin_ctzll(m | (1ull << 63)); }
+
+struct RTab {
+  uint64_t k[kTabRows];  // rows 0 .. rows - 1 are in use
+  int32_t n, rows;
 };
-// single writer (lane 0); v is wave-uniform
-__device__ __forceinline__ void st_store(STab& t, int32_t i, uint64_t v) {
-  if (threadIdx.x == 0) t.l[i] = v;
-  wave_order();
+typedef uint64_t Keys[kTabRows];
+
+// k = min(k, m) / max(k, m) in k's own registers (left to itself the compiler writes the new keys
+// beside the old ones and copies them back where the event paths join, which doubles the table's
+// registers); rt_settle: two wait states before a DPP move may read them
+__device__ __forceinline__ void kmin_to(uint64_t& k, uint64_t m) { asm("v_min_f64 %0, %0, %1" : "+v"(k) : "v"(m)); }
+__device__ __forceinline__ void kmax_to(uint64_t& k, uint64_t m) { asm("v_max_f64 %0, %0, %1" : "+v"(k) : "v"(m)); }
+__device__ __forceinline__ void rt_settle(uint64_t& k) { asm("s_nop 1" : "+v"(k)); }
+__device__ __forceinline__ uint64_t with_hi(uint64_t k, uint32_t hi) { return ((uint64_t)hi << 32) | lo32(k); }
+
+// v (not present) inserted; room for it checked by the caller
+template <int R>
+__device__ __forceinline__ void rt_insert(Keys& k, uint64_t v) {
+  const uint64_t y0 = key_below(k[R - 1]);
+#pragma unroll
+  for (int r = R - 1; r >= 0; --r) kmin_to(k[r], kmax(r > 0 ? k[r > 0 ? r - 1 : 0] : y0, v));
+  rt_settle(k[R - 1]);
 }
-// remove slot i; `last` is the key in slot n-1, which moves into slot i
-__device__ __forceinline__ void st_remove(STab& t, int32_t i, uint64_t last) {
-  const int32_t l = t.n - 1;
-  if (threadIdx.x == 0) {
-    if (i != l) t.l[i] = last;
-    uint64_t none = kNoKey;
-    asm volatile("" : "+v"(none));  // made here: a constant held through the event loop can take a spill slot
-    t.l[l] = none;
+// The present key x replaced by the smaller v: as an insertion, but only up to x's place (a place
+// past it, whose lower neighbour is x or above, takes the minimum with something above every key;
+// only the high half has to say so).
+template <int R>
+__device__ __forceinline__ void rt_lower(Keys& k, uint64_t x, uint64_t v) {
+  const uint64_t y0 = key_below(k[R - 1]);
+#pragma unroll
+  for (int r = R - 1; r >= 0; --r) {
+    const uint64_t y = r > 0 ? k[r > 0 ? r - 1 : 0] : y0;
+    const uint64_t m = kmax(y, v);
+    kmin_to(k[r], with_hi(m, y >= x ? kEmptyHi : hi32(m)));
   }
-  wave_order();
-  t.n = l;
+  rt_settle(k[R - 1]);
 }
-// append v; false when the table is full
-__device__ __forceinline__ bool st_append(STab& t, uint64_t v) {
-  if (t.n == kLdsSlots) return false;
-  st_store(t, t.n, v);
+// The present key x replaced by the larger v (kEmptyKey: removed): the mirror image, from x's place
+// on (a place before it takes the maximum with something below every key).
+template <int R>
+__device__ __forceinline__ void rt_raise(Keys& k, uint64_t x, uint64_t v) {
+  const uint64_t zl = key_above(k[0]);
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const uint64_t z = r < R - 1 ? k[r + 1 < kTabRows ? r + 1 : 0] : zl;
+    const uint64_t m = kmin(z, v);
+    kmax_to(k[r], with_hi(m, k[r] < x ? 0 : hi32(m)));
+  }
+  rt_settle(k[0]);
+}
+template <int R>
+__device__ __forceinline__ void rt_delete(Keys& k, uint64_t x) {
+  rt_raise<R>(k, x, kEmptyKey);
+}
+// the smallest key of size >= u (0 < u < kRowLimit); a key whose size is below u, or kEmptyKey,
+// when there is none
+template <int R>
+__device__ __forceinline__ uint64_t rt_first_fit(const Keys& k, uint32_t u) {
+  uint64_t v = k[R - 1];  // per lane: its smallest key that fits
+#pragma unroll
+  for (int r = R - 2; r >= 0; --r) v = hi32(k[r]) >= u ? k[r] : v;
+  return rl64(v, first_lane(ballot(hi32(k[R - 1]) >= u)));
+}
+// sizes of the free blocks ending at a and starting at e (0: none); each is unique
+template <int R>
+__device__ __forceinline__ void rt_neighbours(const Keys& k, uint32_t a, uint32_t e, uint32_t* left, uint32_t* right) {
+  uint32_t l = 0, g = 0;
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    l = lo32(k[r]) + hi32(k[r]) == a ? hi32(k[r]) : l;
+    g = lo32(k[r]) == e ? hi32(k[r]) : g;
+  }
+  *left = rl(l, first_lane(ballot(l != 0)));
+  *right = rl(g, first_lane(ballot(g != 0)));
+}
+
+// The row counts in use, and the smallest that holds n keys.  (Each is an instance of the event
+// code below; a count between two of them runs on the larger.)
+__device__ __forceinline__ int rows_for(int32_t n) {
+  return n <= 64 ? 1 : n <= 128 ? 2 : n <= 192 ? 3 : n <= 256 ? 4 : n <= 384 ? 6 : n <= 512 ? 8 : kTabRows;
+}
+// at a tile's end a table moves to fewer rows once it would leave a quarter row of them free
+__device__ __forceinline__ int rows_shrunk(int32_t n, int rows) {
+  const int r = rows_for(n + 24);
+  return r < rows ? r : rows;
+}
+// keys in order to and from s[0, 64 rows) / with `rows` rows
+__device__ __forceinline__ void rt_put(const RTab& t, LMEM uint64_t* s) {
+  const int lane = threadIdx.x;
+#pragma unroll
+  for (int r = 0; r < kTabRows; ++r)
+    if (r < t.rows) s[lane * t.rows + r] = t.k[r];
+  wave_order();
+}
+template <class P>
+__device__ __forceinline__ void rt_get(RTab& t, P s, int32_t n, int rows) {
+  const int lane = threadIdx.x;
+  t.n = n;
+  t.rows = rows;
+  uint64_t none = kEmptyKey;
+  asm volatile("" : "+v"(none));  // made here: a constant held through the event loop can take a spill slot
+#pragma unroll
+  for (int r = 0; r < kTabRows; ++r)
+    if (r < rows) t.k[r] = lane * rows + r < n ? s[lane * rows + r] : none;
+}
+__device__ __forceinline__ void rt_rows(RTab& t, int rows, LMEM uint64_t* s) {
+  rt_put(t, s);
+  rt_get(t, s, t.n, rows);
+  wave_order();
+}
+
+__device__ __forceinline__ void rt_insert_any(RTab& t, uint64_t v) {
+  switch (t.rows) {
+    case 1: rt_insert<1>(t.k, v); break;
+    case 2: rt_insert<2>(t.k, v); break;
+    case 3: rt_insert<3>(t.k, v); break;
+    case 4: rt_insert<4>(t.k, v); break;
+    case 6: rt_insert<6>(t.k, v); break;
+    case 8: rt_insert<8>(t.k, v); break;
+    default: rt_insert<kTabRows>(t.k, v); break;
+  }
   t.n += 1;
-  return true;
 }
 
-// this lane's keys of the rows in use (slots past the count read kNoKey).  The table
-// operations take NR, the rows they cover: kLdsRows checks the count before each row;
-// a smaller NR (a table of at most 64 * NR keys) covers rows 0..NR-1 with no checks,
-// since the slots past the count hold kNoKey.
-template <int NR>
-struct Rows {
-  uint64_t x[NR];
-};
-template <int NR>
-__device__ __forceinline__ bool st_row_used(const STab& t, int r) {
-  return NR < kLdsRows || 64 * r < t.n;
-}
-// rows r.. of the table (nested, so every row index is a constant: a loop with an early
-// exit is not always unrolled, and a row array indexed at run time goes to scratch memory)
-template <int NR, int r = 0>
-__device__ __forceinline__ void st_rows(const STab& t, Rows<NR>& R) {
-  if constexpr (r < NR) {
-    if (st_row_used<NR>(t, r)) {
-      R.x[r] = t.l[64 * r + (int)threadIdx.x];
-      st_rows<NR, r + 1>(t, R);
-    }
-  }
-}
-// key in slot n-1 (n > 0), read from the loaded rows
-template <int NR>
-__device__ __forceinline__ uint64_t st_last(const STab& t, const Rows<NR>& R) {
-  const int32_t i = t.n - 1;
-  const int lr = i >> 6, ll = i & 63;
-  uint64_t v = kNoKey;
-#pragma unroll
-  for (int r = 0; r < NR; ++r)
-    if (NR == 1 || r == lr) v = rl64(R.x[r], ll);
-  return v;
-}
-
-// wavefront minimum of 64-bit keys and a lane holding it: the size halves
-// first; the address halves only when several lanes tie on the smallest size
-__device__ __forceinline__ uint64_t wave_min_key(uint64_t k, int* at) {
-  const uint32_t hi = wave_min_u32((uint32_t)(k >> 32));
-  const uint64_t tie = ballot((uint32_t)(k >> 32) == hi);
-  if (__builtin_popcountll(tie) == 1) {
-    *at = __builtin_ctzll(tie);
-    return ((uint64_t)hi << 32) | rl((uint32_t)k, *at);
-  }
-  const uint32_t lo = wave_min_u32((uint32_t)(k >> 32) == hi ? (uint32_t)k : 0xffffffffu);
-  *at = __builtin_ctzll(ballot((uint32_t)(k >> 32) == hi && (uint32_t)k == lo));
-  return ((uint64_t)hi << 32) | lo;
-}
-
-// smallest key >= lo and its slot (-1 if none)
-template <int NR>
-__device__ __forceinline__ uint64_t st_min_ge(const STab& t, const Rows<NR>& R, uint64_t lo, int32_t* slot) {
-  uint64_t best = kNoKey;
-  int32_t bi = -1;
-#pragma unroll
-  for (int r = 0; r < NR; ++r) {
-    if (!st_row_used<NR>(t, r)) break;
-    const uint64_t x = R.x[r];
-    const bool take = x >= lo && x < best;
-    best = take ? x : best;
-    bi = take ? 64 * r + (int32_t)threadIdx.x : bi;
-  }
-  int at;
-  const uint64_t m = wave_min_key(best, &at);
-  if constexpr (NR == 1) *slot = m == kNoKey ? -1 : at;  // one row: the lane is the slot
-  else *slot = m == kNoKey ? -1 : (int32_t)rl((uint32_t)bi, at);
-  return m;
-}
-// slots (and keys) of the free blocks ending at a and starting at e (= a + s);
-// each is unique (the pool's blocks are disjoint), so every lane keeps its own
-// match through the rows and two ballots at the end find the lanes that have one
-template <int NR>
-__device__ __forceinline__ void st_neighbours(const STab& t, const Rows<NR>& R, uint64_t a, uint64_t e, int32_t* ls,
-                                              uint64_t* lk, int32_t* rs, uint64_t* rk) {
-  if constexpr (NR == 1) {  // one row: the lanes of the matches are the slots, their keys are read back
-    const uint64_t x = R.x[0];
-    const uint32_t xa = (uint32_t)x, xs = (uint32_t)(x >> 32);
-    const uint64_t lm = ballot(xa + xs == (uint32_t)a), rm = ballot(xa == (uint32_t)e);
-    *ls = -1; *lk = 0; *rs = -1; *rk = 0;
-    if (lm) { *ls = __builtin_ctzll(lm); *lk = rl64(x, *ls); }
-    if (rm) { *rs = __builtin_ctzll(rm); *rk = rl64(x, *rs); }
-    return;
-  }
-  int32_t li = -1, ri = -1;
-  uint64_t lv = 0, rv = 0;
-#pragma unroll
-  for (int r = 0; r < NR; ++r) {
-    if (!st_row_used<NR>(t, r)) break;
-    const uint64_t x = R.x[r];
-    const uint32_t xa = (uint32_t)x, xs = (uint32_t)(x >> 32);
-    const bool lh = xa + xs == (uint32_t)a, rh = xa == (uint32_t)e;
-    li = lh ? 64 * r + (int32_t)threadIdx.x : li;
-    lv = lh ? x : lv;
-    ri = rh ? 64 * r + (int32_t)threadIdx.x : ri;
-    rv = rh ? x : rv;
-  }
-  const uint64_t lm = ballot(li >= 0), rm = ballot(ri >= 0);
-  *ls = -1; *lk = 0; *rs = -1; *rk = 0;
-  if (lm) { const int l = __builtin_ctzll(lm); *ls = (int32_t)rl((uint32_t)li, l); *lk = rl64(lv, l); }
-  if (rm) { const int l = __builtin_ctzll(rm); *rs = (int32_t)rl((uint32_t)ri, l); *rk = rl64(rv, l); }
-}
-
-struct FastPool {
-  STab t;
-  uint64_t split_min;  // split_min of this pool, in units
+struct RowPool {
+  RTab t;
+  uint32_t split_min;   // split_min of this pool, in units (at most kRowLimit: no remainder reaches it)
   GMEM uint64_t* segs;  // keys of the segments created in this pool, slot k at segs[segdir * k]
   int segdir;
   int32_t nseg;
@@ -1065,15 +1099,20 @@ struct FastPool {
   int32_t maxfree, n_mf;
   int pool;
 };
-__device__ __forceinline__ int32_t pool_free_count(const FastPool& ps) { return ps.t.n; }
+__device__ __forceinline__ int32_t pool_free_count(const RowPool& ps) { return ps.t.n; }
+__device__ __forceinline__ uint32_t row_split_min(const Derived& d, int pool) {
+  const uint64_t s = pool == 0 ? d.split_min_u[0] : d.split_min_u[1];
+  return s < kRowLimit ? (uint32_t)s : (uint32_t)kRowLimit;
+}
 
 // A chain replays a whole trace (CH false: change points go to the trace's
 // record layout) or one chunk of it (CH true: to the chunk's own record region;
 // see the chunked replay below).
 template <int NP, bool CH = false>
-struct FastChain {
+struct RowChain {
   static constexpr bool kChunk = CH;
-  FastPool p[NP];
+  RowPool p[NP];
+  LMEM uint64_t* s;  // kTabSlots keys of LDS, for moving a table between row counts
   uint64_t reserved_u;
   int32_t created, released, n_res;
   int64_t base, n;
@@ -1105,7 +1144,7 @@ __device__ __forceinline__ void note_choice(C& c, uint64_t u, uint64_t S) {
   }
 }
 
-// change points, shared by the fast and the paged chains
+// change points, shared by the row-table and the paged chains
 template <class C>
 __device__ __forceinline__ void record_reserved(C& c, const Gw& w, int64_t e, int shift) {
   if (threadIdx.x == 0) {
@@ -1159,131 +1198,363 @@ __device__ __forceinline__ uint64_t segment_units(const Derived& d, int pool, ui
 
 // Section 3.4 (iv)-(v): units held by idle segments of both pools
 template <int NP, bool CH>
-__device__ __forceinline__ uint64_t fast_idle_units(const FastChain<NP, CH>& c) {
+__device__ __forceinline__ uint64_t row_idle_units(const RowChain<NP, CH>& c) {
   uint64_t mine = 0;
 #pragma unroll
   for (int q = 0; q < NP; ++q) {
-    const FastPool& ps = c.p[q];
-    for (int32_t i = threadIdx.x; i < ps.t.n; i += kWave) {
-      const uint64_t x = ps.t.l[i];
-      if (seg_key_idle(ps.segs, ps.segdir, ps.nseg, x)) mine += key_size(x);
+    const RowPool& ps = c.p[q];
+#pragma unroll
+    for (int r = 0; r < kTabRows; ++r) {
+      if (r < ps.t.rows) {
+        const uint64_t x = ps.t.k[r];
+        if (x < kEmptyKey && seg_key_idle(ps.segs, ps.segdir, ps.nseg, x)) mine += key_size(x);
+      }
     }
   }
   return wave_sum_u64(mine);
 }
-
+// release every idle segment of both pools: the keys that stay, in order through LDS
 template <int NP, bool CH>
-__device__ __forceinline__ void fast_release_idle(FastChain<NP, CH>& c) {
-  const int lane = threadIdx.x;
+__device__ __forceinline__ void row_release_idle(RowChain<NP, CH>& c) {
 #pragma unroll
   for (int q = 0; q < NP; ++q) {
-    FastPool& ps = c.p[q];
-    int32_t i = 0;
-    while (true) {  // first idle slot at or after i; the slot refilled by the removal is examined next
-      int32_t hit = -1;
-      for (int32_t r = i; r < ps.t.n; r += kWave) {
-        const int32_t k = r + lane;
-        const bool idle = k < ps.t.n && seg_key_idle(ps.segs, ps.segdir, ps.nseg, ps.t.l[k]);
-        const uint64_t m = ballot(idle);
-        if (m) { hit = r + __builtin_ctzll(m); break; }
+    RowPool& ps = c.p[q];
+    uint32_t keep = 0, kept = 0;  // this lane's rows that stay (a bit each), and how many
+    uint64_t freed = 0;
+#pragma unroll
+    for (int r = 0; r < kTabRows; ++r) {
+      if (r < ps.t.rows) {
+        const uint64_t x = ps.t.k[r];
+        const bool live = x < kEmptyKey;
+        const bool idle = live && seg_key_idle(ps.segs, ps.segdir, ps.nseg, x);
+        freed += idle ? key_size(x) : 0;
+        keep |= live && !idle ? 1u << r : 0u;
+        kept += live && !idle ? 1u : 0u;
       }
-      if (hit < 0) break;
-      c.reserved_u -= key_size(ps.t.l[hit]);
-      c.released += 1;
-      st_remove(ps.t, hit, ps.t.l[ps.t.n - 1]);
-      i = hit;
+    }
+    const uint32_t incl = wave_incl_sum_u32(kept);
+    const int32_t n = (int32_t)rl(incl, kWave - 1);
+    if (n < ps.t.n) {
+      uint32_t pos = incl - kept;
+#pragma unroll
+      for (int r = 0; r < kTabRows; ++r)
+        if (keep & (1u << r)) c.s[pos++] = ps.t.k[r];
+      wave_order();
+      c.reserved_u -= wave_sum_u64(freed);
+      c.released += ps.t.n - n;
+      rt_get(ps.t, c.s, n, ps.t.rows);
+      wave_order();
     }
   }
 }
 
-// The best fit of u units among the cached free blocks (Section 3.4 (iii)), split
-// or taken whole; false when none fits.  NR: rows of the table covered.
-template <int NR>
-__device__ __forceinline__ bool fast_take(STab& t, uint64_t u, uint64_t split_min, uint64_t* blk) {
-  Rows<NR> R;
-  st_rows<NR>(t, R);
-  int32_t slot;
-  const uint64_t b = st_min_ge<NR>(t, R, u << 32, &slot);
-  if (b == kNoKey) return false;
-  const uint64_t S = key_size(b), A = key_addr(b), rem = S - u;
-  if (rem >= split_min) { st_store(t, slot, key_of(rem, A + u)); *blk = key_of(u, A); }
-  else { st_remove(t, slot, st_last<NR>(t, R)); *blk = b; }
-  return true;
+// A 64-event tile of the trace, each lane its event.
+struct RowTile {
+  uint32_t op;        // an allocation: its units; a free: kRowFree
+  uint32_t dst;       // an allocation: the lane of its free when that lies in the tile, else its own
+  uint32_t pair;      // an allocation whose free is the chain's very next event, and that free: the units; else ~0
+  uint32_t ba, bs;    // block (address, size): of a free, to release; of an allocation freed past the tile
+  uint64_t pairs;     // lanes of such allocations
+};
+constexpr uint32_t kRowFree = 1u << 31;
+
+// The events of `todo` (lanes of the tile, at least one, all of one pool) on R rows, in order, until none is left
+// (false) or one needs more than the table's keys (true; nothing of it done, its bit the lowest
+// left): an allocation that no cached block fits, a free that fills the rows or passes the pool's
+// maximum free count (room: the smaller of the two).
+//
+// An allocation whose free is the chain's next event, and that a cached block fits, is skipped
+// with its free: the free gives the block back to the remainder it was split from (or frees it
+// whole), its left neighbour is not free (no two free blocks are adjacent), so the table is as
+// before; the free count was one lower in between, or the same, and is no new maximum.  In one
+// row the largest key tells how many such pairs go at once (those of other pools: ONE is unset).
+template <int R, bool ONE>
+__device__ __forceinline__ bool row_events(Keys& k, int32_t& n, const int32_t room, const uint32_t split_min, RowTile& T,
+                                           uint64_t& todo) {
+  // nested conditions and one exit: early exits would have every path carry a copy of the table
+  uint64_t rest = 0;
+  do {
+    const int j = __builtin_ctzll(todo);
+    const uint32_t op = rl(T.op, j);
+    uint64_t next = todo & (todo - 1);
+    if (!(op & kRowFree)) {
+      const uint64_t b = rt_first_fit<R>(k, op);
+      const uint32_t a = lo32(b), left = hi32(b) - op;
+      if (left < kEmptyHi - op) {
+        if (!(T.pairs & (todo ^ next))) {
+          uint32_t size = op;
+          if (left >= split_min) {
+            rt_lower<R>(k, b, key_of32(left, a + op));
+          } else {
+            rt_delete<R>(k, b);
+            n -= 1;
+            size = hi32(b);
+          }
+          const uint32_t to = rl(T.dst, j);
+          T.ba = wl(a, to, T.ba);
+          T.bs = wl(size, to, T.bs);
+        } else if (ONE && R == 1) {
+          const uint32_t most = rl(hi32(k[0]), n - 1);
+          const uint64_t stay = todo & ~ballot(T.pair <= most);
+          next = stay ? todo & (~0ull << __builtin_ctzll(stay)) : 0;
+        } else {
+          next &= next - 1;
+        }
+      } else {
+        rest = todo;
+        next = 0;
+      }
+    } else {
+      const uint32_t a = rl(T.ba, j), s = rl(T.bs, j), e = a + s;
+      uint32_t ls, rs;
+      rt_neighbours<R>(k, a, e, &ls, &rs);
+      const uint64_t v = key_of32(s + ls + rs, a - ls);
+      if (ls | rs) {
+        if (ls != 0 && rs != 0) {
+          rt_delete<R>(k, key_of32(rs, e));
+          n -= 1;
+        }
+        rt_raise<R>(k, ls ? key_of32(ls, a - ls) : key_of32(rs, e), v);
+      } else if (n < room) {
+        rt_insert<R>(k, v);
+        n += 1;
+      } else {
+        rest = todo;
+        next = 0;
+      }
+    }
+    todo = next;
+  } while (todo);
+  todo = rest;
+  return rest != 0;
+}
+template <bool ONE>
+__device__ __forceinline__ bool row_events_any(RowPool& ps, RowTile& T, uint64_t& todo) {
+  Keys& k = ps.t.k;
+  const int32_t full = 64 * ps.t.rows, room = ps.maxfree < full ? ps.maxfree : full;
+  switch (ps.t.rows) {
+    case 1: return row_events<1, ONE>(k, ps.t.n, room, ps.split_min, T, todo);
+    case 2: return row_events<2, ONE>(k, ps.t.n, room, ps.split_min, T, todo);
+    case 3: return row_events<3, ONE>(k, ps.t.n, room, ps.split_min, T, todo);
+    case 4: return row_events<4, ONE>(k, ps.t.n, room, ps.split_min, T, todo);
+    case 6: return row_events<6, ONE>(k, ps.t.n, room, ps.split_min, T, todo);
+    case 8: return row_events<8, ONE>(k, ps.t.n, room, ps.split_min, T, todo);
+    default: return row_events<kTabRows, ONE>(k, ps.t.n, room, ps.split_min, T, todo);
+  }
 }
 
-// Allocation of u units (Section 3.4 (i)-(v)); returns a status and the key of
-// the block handed out in *blk.  A table of one or two rows (at most 128 free
-// blocks, the usual case) is scanned with no per-row count checks.
+// An event that row_events left: a new segment (Section 3.4 (ii), (iv); NP 2: under a capacity), or
+// a freed block with no free neighbour.  A key that the table cannot hold hands the chain over
+// before the event has changed anything, so that the state is the one before the event (a chunk
+// resumes there).
 template <int NP, bool CH>
-__device__ __forceinline__ int pool_alloc(FastChain<NP, CH>& c, FastPool& ps, const Derived& d, const Gw& w, uint64_t u,
-                                          int64_t e, uint64_t* blk) {
-  if (u >= kFastLimit) return kRetry;
-  const uint64_t split_min = ps.split_min;
-  if (ps.t.n <= 64 ? fast_take<1>(ps.t, u, split_min, blk)
-                    : ps.t.n <= 128 ? fast_take<2>(ps.t, u, split_min, blk) : fast_take<kLdsRows>(ps.t, u, split_min, blk))
-    return XMEM_T_OK;
-  // nothing cached fits: a new segment (Section 3.4 (ii), (iv))
-  const uint64_t S = segment_units(d, ps.pool, u);
-  if (ps.created_u + S > d.limit_u) return XMEM_T_OVERFLOW;
-  if (ps.bump + S + 1 > kFastLimit) return kRetry;
-  if (NP == 2 && S > d.cap_u - c.reserved_u) {  // Section 3.4 (v): reclaim idle segments, else OOM
-    const uint64_t idle = fast_idle_units(c);
-    if (S > d.cap_u - (c.reserved_u - idle)) return XMEM_T_OOM;
-    fast_release_idle(c);
-  }
-  const uint64_t rem = S - u;
-  // a remainder the table cannot hold: the chain is handed over before the event has changed
-  // anything, so that its state is the one before the event (a chunk resumes there)
-  if (rem >= split_min && ps.t.n == kLdsSlots) return kSpill;
-  const uint64_t A = ps.bump;
-  // the segment table serves reclamation only, which chunked (unbounded) chains never do
-  if (!CH && threadIdx.x == 0) ps.segs[(int64_t)ps.segdir * ps.nseg] = key_of(S, A);
-  ps.nseg += 1;
-  ps.bump += S + 1;  // one-unit gap: segments are never physically adjacent
-  ps.created_u += S;
-  c.reserved_u += S;
-  c.created += 1;
-  record_reserved(c, w, e, d.shift);
-  if (rem >= split_min) {
-    st_append(ps.t, key_of(rem, A + u));  // room checked above
-    *blk = key_of(u, A);
+__device__ __forceinline__ int row_slow_event(RowChain<NP, CH>& c, RowPool& ps, const Derived& d, const Gw& w, int64_t e,
+                                              int j, RowTile& T) {
+  const uint32_t op = rl(T.op, j);
+  uint64_t v = 0;
+  if (!(op & kRowFree)) {
+    if (op >= kRowLimit) return kRetry;
+    const uint64_t S = segment_units(d, ps.pool, op);
+    if (ps.created_u + S > d.limit_u) return XMEM_T_OVERFLOW;
+    if (ps.bump + S + 1 > kRowLimit) return kRetry;
+    if (NP == 2 && S > d.cap_u - c.reserved_u) {  // Section 3.4 (v): reclaim idle segments, else OOM
+      const uint64_t idle = row_idle_units(c);
+      if (S > d.cap_u - (c.reserved_u - idle)) return XMEM_T_OOM;
+      row_release_idle(c);
+    }
+    const uint32_t left = (uint32_t)S - op, a = (uint32_t)ps.bump;
+    const bool split = left >= ps.split_min;
+    if (split && ps.t.n == kTabSlots) return kSpill;
+    // the segment table serves reclamation only, which chunked (unbounded) chains never do
+    if (!CH && threadIdx.x == 0) ps.segs[(int64_t)ps.segdir * ps.nseg] = key_of(S, ps.bump);
+    ps.nseg += 1;
+    ps.bump += S + 1;  // one-unit gap: segments are never physically adjacent
+    ps.created_u += S;
+    c.reserved_u += S;
+    c.created += 1;
+    record_reserved(c, w, e, d.shift);
+    const uint32_t to = rl(T.dst, j);
+    T.ba = wl(a, to, T.ba);
+    T.bs = wl(split ? op : (uint32_t)S, to, T.bs);
+    if (split) v = key_of32(left, a + op);
   } else {
-    *blk = key_of(S, A);
+    if (ps.t.n == kTabSlots) return kSpill;
+    v = key_of32(rl(T.bs, j), rl(T.ba, j));
   }
+  if (v) {
+    if (ps.t.n == 64 * ps.t.rows) rt_rows(ps.t, rows_for(ps.t.n + 1), c.s);
+    rt_insert_any(ps.t, v);
+  }
+  record_free_count(c, ps, w, e);
   return XMEM_T_OK;
 }
 
-// Release of the block with key b: mark it free, coalesce with its free
-// physical neighbours (Section 3.4 (iii)).  NR: rows of the table covered.
-template <int NR>
-__device__ __forceinline__ int fast_release(STab& t, uint64_t b) {
-  const uint64_t A = key_addr(b), S = key_size(b);
-  Rows<NR> R;
-  st_rows<NR>(t, R);
-  int32_t ls, rs;
-  uint64_t lk = 0, rk = 0;
-  st_neighbours<NR>(t, R, A, A + S, &ls, &lk, &rs, &rk);
-  uint64_t ms = S, ma = A;
-  if (ls >= 0) { ms += key_size(lk); ma = key_addr(lk); }
-  if (rs >= 0) ms += key_size(rk);
-  const uint64_t m = key_of(ms, ma);
-  if (ls >= 0 && rs >= 0) {
-    st_store(t, ls, m);
-    // the merged block may itself sit in the last slot
-    const uint64_t last = ls == t.n - 1 ? m : st_last<NR>(t, R);
-    st_remove(t, rs, last);
-  } else if (ls >= 0) {
-    st_store(t, ls, m);
-  } else if (rs >= 0) {
-    st_store(t, rs, m);
-  } else if (!st_append(t, m)) {
-    return kSpill;
-  }
-  return XMEM_T_OK;
+// v of the lane `from` (per lane; taken modulo 64)
+__device__ __forceinline__ uint32_t lane_get(uint32_t v, uint32_t from) {
+  return (uint32_t)__builtin_amdgcn_ds_bpermute((int)(from << 2), (int)v);
 }
+
+// A run's lane registers of allocated blocks (this tile's and the last tile's, each block in its
+// allocation's lane), kept where a chunk on the row table stopped so that the paged replay can take
+// over there: from is the event to resume at (-1: from the start).
+struct Resume { int64_t from; uint64_t cur, prev; };
+
+// Walks events [lo, limit) of the trace in 64-event tiles on the row tables; every free there
+// releases an allocation made there.  The next tile's event words, codes, cross links and mailbox
+// words are loaded while the current tile runs, and consumed before this tile's mailbox store, so
+// that no wait for them waits for stores as well (loads and stores share one counter).
+//
+// Bound by the latency of each event's chain of dependent instructions (a lone wavefront: 7 to 9
+// cycles each) or by vector issue (six on a SIMD), not by memory; so everything about an event that
+// does not depend on the table is made by vector steps per tile, and an event on one row takes
+// about 40 instructions.  Against the table before it (unordered keys in LDS, searched by a
+// wavefront minimum, about 150 instructions an event): 1,024 GPT-shaped traces of 262,144 events
+// 33.4 -> 17.7 ms a step, 64 ResNet-shaped traces of 65,536 events replayed serially under a
+// capacity 32.2 -> 16.3 ms, a 4,096-event MLP trace, nearly all pairs, 1.11 -> 0.09 ms.  A block travels to its free in the registers of the
+// free's own lane: from an allocation of the tile directly, from the last tile by one permutation,
+// from before that through the free's mailbox slot.
+//
+// With ms_ticks (wall-clock ticks per millisecond; 0: off), a chunk raises its wavefront's issue
+// priority as it ages (its age counted from its 64th tile and checked every 64 tiles: 1 past
+// 4 ms, 2 past 8, 3 past 16), so that on a SIMD the long tasks that end a batch of few chunks
+// per pool go first.
 template <int NP, bool CH>
-__device__ __forceinline__ int pool_free(FastChain<NP, CH>&, FastPool& ps, uint64_t b) {
-  return ps.t.n <= 64 ? fast_release<1>(ps.t, b) : ps.t.n <= 128 ? fast_release<2>(ps.t, b) : fast_release<kLdsRows>(ps.t, b);
+__device__ __forceinline__ void row_run(RowChain<NP, CH>& c, const Derived& d, const Gw& w, int pool_one, int64_t lo,
+                                        int64_t limit, int* status_out, int64_t* stop_out, Resume* rs = nullptr,
+                                        uint64_t ms_ticks = 0) {
+  GMEM uint64_t* mkey = (GMEM uint64_t*)w.mbox;  // mailbox viewed as one key per event
+  const int lane = threadIdx.x;
+  int status = XMEM_T_OK;
+  int64_t stop = -1;
+  uint64_t x = 0, mb = 0;
+  uint32_t cd = 0, lx = 0;
+  if (lo + lane < limit) {
+    const int64_t le = lo + lane;
+    x = w.ev[c.base + le];
+    cd = w.code[c.base + le];
+    lx = w.lx[c.base + le];
+  }
+  RowTile T;
+  T.ba = T.bs = 0;
+  uint64_t t_aged = 0;
+  int prio = 0;
+  for (int64_t ts = lo; ts < limit; ts += kWave) {
+    wave_order();
+    if constexpr (CH) {
+      if (ms_ticks && (((ts - lo) >> 6) & 63) == 63) {
+        const uint64_t now = wall_clock64();
+        if (t_aged == 0) t_aged = now;
+        const uint64_t age = now - t_aged;
+        const int p = age > 16 * ms_ticks ? 3 : age > 8 * ms_ticks ? 2 : age > 4 * ms_ticks ? 1 : 0;
+        if (p != prio) {  // the priority is an immediate operand
+          prio = p;
+          if (p == 1) __builtin_amdgcn_s_setprio(1);
+          else if (p == 2) __builtin_amdgcn_s_setprio(2);
+          else if (p == 3) __builtin_amdgcn_s_setprio(3);
+        }
+      }
+    }
+    int32_t bound = INT32_MAX;  // every fourth tile: loaded with the next tile, read after this one
+    if constexpr (CH) {
+      if (c.bound && (((ts - lo) >> 6) & 3) == 0)
+        bound = __hip_atomic_load(c.bound, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    // the tile's events, from the words loaded a tile ago (indices within a trace stay below 2^31)
+    const uint32_t t32 = (uint32_t)ts, le32 = t32 + (uint32_t)lane;
+    const uint32_t kind = cd & kCodeKind;
+    const bool own = kind != 0 && (NP == 2 || ((cd & kCodePool) ? 1 : 0) == pool_one);
+    const bool alloc = own && kind == kCodeAlloc;
+    const uint64_t u64 = (x + ((1ull << d.shift) - 1)) >> d.shift;
+    const uint32_t u = u64 < kRowLimit ? (uint32_t)u64 : (uint32_t)kRowLimit;
+    // an allocation's first free (all ones: none), relative to the tile
+    const uint32_t fe = (cd & kCodeInTile) ? (le32 & ~(uint32_t)(kTile - 1)) + (cd >> 4) : 0xffffffffu - lx;
+    const uint32_t rel = fe - t32;
+    const bool near = alloc && (lx | (cd & kCodeInTile)) != 0 && rel < kWave;
+    const bool far = alloc && (lx | (cd & kCodeInTile)) != 0 && rel >= 2 * kWave && fe < (uint64_t)c.n;
+    const uint64_t own_m = ballot(own);
+    const uint32_t prev_a = T.ba, prev_s = T.bs;
+    {
+      // a free's allocation, relative to the tile: in it, in the last one, or before
+      const uint32_t hd = (uint32_t)x - t32;
+      const bool last = (uint32_t)(hd + kWave) < kWave;
+      const uint32_t ga = lane_get(T.ba, hd), gs = lane_get(T.bs, hd);  // the last tile's lane hd + 64
+      T.ba = last ? ga : lo32(mb);
+      T.bs = last ? gs : hi32(mb);
+      T.op = alloc ? u : kRowFree;
+      T.dst = near ? rel : (uint32_t)lane;
+      const uint64_t after = (own_m >> lane) >> 1;  // the chain's events past this one
+      const bool pair = near && after != 0 && (uint32_t)(lane + 1 + __builtin_ctzll(after | (1ull << 63))) == rel;
+      const uint32_t pu = pair ? u : 0xffffffffu;
+      const uint32_t pf = lane_get(pu, hd);
+      T.pair = alloc ? pu : own && hd < kWave ? pf : 0xffffffffu;
+      T.pairs = ballot(pair);
+    }
+    uint64_t nx = 0, nmb = 0;
+    uint32_t ncd = 0, nlx = 0;
+    {  // the next tile; its mailbox slots hold the blocks of allocations two or more tiles back
+      const int64_t le = ts + kWave + lane;
+      if (le < limit) { nx = w.ev[c.base + le]; ncd = w.code[c.base + le]; nlx = w.lx[c.base + le]; nmb = mkey[c.base + le]; }
+    }
+    uint64_t todo = own_m;
+    const uint64_t large = NP == 2 ? ballot(own && (cd & kCodePool)) : 0;
+    while (todo) {
+      uint64_t later = 0;  // NP 2: the events past this run of one pool's
+      int st = XMEM_T_OK, j = 0;
+      bool slow;
+      if (NP == 1) {
+        slow = row_events_any<true>(c.p[0], T, todo);
+      } else {
+        const bool big = (large >> __builtin_ctzll(todo)) & 1;
+        const uint64_t others = todo & (big ? ~large : large);
+        later = others ? todo & (~0ull << __builtin_ctzll(others)) : 0;
+        todo &= ~later;
+        slow = big ? row_events_any<false>(c.p[NP - 1], T, todo) : row_events_any<false>(c.p[0], T, todo);
+        if (slow && big) st = row_slow_event(c, c.p[NP - 1], d, w, ts + __builtin_ctzll(todo), __builtin_ctzll(todo), T);
+      }
+      if (slow) {
+        j = __builtin_ctzll(todo);
+        if (NP == 1 || !((large >> j) & 1)) st = row_slow_event(c, c.p[0], d, w, ts + j, j, T);
+        if (st != XMEM_T_OK) { status = st; stop = ts + j; break; }
+        todo &= todo - 1;
+      }
+      todo |= later;
+    }
+    if (stop >= 0) {
+      if (rs) {
+        rs->cur = key_of32(lane_get(T.bs, T.dst), lane_get(T.ba, T.dst));
+        rs->prev = key_of32(prev_s, prev_a);
+      }
+      break;
+    }
+#pragma unroll
+    for (int q = 0; q < NP; ++q) {
+      RTab& t = c.p[q].t;
+      if (t.rows > 1) {
+        const int r = rows_shrunk(t.n, t.rows);
+        if (r < t.rows) rt_rows(t, r, c.s);
+      }
+    }
+    asm volatile("" ::"v"(nx), "v"(ncd), "v"(nlx), "v"(nmb));  // loaded by now
+    // every allocation of the tile whose free lies two or more tiles ahead: its block to the
+    // free's mailbox slot, all in one vector store (ordered before the next tile's loads)
+    if (far) mkey[c.base + fe] = key_of32(T.bs, T.ba);
+    if constexpr (CH) {
+      // another chunk of the round created segments or stopped before this one: the walk will
+      // never read this chunk's results, so it ends here and writes none
+      if (c.k_self > __builtin_amdgcn_readfirstlane(bound)) {
+        status = kAbandoned;
+        stop = ts;
+        break;
+      }
+    }
+    x = nx;
+    cd = ncd;
+    lx = nlx;
+    mb = nmb;
+  }
+  if (prio) __builtin_amdgcn_s_setprio(0);
+  *status_out = status;
+  *stop_out = stop;
 }
 
 // ------------------------------------------------------------------ the serial event loop of one chain
@@ -1313,11 +1584,6 @@ __device__ __forceinline__ int chain_step(C& c, const Derived& d, const Gw& w, G
   return XMEM_T_OK;
 }
 
-// A run's lane registers of allocated blocks (this tile's and the last tile's), kept where a
-// chunk on the LDS table stopped so that the paged replay can take over there: from is the
-// event to resume at (-1: from the start).
-struct Resume { int64_t from; uint64_t cur, prev; };
-
 // Walks the trace's annotated stream in 64-event tiles (the next tile's op,
 // link and mailbox words prefetched) and takes the chain's events with a
 // ballot + s_ff1 loop.  Allocated blocks reach their frees through lane
@@ -1326,14 +1592,9 @@ struct Resume { int64_t from; uint64_t cur, prev; };
 // made there.  With rs: resumes at rs->from (tiles stay aligned to lo; the
 // events before it in its tile were replayed, their blocks in rs->cur and the
 // last tile's in rs->prev), and leaves the registers in rs at the end.
-// With ms_ticks (wall-clock ticks per millisecond; 0: off), a chunk raises its wavefront's issue
-// priority as it ages (its age counted from its 64th tile and checked every 64 tiles: 1 past
-// 4 ms, 2 past 8, 3 past 16), so that on a SIMD the long tasks that end a batch of few chunks
-// per pool go first.
 template <int NP, class C>
 __device__ __forceinline__ void chain_run(C& c, const Derived& d, const Gw& w, int pool_one, int64_t lo, int64_t limit,
-                                          int* status_out, int64_t* stop_out, Resume* rs = nullptr,
-                                          uint64_t ms_ticks = 0) {
+                                          int* status_out, int64_t* stop_out, Resume* rs = nullptr) {
   GMEM uint64_t* mkey = (GMEM uint64_t*)w.mbox;  // mailbox viewed as one key per event
   const int lane = threadIdx.x;
   int status = XMEM_T_OK;
@@ -1358,29 +1619,8 @@ __device__ __forceinline__ void chain_run(C& c, const Derived& d, const Gw& w, i
   // loop would make every event wait for all earlier stores (stores and loads
   // share one counter).
   asm volatile("" ::"v"(cur_op), "v"(cur_link), "v"(cur_mb));
-  uint64_t t_aged = 0;
-  int prio = 0;
   for (int64_t ts = first; ts < limit; ts += kWave) {
     wave_order();
-    if constexpr (C::kChunk) {
-      if (ms_ticks && (((ts - first) >> 6) & 63) == 63) {
-        const uint64_t now = wall_clock64();
-        if (t_aged == 0) t_aged = now;
-        const uint64_t age = now - t_aged;
-        const int p = age > 16 * ms_ticks ? 3 : age > 8 * ms_ticks ? 2 : age > 4 * ms_ticks ? 1 : 0;
-        if (p != prio) {  // the priority is an immediate operand
-          prio = p;
-          if (p == 1) __builtin_amdgcn_s_setprio(1);
-          else if (p == 2) __builtin_amdgcn_s_setprio(2);
-          else if (p == 3) __builtin_amdgcn_s_setprio(3);
-        }
-      }
-    }
-    int32_t bound = INT32_MAX;  // every fourth tile: loaded with the next tile, read after this one
-    if constexpr (C::kChunk) {
-      if (c.bound && (((ts - lo) >> 6) & 3) == 0)
-        bound = __hip_atomic_load(c.bound, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
     {  // prefetch the next tile; its mailbox slots hold the blocks of allocations two or more tiles back
       const int64_t le = ts + kWave + lane;
       nxt_x = 0; nxt_c = 0; nxt_lx = 0; nxt_mb = 0;
@@ -1416,19 +1656,9 @@ __device__ __forceinline__ void chain_run(C& c, const Derived& d, const Gw& w, i
     }
     fwd_prev = fwd_cur;
     fwd_cur = 0;
-    if constexpr (C::kChunk) {
-      // another chunk of the round created segments or stopped before this one: the walk will
-      // never read this chunk's results, so it ends here and writes none
-      if (c.k_self > __builtin_amdgcn_readfirstlane(bound)) {
-        status = kAbandoned;
-        stop = ts;
-        break;
-      }
-    }
     annotate(nxt_x, nxt_c, nxt_lx, ts + kWave + lane, d.shift, &cur_op, &cur_link);
     cur_mb = nxt_mb;
   }
-  if (prio) __builtin_amdgcn_s_setprio(0);
   if (rs) {
     rs->cur = fwd_cur;
     rs->prev = fwd_prev;
@@ -1455,39 +1685,36 @@ __global__ __launch_bounds__(kWave, NP == 1 ? 6 : 3) void k_replay_fast(const in
   const Gw w = typed(ws);
   const GMEM int64_t* off = gp(off_);
   if (w.ctl[0]) return;
-  __shared__ uint64_t s_k[NP][kLdsSlots];
-  const int lane = threadIdx.x;
+  __shared__ uint64_t s_k[kTabSlots];
   const int64_t chain = blockIdx.x;
   const int64_t t = NP == 1 ? (chain >> 1) : chain;
   const int pool_one = NP == 1 ? (int)(chain & 1) : 0;  // pool of a split chain
   GMEM uint64_t* sgk = (GMEM uint64_t*)w.segs;
-  FastChain<NP> c;
-  c.base = off[t];
-  c.n = off[t + 1] - c.base;
-  const uint64_t sb = w.stop_bad[t];
+  RowChain<NP> c;
+  c.s = (LMEM uint64_t*)s_k;
+  c.base = (int64_t)uni64(off[t]);
+  c.n = (int64_t)uni64(off[t + 1]) - c.base;
+  const uint64_t sb = uni64(w.stop_bad[t]);
   const int64_t limit = sb == kNoStop ? c.n : (int64_t)(sb >> 8);
 #pragma unroll
   for (int q = 0; q < NP; ++q) {
     const int pool = NP == 1 ? pool_one : q;
-    FastPool& ps = c.p[q];
-    ps.t.l = (LMEM uint64_t*)s_k[q];
-#pragma unroll
-    for (int r = 0; r < kLdsRows; ++r) ps.t.l[64 * r + lane] = kNoKey;
-    ps.t.n = 0;
+    RowPool& ps = c.p[q];
+    rt_get(ps.t, c.s, 0, 1);
     ps.segdir = pool == 0 ? 1 : -1;
     ps.segs = pool == 0 ? sgk + c.base : sgk + c.base + c.n - 1;
     ps.nseg = 0;
     ps.bump = ps.created_u = 0;
     ps.maxfree = ps.n_mf = 0;
     ps.pool = pool;
-    ps.split_min = pool == 0 ? d.split_min_u[0] : d.split_min_u[1];
+    ps.split_min = row_split_min(d, pool);
   }
   c.reserved_u = 0;
   c.created = c.released = c.n_res = 0;
   c.back_res = NP == 1 && pool_one == 1;
   int status;
   int64_t stop;
-  chain_run<NP>(c, d, w, pool_one, 0, limit, &status, &stop);
+  row_run<NP>(c, d, w, pool_one, 0, limit, &status, &stop);
   chain_header(c, w, NP, t, pool_one, status, stop, c.p[0].n_mf, c.p[NP - 1].n_mf);
 }
 
@@ -2025,51 +2252,43 @@ __device__ __forceinline__ int fast_chunk(const Gw& w, const GMEM int64_t* off, 
   const int K = w.chunks;
   const int64_t t = chain >> 1;
   const int pool_one = (int)(chain & 1);
-  FastChain<1, true> c;
-  c.base = off[t];
-  c.n = off[t + 1] - c.base;
-  FastPool& ps = c.p[0];
-  ps.t.l = s_k;
+  RowChain<1, true> c;
+  c.s = s_k;
+  c.base = (int64_t)uni64(off[t]);
+  c.n = (int64_t)uni64(off[t + 1]) - c.base;
+  RowPool& ps = c.p[0];
   ps.segdir = 1;
   ps.segs = (GMEM uint64_t*)w.segs + c.base;  // not written in chunk mode
   ps.nseg = 0;
   ps.pool = pool_one;
-  ps.split_min = pool_one == 0 ? d.split_min_u[0] : d.split_min_u[1];
+  ps.split_min = row_split_min(d, pool_one);
   // a small-pool chunk may be certified, with its counts shifted by a delta: it
   // records every new maximum of its own from its first event on
-  ps.maxfree = pool_one == 0 ? -1 : ctl.runmax;
+  ps.maxfree = pool_one == 0 ? -1 : uni(ctl.runmax);
   ps.n_mf = 0;
-  if (ctl.f == 0) {
-#pragma unroll
-    for (int r = 0; r < kLdsRows; ++r) ps.t.l[64 * r + lane] = kNoKey;
-    ps.t.n = 0;
+  if (uni(ctl.f) == 0) {
+    rt_get(ps.t, s_k, 0, 1);
     ps.bump = ps.created_u = 0;
     c.reserved_u = 0;
     c.created = 0;
-  } else {  // the frontier's state: the end state of the chunk before it
+  } else {  // the frontier's state: the end state of the chunk before it, its keys in order
     const GMEM uint64_t* src = w.cst + (chain * K + ctl.f - 1) * kStateWords;
-    const uint64_t cw = src[kStateKeys + 3];
+    const uint64_t cw = uni64(src[kStateKeys + 3]);
     const int32_t cnt = (int32_t)(uint32_t)cw;
-    uint64_t none = kNoKey;
-    asm volatile("" : "+v"(none));  // made here: a constant held through the task loop can take a spill slot
-#pragma unroll
-    for (int r = 0; r < kLdsRows; ++r) {
-      const int32_t i = 64 * r + lane;
-      ps.t.l[i] = i < cnt ? src[i] : none;
-    }
-    ps.t.n = cnt;
-    ps.bump = src[kStateKeys];
-    ps.created_u = src[kStateKeys + 1];
-    c.reserved_u = src[kStateKeys + 2];
+    const int32_t nd = uni(ctl.nd);
+    rt_get(ps.t, src, cnt, rows_for(cnt + nd));
+    ps.bump = uni64(src[kStateKeys]);
+    ps.created_u = uni64(src[kStateKeys + 1]);
+    c.reserved_u = uni64(src[kStateKeys + 2]);
     c.created = (int32_t)(cw >> 32);
-    if (ctl.nd > 0) {  // plus the delta keys (certification left room for them) and the counters after them
+    if (nd > 0) {  // plus the delta keys (certification left room for them) and the counters after them
       const GMEM uint64_t* del = w.cdel + chain * kDeltaWords;
-      if (lane < ctl.nd && cnt + lane < kLdsSlots) ps.t.l[cnt + lane] = del[lane];
-      ps.t.n = cnt + ctl.nd;
-      ps.bump = del[kMaxDelta];
-      ps.created_u = del[kMaxDelta + 1];
-      c.reserved_u = del[kMaxDelta + 2];
-      c.created = (int32_t)del[kMaxDelta + 3];
+      const uint64_t mine = lane < nd ? del[lane] : 0;
+      for (int i = 0; i < nd && ps.t.n < kTabSlots; ++i) rt_insert_any(ps.t, rl64(mine, i));
+      ps.bump = uni64(del[kMaxDelta]);
+      ps.created_u = uni64(del[kMaxDelta + 1]);
+      c.reserved_u = uni64(del[kMaxDelta + 2]);
+      c.created = uni((int32_t)del[kMaxDelta + 3]);
     }
   }
   wave_order();
@@ -2078,7 +2297,7 @@ __device__ __forceinline__ int fast_chunk(const Gw& w, const GMEM int64_t* off, 
   c.back_res = false;
   // the chunk's records sit at the chain's own-event positions: pool 0 from the
   // front of the trace's slots, pool 1 from the back (the pools' events are disjoint)
-  const int64_t olo = w.cown[chain * (K + 1) + k];
+  const int64_t olo = uni(w.cown[chain * (K + 1) + k]);
   c.cres = (GMEM ChunkRes*)w.ovf + c.base + (pool_one ? c.n - 1 - olo : olo);
   c.cres_dir = pool_one ? -1 : 1;
   c.cmf = (GMEM MfRec*)w.segs + c.base + (pool_one ? c.n - 1 - olo : olo);
@@ -2089,7 +2308,7 @@ __device__ __forceinline__ int fast_chunk(const Gw& w, const GMEM int64_t* off, 
   int status;
   int64_t stop;
   Resume rs{-1, 0, 0};
-  chain_run<1>(c, d, w, pool_one, lo, hi, &status, &stop, KEEP ? &rs : nullptr, ms_ticks);
+  row_run<1>(c, d, w, pool_one, lo, hi, &status, &stop, KEEP ? &rs : nullptr, ms_ticks);
   if (status == kAbandoned) return 0;
   if (KEEP && status == kSpill && ctl.mode == 0 && ctl.f == 0) {
     // the first chunk outgrew the table (its state below is the one before the stopping event):
@@ -2101,9 +2320,9 @@ __device__ __forceinline__ int fast_chunk(const Gw& w, const GMEM int64_t* off, 
   }
   GMEM uint64_t* dst = w.cst + (chain * K + k) * kStateWords;
 #pragma unroll
-  for (int r = 0; r < kLdsRows; ++r) {
-    const int32_t i = 64 * r + lane;
-    if (i < ps.t.n) dst[i] = ps.t.l[i];
+  for (int r = 0; r < kTabRows; ++r) {
+    const int32_t i = lane * ps.t.rows + r;
+    if (r < ps.t.rows && i < ps.t.n) dst[i] = ps.t.k[r];
   }
   if (lane == 0) {
     dst[kStateKeys] = ps.bump;
@@ -2175,7 +2394,7 @@ __device__ __forceinline__ void stitch_walk(const Gw& w, const GMEM int64_t* off
   if (CERT && ctl.nd > 0) sf_bump = del[kMaxDelta];
   else if (BIG && ctl.f > 0) sf_bump = w.bstate[(chain * K + ctl.f - 1) * w.bstate_words];
   else if (CERT && ctl.f > 0) sf_bump = w.cst[(chain * K + ctl.f - 1) * kStateWords + kStateKeys];
-  const int32_t room = BIG ? 32 * w.bcap : kLdsSlots;  // free blocks a state certainly holds
+  const int32_t room = BIG ? 32 * w.bcap : kTabSlots;  // free blocks a state certainly holds
   int nd = 0;              // delta keys of this walk (new segments of chunk jd)
   int jd = -1;
   uint64_t dkey = kNoKey;  // lane i < nd: delta key i, in descending address order
@@ -2436,11 +2655,6 @@ __device__ __forceinline__ uint32_t q_load(const GMEM uint32_t* p) {
 __device__ __forceinline__ void q_abort(const Gw& w) {
   __hip_atomic_store(w.cqc + kQAbort, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-__device__ __forceinline__ uint64_t rfl64(uint64_t v) {
-  return (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)v) |
-         ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(v >> 32)) << 32);
-}
-
 // lane 0 only: the task of ticket t, or 0 once every chain is done (or the
 // safety limit has passed).  The limit counts from the last sign of progress
 // seen while waiting: a task queued, finished or still running (tickets below
@@ -2659,7 +2873,7 @@ __device__ __forceinline__ void sched_run(LMEM uint64_t* s_k) {
         const uint32_t t = __hip_atomic_fetch_add(w.cqc + kQHead, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         task = q_wait(w, t, A->nchains, A->limit);
       }
-      task = rfl64(task);
+      task = uni64(task);
     }
     if (task == 0) return;
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");  // the frontier the chain's last walk wrote
@@ -2675,7 +2889,7 @@ __device__ __forceinline__ void sched_run(LMEM uint64_t* s_k) {
       const Derived d = kload(&A->d);
       const int K = w.chunks;
       const CCtl ctl = gload(&w.cctl[chain]);
-      nk = w.cnum[chain];
+      nk = uni(w.cnum[chain]);
       const GMEM int32_t* bnd = w.cbound + chain * (K + 1);
       // without windows (a batch of fewer chains): a chunk of a chain's later round, which the
       // chain waits for, issues before first-round chunks on its SIMD (its priority: the round,
@@ -2684,7 +2898,7 @@ __device__ __forceinline__ void sched_run(LMEM uint64_t* s_k) {
       if (tp == 1) __builtin_amdgcn_s_setprio(1);
       else if (tp == 2) __builtin_amdgcn_s_setprio(2);
       else if (tp >= 3) __builtin_amdgcn_s_setprio(3);
-      out = fast_chunk(w, gp(A->off), d, chain, k, bnd[k], mode == 2 ? bnd[nk] : bnd[k + 1], ctl, s_k,
+      out = fast_chunk(w, gp(A->off), d, chain, k, uni(bnd[k]), uni(mode == 2 ? bnd[nk] : bnd[k + 1]), ctl, s_k,
                        WIN && mode == 1 ? w.cpend + A->nchains + chain : nullptr,
                        AGED ? A->limit / (kSchedLimitSeconds * 1000) : 0);
       if (tp) __builtin_amdgcn_s_setprio(0);
@@ -2716,7 +2930,7 @@ __device__ __forceinline__ void sched_run(LMEM uint64_t* s_k) {
 template <bool WIN>
 __global__ __launch_bounds__(kWave, 6) void k_chunk_sched(SchedArgs args) {
   (void)args;  // the first argument: at the start of the kernel-argument segment
-  __shared__ uint64_t s_k[kLdsSlots];  // the chunk's table; then the walk's delta keys
+  __shared__ uint64_t s_k[kTabSlots];  // where the chunk moves its table between row counts; then the walk's delta keys
   sched_run<WIN, false>((LMEM uint64_t*)s_k);
 }
 // Batches of few chunks per pool (fewer than 16): every task is a long part of its chain, and
@@ -2726,7 +2940,7 @@ __global__ __launch_bounds__(kWave, 6) void k_chunk_sched(SchedArgs args) {
 // about 1-2%, so they run the instances above.
 __global__ __launch_bounds__(kWave, 6) void k_chunk_sched_aged(SchedArgs args) {
   (void)args;
-  __shared__ uint64_t s_k[kLdsSlots];
+  __shared__ uint64_t s_k[kTabSlots];
   sched_run<true, true>((LMEM uint64_t*)s_k);
 }
 
@@ -2789,10 +3003,6 @@ static_assert(2 * (int64_t)(kBigDir1 + 2) * kPage <= kBigSlotKeys, "slot holds b
 static_assert(kBigDir1 <= 64 * kWave, "one summary register covers the directory");
 static_assert(kBigSlotKeys == kBigSlotKeysHost && kBigSlots == 64, "the workspace carving matches this layout");
 
-__device__ __forceinline__ uint32_t uni(uint32_t v) { return __builtin_amdgcn_readfirstlane(v); }
-__device__ __forceinline__ uint64_t uni64(uint64_t v) {
-  return (uint64_t)uni((uint32_t)v) | ((uint64_t)uni((uint32_t)(v >> 32)) << 32);
-}
 __device__ __forceinline__ int msb64(uint64_t m) { return 63 - __builtin_clzll(m); }
 
 struct Pss {
@@ -3090,13 +3300,11 @@ struct BigChain {
   int64_t base, n;
   bool back_res;
   LMEM uint64_t* stage;  // 2 kPage + 2 keys of LDS for page merges and splits
-  GMEM ChunkRes* cres;   // chunk mode, as for FastChain
+  GMEM ChunkRes* cres;   // chunk mode, as for RowChain
   int cres_dir;
   GMEM MfRec* cmf;
   int cmf_dir;
   uint32_t g;            // chunk mode: lane b, the largest block chosen for a request of bucket b (gbucket)
-  const GMEM int32_t* bound;  // as for FastChain; the paged chunks' rounds never set it
-  int32_t k_self;
 };
 
 // Section 3.4 (iv)-(v) on the paged sets: units held by idle segments of both pools
@@ -3387,8 +3595,6 @@ __device__ __forceinline__ void big_chunk(const Gw& w, const GMEM int64_t* off, 
   c.cres_dir = pool_one ? -1 : 1;
   c.cmf = (GMEM MfRec*)w.segs + c.base + (pool_one ? c.n - 1 - olo : olo);
   c.cmf_dir = pool_one ? -1 : 1;
-  c.bound = nullptr;
-  c.k_self = k;
   int status = kRetry;
   int64_t stop = lo;
   if (loaded) chain_run<1>(c, d, w, pool_one, lo, hi, &status, &stop, &rs);
@@ -3415,7 +3621,7 @@ __global__ __launch_bounds__(kWave) void k_replay_combo(const int64_t* off_, int
   __shared__ uint64_t s_dkey[2][kBigDir1 + 2];
   __shared__ uint32_t s_dpg[2][kBigDir1 + 2];
   __shared__ uint64_t s_stage[2 * kPage + 2];
-  static_assert(sizeof(s_dkey[0]) >= sizeof(uint64_t) * kLdsRows * 64, "the LDS table fits in a directory");
+  static_assert(sizeof(s_dkey[0]) >= sizeof(uint64_t) * kTabSlots, "a row table's keys fit in a directory");
   const Gw w = typed(ws);
   const GMEM int64_t* off = gp(off_);
   if (w.ctl[0]) return;
@@ -3434,7 +3640,7 @@ __global__ __launch_bounds__(kWave) void k_replay_combo(const int64_t* off_, int
     big_chunk(w, off, d, chain, k, lo, hi, ctl, (LMEM uint64_t*)s_dkey[0], (LMEM uint64_t*)s_dkey[1],
               (LMEM uint32_t*)s_dpg[0], (LMEM uint32_t*)s_dpg[1], (LMEM uint64_t*)s_stage);
   else
-    fast_chunk<true>(w, off, d, chain, k, lo, hi, ctl, (LMEM uint64_t*)s_dkey[0]);
+    fast_chunk<true>(w, off, d, chain, k, uni((int32_t)lo), uni((int32_t)hi), ctl, (LMEM uint64_t*)s_dkey[0]);
 }
 
 // After each k_replay_combo round: the walk of k_chunk_stitch in each chain's

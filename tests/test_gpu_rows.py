@@ -1,0 +1,99 @@
+"""Parity of the row tables (a pool's free blocks sorted in registers, on 1, 2, 3, 4, 6, 8 or 12
+rows of 64) with the CPU oracle, bit-exact: free counts that cross and settle on every row
+boundary, runs of allocations freed at once (skipped when a cached block fits them), and
+reclamation from tables of several rows."""
+import numpy as np
+import pytest
+
+import oracle
+from evw import A, F, KiB, MiB
+from gpu_util import check
+from spill_traces import batch
+
+pytestmark = pytest.mark.gpu
+
+P = oracle.paper_params()
+PT = oracle.pytorch_like_params()
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _gpu():
+    import torch
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    import paper_2510_21048_amd as xm
+    xm.load()
+    yield
+
+
+def around(seed: int, holes: int, large: bool, churn: int = 400, pairs: bool = True) -> np.ndarray:
+    """`holes` free blocks that cannot coalesce, then random allocations and frees that keep the
+    free count around it (some allocations freed by the very next event, of sizes up to past every
+    free block), then everything freed but a few blocks."""
+    rng = np.random.default_rng(seed)
+    unit, top = (MiB + 512, 6 * MiB) if large else (512, 24 * KiB)
+    size = lambda: int(rng.integers(unit, top))
+    ev = [A(size()) for _ in range(2 * holes + 1)]
+    live = list(range(0, 2 * holes + 1, 2))
+    gone = list(range(1, 2 * holes + 1, 2))
+    rng.shuffle(gone)
+    ev += [F(h) for h in gone]
+    for _ in range(churn):
+        r = rng.random()
+        if pairs and r < 0.4:  # freed at once: usually fits, sometimes needs a new segment
+            big = rng.random() < 0.1
+            ev.append(A(top * 4 if big and large else MiB if big else size()))
+            ev.append(F(len(ev) - 1))
+        elif r < 0.7 or not live:
+            live.append(len(ev))
+            ev.append(A(size()))
+        else:
+            k = int(rng.integers(len(live)))
+            live[k], live[-1] = live[-1], live[k]
+            ev.append(F(live.pop()))
+    rng.shuffle(live)
+    ev += [F(h) for h in live[3:]]
+    return np.array(ev, dtype=np.uint64)
+
+
+@pytest.mark.parametrize("large", [False, True])
+@pytest.mark.parametrize("params", [P, PT], ids=["paper", "pytorch_like"])
+@pytest.mark.parametrize("chunks", [0, 1])
+def test_every_row_boundary(params, large, chunks):
+    holes = [0, 1, 62, 63, 64, 65, 104, 127, 128, 129, 191, 193, 255, 256, 257, 383, 385, 511, 513, 766, 767, 768, 769]
+    ev, off = batch([around(100 + h, h, large) for h in holes])
+    check(ev, off, params, chunks=chunks, what=f"row boundaries large={large}")
+
+
+@pytest.mark.parametrize("gap", [0, 1, 61, 62, 63, 64, 65])
+def test_pairs_across_a_tile(gap):
+    """Allocation/free pairs at every place of the 64-event tiles, split by a tile boundary, with
+    the other pool's pairs inside them, and runs that stop at one that needs a new segment."""
+    ev = [A(1 * KiB)] * gap
+    for i in range(200):
+        ev += [A(2 * KiB + 512 * (i % 7)), F(len(ev))]
+        if i % 3 == 0:
+            n = len(ev)
+            ev += [A(600), A(3 * MiB), F(n + 1), F(n)]
+        if i % 50 == 49:
+            ev += [A(MiB), A(MiB), F(len(ev))]
+    ev, off = batch([np.array(ev, dtype=np.uint64)])
+    check(ev, off, P, what=f"pairs, {gap} events before")
+    check(ev, off, dict(P, device_capacity_bytes=64 * MiB), what=f"pairs under a capacity, {gap} events before")
+
+
+@pytest.mark.parametrize("holes", [3, 64, 130, 300, 600])
+def test_reclaim_from_rows(holes):
+    """Idle segments released from tables of one to twelve rows in both pools, among fragments that
+    stay; then the pools grow again, up to OOM."""
+    n = holes + 1
+    ev = [A(MiB)] * (2 * n)                                       # two to a segment
+    ev += [F(i) for i in range(0, 2 * n, 2)]                      # fragments: no segment idle
+    ev += [F(i) for i in range(1, n, 2)]                          # half of the segments idle
+    s = len(ev)
+    ev += [A(15 * MiB)] * 8
+    ev += [F(s + i) for i in (1, 2, 5)]
+    ev += [A((11 + i) * MiB) for i in range(40)]                  # past the capacity: reclaim, reuse, OOM at last
+    ev, off = batch([np.array(ev, dtype=np.uint64)])
+    cap = (2 * n + 8 * 16 + 100) * MiB
+    g, _ = check(ev, off, dict(P, device_capacity_bytes=cap), what=f"reclaim, {holes} fragments")
+    assert int(g["segments_released"][0]) > 0 and int(g["status"][0]) == 1
