@@ -915,17 +915,18 @@ __device__ __forceinline__ int64_t event_delta(const Gw& w, int64_t base, int64_
 // Sizes stay below kRowLimit, so a key is also a non-negative finite double in
 // the same order, and an insertion is one v_max_f64 and one v_min_f64 per row:
 //   with v inserted, place p holds min(x[p], max(x[p - 1], v)).
-// The slots past the count hold kEmptyKey, above every key.  A chain hands
+// The slots past the count hold kEmptyKey, above every key; one is always left, so
+// that a search always ends at a key or there.  A chain hands
 // itself over when a pool would need more free blocks than the rows hold (status
 // kSpill, to the paged chain kernel) or when sizes or addresses reach kRowLimit
 // units (status kRetry, to the 64-bit chain kernel); either replays it again.
 constexpr int kTabRows = 12;
-constexpr int32_t kTabSlots = kTabRows * 64;
+constexpr int32_t kTabSlots = kTabRows * 64 - 1;
 constexpr uint64_t kFastLimit = 1ull << 31;  // the paged chains' sizes and addresses
 constexpr uint32_t kEmptyHi = 0x7fe00000u;   // a finite double above every key
 constexpr uint64_t kEmptyKey = (uint64_t)kEmptyHi << 32;
 constexpr uint64_t kRowLimit = kEmptyHi;
-static_assert(kStateKeys == kTabSlots, "a chunk state holds a full table");
+static_assert(kStateKeys >= kTabSlots, "a chunk state holds a full table");
 constexpr uint64_t kNoKey = ~0ull;
 constexpr int kRetry = 0x40;
 constexpr int kSpill = 0x41;
@@ -963,88 +964,77 @@ extern "C" __device__ int xmem_llvm_writelane(int val, int lane, int v) __asm("l
 __device__ __forceinline__ uint32_t wl(uint32_t val, uint32_t lane, uint32_t v) {
   return (uint32_t)xmem_llvm_writelane((int)val, (int)lane, (int)v);
 }
-// the lowest set lane of a mask (lane 63 when there is none)
-__device__ __forceinline__ int first_lane(uint64_t m) { return __builtin_ctzll(m | (1ull << 63)); }
-
 struct RTab {
   uint64_t k[kTabRows];  // rows 0 .. rows - 1 are in use
   int32_t n, rows;
 };
 typedef uint64_t Keys[kTabRows];
 
-// k = min(k, m) / max(k, m) in k's own registers (left to itself the compiler writes the new keys
-// beside the old ones and copies them back where the event paths join, which doubles the table's
-// registers); rt_settle: two wait states before a DPP move may read them
-__device__ __forceinline__ void kmin_to(uint64_t& k, uint64_t m) { asm("v_min_f64 %0, %0, %1" : "+v"(k) : "v"(m)); }
-__device__ __forceinline__ void kmax_to(uint64_t& k, uint64_t m) { asm("v_max_f64 %0, %0, %1" : "+v"(k) : "v"(m)); }
-__device__ __forceinline__ void rt_settle(uint64_t& k) { asm("s_nop 1" : "+v"(k)); }
 __device__ __forceinline__ uint64_t with_hi(uint64_t k, uint32_t hi) { return ((uint64_t)hi << 32) | lo32(k); }
+// this lane's bit of a wave-uniform mask
+__device__ __forceinline__ bool lane_bit(uint64_t m) { return __builtin_amdgcn_inverse_ballot_w64(m); }
 
 // v (not present) inserted; room for it checked by the caller
 template <int R>
 __device__ __forceinline__ void rt_insert(Keys& k, uint64_t v) {
   const uint64_t y0 = key_below(k[R - 1]);
 #pragma unroll
-  for (int r = R - 1; r >= 0; --r) kmin_to(k[r], kmax(r > 0 ? k[r > 0 ? r - 1 : 0] : y0, v));
-  rt_settle(k[R - 1]);
+  for (int r = R - 1; r >= 0; --r) k[r] = kmin(k[r], kmax(r > 0 ? k[r > 0 ? r - 1 : 0] : y0, v));
 }
-// The present key x replaced by the smaller v: as an insertion, but only up to x's place (a place
-// past it, whose lower neighbour is x or above, takes the minimum with something above every key;
-// only the high half has to say so).
+// The present key x, in lane at, replaced by the smaller v: as an insertion, but only up to x's
+// place (a place past it, whose lower neighbour is x or above, takes the minimum with something
+// above every key; only the high half has to say so).  In one row the lane is the place.
 template <int R>
-__device__ __forceinline__ void rt_lower(Keys& k, uint64_t x, uint64_t v) {
+__device__ __forceinline__ void rt_lower(Keys& k, uint64_t x, int at, uint64_t v) {
   const uint64_t y0 = key_below(k[R - 1]);
 #pragma unroll
   for (int r = R - 1; r >= 0; --r) {
     const uint64_t y = r > 0 ? k[r > 0 ? r - 1 : 0] : y0;
     const uint64_t m = kmax(y, v);
-    kmin_to(k[r], with_hi(m, y >= x ? kEmptyHi : hi32(m)));
+    k[r] = kmin(k[r], with_hi(m, (R == 1 ? lane_bit(~1ull << at) : y >= x) ? kEmptyHi : hi32(m)));
   }
-  rt_settle(k[R - 1]);
 }
-// The present key x replaced by the larger v (kEmptyKey: removed): the mirror image, from x's place
-// on (a place before it takes the maximum with something below every key).
+// The present key x, in lane at, replaced by the larger v (kEmptyKey: removed): the mirror image,
+// from x's place on (a place before it takes the maximum with something below every key).
 template <int R>
-__device__ __forceinline__ void rt_raise(Keys& k, uint64_t x, uint64_t v) {
+__device__ __forceinline__ void rt_raise(Keys& k, uint64_t x, int at, uint64_t v) {
   const uint64_t zl = key_above(k[0]);
 #pragma unroll
   for (int r = 0; r < R; ++r) {
     const uint64_t z = r < R - 1 ? k[r + 1 < kTabRows ? r + 1 : 0] : zl;
     const uint64_t m = kmin(z, v);
-    kmax_to(k[r], with_hi(m, k[r] < x ? 0 : hi32(m)));
+    k[r] = kmax(k[r], with_hi(m, (R == 1 ? lane_bit(~0ull << at) : k[r] >= x) ? hi32(m) : 0));
   }
-  rt_settle(k[0]);
 }
+// the smallest key of size >= u (0 < u < kRowLimit), kEmptyKey when there is none; *at: its lane
 template <int R>
-__device__ __forceinline__ void rt_delete(Keys& k, uint64_t x) {
-  rt_raise<R>(k, x, kEmptyKey);
-}
-// the smallest key of size >= u (0 < u < kRowLimit); a key whose size is below u, or kEmptyKey,
-// when there is none
-template <int R>
-__device__ __forceinline__ uint64_t rt_first_fit(const Keys& k, uint32_t u) {
+__device__ __forceinline__ uint64_t rt_first_fit(const Keys& k, uint32_t u, int* at) {
   uint64_t v = k[R - 1];  // per lane: its smallest key that fits
 #pragma unroll
   for (int r = R - 2; r >= 0; --r) v = hi32(k[r]) >= u ? k[r] : v;
-  return rl64(v, first_lane(ballot(hi32(k[R - 1]) >= u)));
+  *at = __builtin_ctzll(ballot(hi32(k[R - 1]) >= u));
+  return rl64(v, *at);
 }
-// sizes of the free blocks ending at a and starting at e (0: none); each is unique
+// The free blocks ending at a and starting at e (each is unique, if there): a mask of the lane that
+// holds one, and in that lane its size.
+struct Near { uint64_t left, right; uint32_t ls, rs; };
 template <int R>
-__device__ __forceinline__ void rt_neighbours(const Keys& k, uint32_t a, uint32_t e, uint32_t* left, uint32_t* right) {
+__device__ __forceinline__ Near rt_neighbours(const Keys& k, uint32_t a, uint32_t e) {
+  if constexpr (R == 1)
+    return Near{ballot(lo32(k[0]) + hi32(k[0]) == a), ballot(lo32(k[0]) == e), hi32(k[0]), hi32(k[0])};
   uint32_t l = 0, g = 0;
 #pragma unroll
   for (int r = 0; r < R; ++r) {
     l = lo32(k[r]) + hi32(k[r]) == a ? hi32(k[r]) : l;
     g = lo32(k[r]) == e ? hi32(k[r]) : g;
   }
-  *left = rl(l, first_lane(ballot(l != 0)));
-  *right = rl(g, first_lane(ballot(g != 0)));
+  return Near{ballot(l != 0), ballot(g != 0), l, g};
 }
 
 // The row counts in use, and the smallest that holds n keys.  (Each is an instance of the event
 // code below; a count between two of them runs on the larger.)
 __device__ __forceinline__ int rows_for(int32_t n) {
-  return n <= 64 ? 1 : n <= 128 ? 2 : n <= 192 ? 3 : n <= 256 ? 4 : n <= 384 ? 6 : n <= 512 ? 8 : kTabRows;
+  return n < 64 ? 1 : n < 128 ? 2 : n < 192 ? 3 : n < 256 ? 4 : n < 384 ? 6 : n < 512 ? 8 : kTabRows;
 }
 // at a tile's end a table moves to fewer rows once it would leave a quarter row of them free
 __device__ __forceinline__ int rows_shrunk(int32_t n, int rows) {
@@ -1112,7 +1102,7 @@ template <int NP, bool CH = false>
 struct RowChain {
   static constexpr bool kChunk = CH;
   RowPool p[NP];
-  LMEM uint64_t* s;  // kTabSlots keys of LDS, for moving a table between row counts
+  LMEM uint64_t* s;  // 64 kTabRows keys of LDS, for moving a table between row counts
   uint64_t reserved_u;
   int32_t created, released, n_res;
   int64_t base, n;
@@ -1250,11 +1240,11 @@ __device__ __forceinline__ void row_release_idle(RowChain<NP, CH>& c) {
 
 // A 64-event tile of the trace, each lane its event.
 struct RowTile {
-  uint32_t op;        // an allocation: its units; a free: kRowFree
+  uint32_t op;        // an allocation: its units; a free: kRowFree; an allocation freed next: both
   uint32_t dst;       // an allocation: the lane of its free when that lies in the tile, else its own
   uint32_t pair;      // an allocation whose free is the chain's very next event, and that free: the units; else ~0
   uint32_t ba, bs;    // block (address, size): of a free, to release; of an allocation freed past the tile
-  uint64_t pairs;     // lanes of such allocations
+                      // (the size from the start: the units, but for a block handed out whole)
 };
 constexpr uint32_t kRowFree = 1u << 31;
 
@@ -1276,54 +1266,72 @@ __device__ __forceinline__ bool row_events(Keys& k, int32_t& n, const int32_t ro
   do {
     const int j = __builtin_ctzll(todo);
     const uint32_t op = rl(T.op, j);
-    uint64_t next = todo & (todo - 1);
+    asm("s_bitset0_b64 %0, %1" : "+s"(todo) : "s"(j));
     if (!(op & kRowFree)) {
-      const uint64_t b = rt_first_fit<R>(k, op);
-      const uint32_t a = lo32(b), left = hi32(b) - op;
-      if (left < kEmptyHi - op) {
-        if (!(T.pairs & (todo ^ next))) {
-          uint32_t size = op;
-          if (left >= split_min) {
-            rt_lower<R>(k, b, key_of32(left, a + op));
-          } else {
-            rt_delete<R>(k, b);
-            n -= 1;
-            size = hi32(b);
-          }
-          const uint32_t to = rl(T.dst, j);
-          T.ba = wl(a, to, T.ba);
-          T.bs = wl(size, to, T.bs);
-        } else if (ONE && R == 1) {
-          const uint32_t most = rl(hi32(k[0]), n - 1);
-          const uint64_t stay = todo & ~ballot(T.pair <= most);
-          next = stay ? todo & (~0ull << __builtin_ctzll(stay)) : 0;
+      int at;
+      const uint64_t b = rt_first_fit<R>(k, op, &at);
+      if (hi32(b) != kEmptyHi) {
+        const uint32_t a = lo32(b), left = hi32(b) - op, to = rl(T.dst, j);
+        if (left >= split_min) {
+          rt_lower<R>(k, b, at, key_of32(left, a + op));
         } else {
-          next &= next - 1;
-        }
-      } else {
-        rest = todo;
-        next = 0;
-      }
-    } else {
-      const uint32_t a = rl(T.ba, j), s = rl(T.bs, j), e = a + s;
-      uint32_t ls, rs;
-      rt_neighbours<R>(k, a, e, &ls, &rs);
-      const uint64_t v = key_of32(s + ls + rs, a - ls);
-      if (ls | rs) {
-        if (ls != 0 && rs != 0) {
-          rt_delete<R>(k, key_of32(rs, e));
+          rt_raise<R>(k, b, at, kEmptyKey);
           n -= 1;
+          if (left) T.bs = wl(hi32(b), to, T.bs);
         }
-        rt_raise<R>(k, ls ? key_of32(ls, a - ls) : key_of32(rs, e), v);
+        T.ba = wl(a, to, T.ba);
+      } else {
+        rest = todo | (1ull << j);
+        todo = 0;
+      }
+    } else if (op == kRowFree) {
+      uint32_t a = rl(T.ba, j), s = rl(T.bs, j);
+      const uint32_t e = a + s;
+      const Near q = rt_neighbours<R>(k, a, e);
+      if (q.left | q.right) {
+        uint64_t x;
+        int at;
+        if (q.left) {
+          at = __builtin_ctzll(q.left);
+          const uint32_t ls = rl(q.ls, at);
+          a -= ls;
+          s += ls;
+          x = key_of32(ls, a);
+          if (q.right) {
+            const int at2 = __builtin_ctzll(q.right);
+            const uint32_t rs = rl(q.rs, at2);
+            rt_raise<R>(k, key_of32(rs, e), at2, kEmptyKey);
+            n -= 1;
+            s += rs;
+            at -= (int)((uint32_t)(at2 - at) >> 31);  // one row: the keys past the removed one moved down a lane
+          }
+        } else {
+          at = __builtin_ctzll(q.right);
+          const uint32_t rs = rl(q.rs, at);
+          x = key_of32(rs, e);
+          s += rs;
+        }
+        rt_raise<R>(k, x, at, key_of32(s, a));
       } else if (n < room) {
-        rt_insert<R>(k, v);
+        rt_insert<R>(k, key_of32(s, a));
         n += 1;
       } else {
-        rest = todo;
-        next = 0;
+        rest = todo | (1ull << j);
+        todo = 0;
+      }
+    } else {
+      int at;
+      if (hi32(rt_first_fit<R>(k, op & ~kRowFree, &at)) == kEmptyHi) {
+        rest = todo | (1ull << j);
+        todo = 0;
+      } else if (ONE && R == 1) {
+        const uint32_t most = rl(hi32(k[0]), n - 1);
+        const uint64_t stay = todo & ~ballot(T.pair <= most);
+        todo = stay ? todo & (~0ull << __builtin_ctzll(stay)) : 0;
+      } else {
+        todo &= todo - 1;
       }
     }
-    todo = next;
   } while (todo);
   todo = rest;
   return rest != 0;
@@ -1331,7 +1339,7 @@ __device__ __forceinline__ bool row_events(Keys& k, int32_t& n, const int32_t ro
 template <bool ONE>
 __device__ __forceinline__ bool row_events_any(RowPool& ps, RowTile& T, uint64_t& todo) {
   Keys& k = ps.t.k;
-  const int32_t full = 64 * ps.t.rows, room = ps.maxfree < full ? ps.maxfree : full;
+  const int32_t full = 64 * ps.t.rows - 1, room = ps.maxfree < full ? ps.maxfree : full;
   switch (ps.t.rows) {
     case 1: return row_events<1, ONE>(k, ps.t.n, room, ps.split_min, T, todo);
     case 2: return row_events<2, ONE>(k, ps.t.n, room, ps.split_min, T, todo);
@@ -1350,9 +1358,9 @@ __device__ __forceinline__ bool row_events_any(RowPool& ps, RowTile& T, uint64_t
 template <int NP, bool CH>
 __device__ __forceinline__ int row_slow_event(RowChain<NP, CH>& c, RowPool& ps, const Derived& d, const Gw& w, int64_t e,
                                               int j, RowTile& T) {
-  const uint32_t op = rl(T.op, j);
+  const uint32_t word = rl(T.op, j), op = word & ~kRowFree;
   uint64_t v = 0;
-  if (!(op & kRowFree)) {
+  if (word != kRowFree) {
     if (op >= kRowLimit) return kRetry;
     const uint64_t S = segment_units(d, ps.pool, op);
     if (ps.created_u + S > d.limit_u) return XMEM_T_OVERFLOW;
@@ -1382,7 +1390,7 @@ __device__ __forceinline__ int row_slow_event(RowChain<NP, CH>& c, RowPool& ps, 
     v = key_of32(rl(T.bs, j), rl(T.ba, j));
   }
   if (v) {
-    if (ps.t.n == 64 * ps.t.rows) rt_rows(ps.t, rows_for(ps.t.n + 1), c.s);
+    if (ps.t.n == 64 * ps.t.rows - 1) rt_rows(ps.t, rows_for(ps.t.n + 1), c.s);
     rt_insert_any(ps.t, v);
   }
   record_free_count(c, ps, w, e);
@@ -1407,10 +1415,10 @@ struct Resume { int64_t from; uint64_t cur, prev; };
 // Bound by the latency of each event's chain of dependent instructions (a lone wavefront: 7 to 9
 // cycles each) or by vector issue (six on a SIMD), not by memory; so everything about an event that
 // does not depend on the table is made by vector steps per tile, and an event on one row takes
-// about 40 instructions.  Against the table before it (unordered keys in LDS, searched by a
+// about 30 instructions.  Against the table before it (unordered keys in LDS, searched by a
 // wavefront minimum, about 150 instructions an event): 1,024 GPT-shaped traces of 262,144 events
-// 33.4 -> 17.7 ms a step, 64 ResNet-shaped traces of 65,536 events replayed serially under a
-// capacity 32.2 -> 16.3 ms, a 4,096-event MLP trace, nearly all pairs, 1.11 -> 0.09 ms.  A block travels to its free in the registers of the
+// 33.4 -> 16.4 ms a step, 64 ResNet-shaped traces of 65,536 events replayed serially under a
+// capacity 32.2 -> 13.7 ms, a 4,096-event MLP trace, nearly all pairs, 1.11 -> 0.09 ms.  A block travels to its free in the registers of the
 // free's own lane: from an allocation of the tile directly, from the last tile by one permutation,
 // from before that through the free's mailbox slot.
 //
@@ -1478,16 +1486,16 @@ __device__ __forceinline__ void row_run(RowChain<NP, CH>& c, const Derived& d, c
       const uint32_t hd = (uint32_t)x - t32;
       const bool last = (uint32_t)(hd + kWave) < kWave;
       const uint32_t ga = lane_get(T.ba, hd), gs = lane_get(T.bs, hd);  // the last tile's lane hd + 64
+      const uint32_t gu = lane_get(u, hd);  // in this tile: its units
       T.ba = last ? ga : lo32(mb);
-      T.bs = last ? gs : hi32(mb);
-      T.op = alloc ? u : kRowFree;
+      T.bs = alloc ? u : hd < kWave ? gu : last ? gs : hi32(mb);
       T.dst = near ? rel : (uint32_t)lane;
       const uint64_t after = (own_m >> lane) >> 1;  // the chain's events past this one
       const bool pair = near && after != 0 && (uint32_t)(lane + 1 + __builtin_ctzll(after | (1ull << 63))) == rel;
-      const uint32_t pu = pair ? u : 0xffffffffu;
-      const uint32_t pf = lane_get(pu, hd);
-      T.pair = alloc ? pu : own && hd < kWave ? pf : 0xffffffffu;
-      T.pairs = ballot(pair);
+      const uint64_t pairs = ballot(pair);
+      const bool freed = own && !alloc && hd < kWave && ((pairs >> (hd & 63)) & 1);  // the free of one of them
+      T.pair = pair || freed ? T.bs : 0xffffffffu;
+      T.op = alloc ? (pair ? kRowFree : 0u) | u : kRowFree;
     }
     uint64_t nx = 0, nmb = 0;
     uint32_t ncd = 0, nlx = 0;
@@ -1685,7 +1693,7 @@ __global__ __launch_bounds__(kWave, NP == 1 ? 6 : 3) void k_replay_fast(const in
   const Gw w = typed(ws);
   const GMEM int64_t* off = gp(off_);
   if (w.ctl[0]) return;
-  __shared__ uint64_t s_k[kTabSlots];
+  __shared__ uint64_t s_k[64 * kTabRows];
   const int64_t chain = blockIdx.x;
   const int64_t t = NP == 1 ? (chain >> 1) : chain;
   const int pool_one = NP == 1 ? (int)(chain & 1) : 0;  // pool of a split chain
@@ -2930,7 +2938,7 @@ __device__ __forceinline__ void sched_run(LMEM uint64_t* s_k) {
 template <bool WIN>
 __global__ __launch_bounds__(kWave, 6) void k_chunk_sched(SchedArgs args) {
   (void)args;  // the first argument: at the start of the kernel-argument segment
-  __shared__ uint64_t s_k[kTabSlots];  // where the chunk moves its table between row counts; then the walk's delta keys
+  __shared__ uint64_t s_k[64 * kTabRows];  // where the chunk moves its table between row counts; then the walk's delta keys
   sched_run<WIN, false>((LMEM uint64_t*)s_k);
 }
 // Batches of few chunks per pool (fewer than 16): every task is a long part of its chain, and
@@ -2940,7 +2948,7 @@ __global__ __launch_bounds__(kWave, 6) void k_chunk_sched(SchedArgs args) {
 // about 1-2%, so they run the instances above.
 __global__ __launch_bounds__(kWave, 6) void k_chunk_sched_aged(SchedArgs args) {
   (void)args;
-  __shared__ uint64_t s_k[kTabSlots];
+  __shared__ uint64_t s_k[64 * kTabRows];
   sched_run<true, true>((LMEM uint64_t*)s_k);
 }
 
@@ -3621,7 +3629,7 @@ __global__ __launch_bounds__(kWave) void k_replay_combo(const int64_t* off_, int
   __shared__ uint64_t s_dkey[2][kBigDir1 + 2];
   __shared__ uint32_t s_dpg[2][kBigDir1 + 2];
   __shared__ uint64_t s_stage[2 * kPage + 2];
-  static_assert(sizeof(s_dkey[0]) >= sizeof(uint64_t) * kTabSlots, "a row table's keys fit in a directory");
+  static_assert(sizeof(s_dkey[0]) >= sizeof(uint64_t) * 64 * kTabRows, "a row table's keys fit in a directory");
   const Gw w = typed(ws);
   const GMEM int64_t* off = gp(off_);
   if (w.ctl[0]) return;
