@@ -366,6 +366,43 @@ __device__ __forceinline__ void gstore(GMEM T* p, const T& v) {
   for (size_t i = 0; i < sizeof(T) / 8; ++i) q[i] = d[i];
 }
 
+// What one task of the chunk scheduler writes for another (states, headers, records, control words):
+// each 8 bytes an agent-scope access, which goes past the XCD's L2 where the XCDs share memory, so
+// no task has to write a whole L2 back or invalidate it.  cst/cld: one word, ast/ald: a struct.
+__device__ __forceinline__ void cst(GMEM uint64_t* p, uint64_t v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ uint64_t cld(const GMEM uint64_t* p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+template <class T>
+__device__ __forceinline__ T ald(const GMEM T* p) {
+  static_assert(sizeof(T) % 8 == 0, "8-byte multiple");
+  T v;
+  const GMEM uint64_t* q = (const GMEM uint64_t*)p;
+  uint64_t* d = reinterpret_cast<uint64_t*>(&v);
+#pragma unroll
+  for (size_t i = 0; i < sizeof(T) / 8; ++i) d[i] = cld(q + i);
+  return v;
+}
+template <class T>
+__device__ __forceinline__ void ast(GMEM T* p, const T& v) {
+  static_assert(sizeof(T) % 8 == 0, "8-byte multiple");
+  GMEM uint64_t* q = (GMEM uint64_t*)p;
+  const uint64_t* d = reinterpret_cast<const uint64_t*>(&v);
+#pragma unroll
+  for (size_t i = 0; i < sizeof(T) / 8; ++i) cst(q + i, d[i]);
+}
+// Every such store of this wavefront is done: what it stores after this is seen after them.  (An
+// agent-scope release fence would do as well, but it writes back the XCD's whole L2, and the
+// acquire that pairs with it invalidates it: with a few fences a microsecond on each XCD, the
+// other wavefronts' tile loads kept missing.  256 ResNet-shaped traces of 65,536 events 2.89 ->
+// 2.10 ms a step, 1,024 GPT-shaped ones of 262,144 16.4 -> 15.2 ms.)
+__device__ __forceinline__ void stores_done() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+// What follows is read after what was read (a task word, a count) to get here: such loads issue in
+// program order, and their addresses or the branch to them depend on it; only the compiler is held.
+__device__ __forceinline__ void loads_after() { asm volatile("" ::: "memory"); }
+
 __device__ __forceinline__ Gw typed(const Ws& w) {
   return Gw{gp(w.ctl),  gp(w.tile_base), gp(w.tile_part), gp(w.tinfo), gp(w.stop_bad), gp(w.hdr),  gp(w.code),
             gp(w.lx),   gp(w.ev),        gp(w.mbox),      gp(w.res),       gp(w.mf),       gp(w.ovf),  gp(w.segs),
@@ -1049,7 +1086,8 @@ __device__ __forceinline__ void rt_put(const RTab& t, LMEM uint64_t* s) {
     if (r < t.rows) s[lane * t.rows + r] = t.k[r];
   wave_order();
 }
-template <class P>
+// (SHARED: s is another task's state in global memory)
+template <bool SHARED = false, class P>
 __device__ __forceinline__ void rt_get(RTab& t, P s, int32_t n, int rows) {
   const int lane = threadIdx.x;
   t.n = n;
@@ -1058,7 +1096,10 @@ __device__ __forceinline__ void rt_get(RTab& t, P s, int32_t n, int rows) {
   asm volatile("" : "+v"(none));  // made here: a constant held through the event loop can take a spill slot
 #pragma unroll
   for (int r = 0; r < kTabRows; ++r)
-    if (r < rows) t.k[r] = lane * rows + r < n ? s[lane * rows + r] : none;
+    if (r < rows) {
+      if constexpr (SHARED) t.k[r] = lane * rows + r < n ? cld(s + lane * rows + r) : none;
+      else t.k[r] = lane * rows + r < n ? s[lane * rows + r] : none;
+    }
 }
 __device__ __forceinline__ void rt_rows(RTab& t, int rows, LMEM uint64_t* s) {
   rt_put(t, s);
@@ -1139,7 +1180,7 @@ template <class C>
 __device__ __forceinline__ void record_reserved(C& c, const Gw& w, int64_t e, int shift) {
   if (threadIdx.x == 0) {
     if constexpr (C::kChunk) {
-      gstore(&c.cres[(int64_t)c.cres_dir * c.n_res], ChunkRes{(int64_t)(c.reserved_u << shift), (int32_t)e, c.created});
+      ast(&c.cres[(int64_t)c.cres_dir * c.n_res], ChunkRes{(int64_t)(c.reserved_u << shift), (int32_t)e, c.created});
     } else {
       const int64_t slot = c.back_res ? c.base + c.n - 1 - c.n_res : c.base + c.n_res;
       gstore(&w.res[slot], ResRec{(int64_t)(c.reserved_u << shift), (int32_t)e, c.created, c.released, 0});
@@ -1154,7 +1195,7 @@ __device__ __forceinline__ void record_free_count(C& c, P& ps, const Gw& w, int6
     ps.maxfree = nf;
     if (threadIdx.x == 0) {
       if constexpr (C::kChunk) {
-        gstore(&c.cmf[(int64_t)c.cmf_dir * ps.n_mf], MfRec{(int32_t)e, nf});
+        ast(&c.cmf[(int64_t)c.cmf_dir * ps.n_mf], MfRec{(int32_t)e, nf});
       } else {
         const int64_t slot = ps.pool == 1 ? c.base + c.n - 1 - ps.n_mf : c.base + ps.n_mf;
         gstore(&w.mf[slot], MfRec{(int32_t)e, nf});
@@ -1545,7 +1586,11 @@ __device__ __forceinline__ void row_run(RowChain<NP, CH>& c, const Derived& d, c
     asm volatile("" ::"v"(nx), "v"(ncd), "v"(nlx), "v"(nmb));  // loaded by now
     // every allocation of the tile whose free lies two or more tiles ahead: its block to the
     // free's mailbox slot, all in one vector store (ordered before the next tile's loads)
-    if (far) mkey[c.base + fe] = key_of32(T.bs, T.ba);
+    if (far) {
+      // (a chunk: past the L2, where a line left dirty could be written over a later run's on another XCD)
+      if (CH) cst(mkey + c.base + fe, key_of32(T.bs, T.ba));
+      else mkey[c.base + fe] = key_of32(T.bs, T.ba);
+    }
     if constexpr (CH) {
       // another chunk of the round created segments or stopped before this one: the walk will
       // never read this chunk's results, so it ends here and writes none
@@ -2281,22 +2326,22 @@ __device__ __forceinline__ int fast_chunk(const Gw& w, const GMEM int64_t* off, 
     c.created = 0;
   } else {  // the frontier's state: the end state of the chunk before it, its keys in order
     const GMEM uint64_t* src = w.cst + (chain * K + ctl.f - 1) * kStateWords;
-    const uint64_t cw = uni64(src[kStateKeys + 3]);
+    const uint64_t cw = uni64(cld(src + kStateKeys + 3));
     const int32_t cnt = (int32_t)(uint32_t)cw;
     const int32_t nd = uni(ctl.nd);
-    rt_get(ps.t, src, cnt, rows_for(cnt + nd));
-    ps.bump = uni64(src[kStateKeys]);
-    ps.created_u = uni64(src[kStateKeys + 1]);
-    c.reserved_u = uni64(src[kStateKeys + 2]);
+    rt_get<true>(ps.t, src, cnt, rows_for(cnt + nd));
+    ps.bump = uni64(cld(src + kStateKeys));
+    ps.created_u = uni64(cld(src + kStateKeys + 1));
+    c.reserved_u = uni64(cld(src + kStateKeys + 2));
     c.created = (int32_t)(cw >> 32);
     if (nd > 0) {  // plus the delta keys (certification left room for them) and the counters after them
       const GMEM uint64_t* del = w.cdel + chain * kDeltaWords;
-      const uint64_t mine = lane < nd ? del[lane] : 0;
+      const uint64_t mine = lane < nd ? cld(del + lane) : 0;
       for (int i = 0; i < nd && ps.t.n < kTabSlots; ++i) rt_insert_any(ps.t, rl64(mine, i));
-      ps.bump = uni64(del[kMaxDelta]);
-      ps.created_u = uni64(del[kMaxDelta + 1]);
-      c.reserved_u = uni64(del[kMaxDelta + 2]);
-      c.created = uni((int32_t)del[kMaxDelta + 3]);
+      ps.bump = uni64(cld(del + kMaxDelta));
+      ps.created_u = uni64(cld(del + kMaxDelta + 1));
+      c.reserved_u = uni64(cld(del + kMaxDelta + 2));
+      c.created = uni((int32_t)cld(del + kMaxDelta + 3));
     }
   }
   wave_order();
@@ -2330,14 +2375,14 @@ __device__ __forceinline__ int fast_chunk(const Gw& w, const GMEM int64_t* off, 
 #pragma unroll
   for (int r = 0; r < kTabRows; ++r) {
     const int32_t i = lane * ps.t.rows + r;
-    if (r < ps.t.rows && i < ps.t.n) dst[i] = ps.t.k[r];
+    if (r < ps.t.rows && i < ps.t.n) cst(dst + i, ps.t.k[r]);
   }
   if (lane == 0) {
-    dst[kStateKeys] = ps.bump;
-    dst[kStateKeys + 1] = ps.created_u;
-    dst[kStateKeys + 2] = c.reserved_u;
-    dst[kStateKeys + 3] = (uint64_t)(uint32_t)ps.t.n | ((uint64_t)(uint32_t)c.created << 32);
-    gstore(&w.chdr[chain * K + k],
+    cst(dst + kStateKeys, ps.bump);
+    cst(dst + kStateKeys + 1, ps.created_u);
+    cst(dst + kStateKeys + 2, c.reserved_u);
+    cst(dst + kStateKeys + 3, (uint64_t)(uint32_t)ps.t.n | ((uint64_t)(uint32_t)c.created << 32));
+    ast(&w.chdr[chain * K + k],
            CHdr{stop, status, c.n_res, ps.n_mf, c.created - created0, ps.maxfree > n0 ? ps.maxfree : n0, 0});
   }
   return (c.created != created0 ? kChunkGrew : 0) | (status != XMEM_T_OK ? kChunkStopped : 0);
@@ -2390,7 +2435,7 @@ __device__ __forceinline__ void stitch_walk(const Gw& w, const GMEM int64_t* off
   const int K = w.chunks;
   const int64_t t = chain >> 1;
   const int pool_one = (int)(chain & 1);
-  const int nk = w.cnum[chain];
+  const int nk = uni(w.cnum[chain]);
   const int64_t base = off[t], n = off[t + 1] - base;
   // certification: paged chunks, and small-pool chunks on the LDS table, which need no choice
   // summary (a small request never prefers a whole new small segment: no small block is larger,
@@ -2399,9 +2444,9 @@ __device__ __forceinline__ void stitch_walk(const Gw& w, const GMEM int64_t* off
   // the frontier state's bump: segments created by chunks replayed from it lie at or above it
   GMEM uint64_t* del = w.cdel + chain * kDeltaWords;
   uint64_t sf_bump = 0;
-  if (CERT && ctl.nd > 0) sf_bump = del[kMaxDelta];
+  if (CERT && ctl.nd > 0) sf_bump = cld(del + kMaxDelta);
   else if (BIG && ctl.f > 0) sf_bump = w.bstate[(chain * K + ctl.f - 1) * w.bstate_words];
-  else if (CERT && ctl.f > 0) sf_bump = w.cst[(chain * K + ctl.f - 1) * kStateWords + kStateKeys];
+  else if (CERT && ctl.f > 0) sf_bump = cld(w.cst + (chain * K + ctl.f - 1) * kStateWords + kStateKeys);
   const int32_t room = BIG ? 32 * w.bcap : kTabSlots;  // free blocks a state certainly holds
   int nd = 0;              // delta keys of this walk (new segments of chunk jd)
   int jd = -1;
@@ -2410,8 +2455,13 @@ __device__ __forceinline__ void stitch_walk(const Gw& w, const GMEM int64_t* off
   int have = 0;            // delta segments the last walked chunk's end state holds (the lowest ones)
   int64_t stop = -1;
   int status = XMEM_T_OK;
+  CHdr hs{};  // lane i: the header of chunk k0 + i (64 loaded at once: one after the other each costs a round trip)
+  const int f0 = ctl.f;
   for (int k = ctl.f;; ++k) {
-    const CHdr h = gload(&w.chdr[chain * K + k]);
+    const int hl = (k - f0) & (kWave - 1);
+    if (hl == 0 && k + lane < nk) hs = ald(&w.chdr[chain * K + k + lane]);
+    const CHdr h{(int64_t)rl64((uint64_t)hs.stop, hl), (int32_t)rl((uint32_t)hs.status, hl), (int32_t)rl((uint32_t)hs.n_res, hl),
+                 (int32_t)rl((uint32_t)hs.n_mf, hl), (int32_t)rl((uint32_t)hs.changed, hl), (int32_t)rl((uint32_t)hs.maxc, hl), 0};
     // A small-pool chunk on the paged sets that created segments although a delta was pending
     // ran from the state without the delta, and its new segments are the delta's lowest ones
     // (every small segment has one size, and both runs create them at the same bump, in the
@@ -2440,12 +2490,12 @@ __device__ __forceinline__ void stitch_walk(const Gw& w, const GMEM int64_t* off
             kc0 = st[0]; kc1 = st[1]; kc2 = st[2]; kc3 = st[4];
           } else {  // the saved table, unordered: its keys at or above the bump, then sorted
             const GMEM uint64_t* st = w.cst + (chain * K + k) * kStateWords;
-            const uint64_t cw = st[kStateKeys + 3];
+            const uint64_t cw = cld(st + kStateKeys + 3);
             const int32_t cnt = (int32_t)(uint32_t)cw;
-            kc0 = st[kStateKeys]; kc1 = st[kStateKeys + 1]; kc2 = st[kStateKeys + 2]; kc3 = cw >> 32;
+            kc0 = cld(st + kStateKeys); kc1 = cld(st + kStateKeys + 1); kc2 = cld(st + kStateKeys + 2); kc3 = cw >> 32;
             for (int32_t r0 = 0; r0 < cnt; r0 += kWave) {
               const int32_t i = r0 + lane;
-              const uint64_t x = i < cnt ? st[i] : kNoKey;
+              const uint64_t x = i < cnt ? cld(st + i) : kNoKey;
               const bool is_new = i < cnt && key_addr(x) >= sf_bump;
               const uint64_t m = ballot(is_new);
               const int pos = kfound + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
@@ -2485,12 +2535,12 @@ __device__ __forceinline__ void stitch_walk(const Gw& w, const GMEM int64_t* off
         ctl.f = k;
         ctl.nd = nd - have;  // the end state of chunk k - 1 holds the lowest `have` delta segments already
         if (ctl.nd > 0) {
-          if (lane < ctl.nd) del[lane] = dkey;
+          if (lane < ctl.nd) cst(del + lane, dkey);
           if (lane == 0) {
-            del[kMaxDelta] = dc0;
-            del[kMaxDelta + 1] = dc1;
-            del[kMaxDelta + 2] = dc2;
-            del[kMaxDelta + 3] = dc3;
+            cst(del + kMaxDelta, dc0);
+            cst(del + kMaxDelta + 1, dc1);
+            cst(del + kMaxDelta + 2, dc2);
+            cst(del + kMaxDelta + 3, dc3);
           }
         }
         break;
@@ -2501,7 +2551,7 @@ __device__ __forceinline__ void stitch_walk(const Gw& w, const GMEM int64_t* off
     const GMEM MfRec* cm = (const GMEM MfRec*)w.segs + base + (pool_one ? n - 1 - olo : olo);
     const int dir = pool_one ? -1 : 1;
     for (int32_t i = renamed + lane; i < h.n_res; i += kWave) {
-      const ChunkRes r = gload(&cr[(int64_t)dir * i]);
+      const ChunkRes r = ald(&cr[(int64_t)dir * i]);
       const int64_t j = ctl.n_res + (i - renamed);
       gstore(&w.res[pool_one ? base + n - 1 - j : base + j], ResRec{r.reserved, r.event, r.created, 0, 0});
     }
@@ -2509,11 +2559,11 @@ __device__ __forceinline__ void stitch_walk(const Gw& w, const GMEM int64_t* off
     if (renamed > 0) {
       // true count = own count + nd - (renamed creations so far): a shift that only falls, so every
       // true new maximum is one of the chunk's own; each is kept if above everything before it
-      const int32_t cev = lane < renamed ? gload(&cr[(int64_t)dir * lane]).event : INT32_MAX;
+      const int32_t cev = lane < renamed ? ald(&cr[(int64_t)dir * lane]).event : INT32_MAX;
       int32_t run = ctl.runmax;
       for (int32_t i0 = 0; i0 < h.n_mf; i0 += kWave) {
         const int32_t i = i0 + lane;
-        const MfRec r = i < h.n_mf ? gload(&cm[(int64_t)dir * i]) : MfRec{INT32_MAX, INT32_MIN};
+        const MfRec r = i < h.n_mf ? ald(&cm[(int64_t)dir * i]) : MfRec{INT32_MAX, INT32_MIN};
         int c = 0;
         for (int j = 0; j < renamed; ++j) c += __shfl(cev, j, 64) <= r.event ? 1 : 0;
         const int32_t tv = i < h.n_mf ? r.value + (nd - c) : INT32_MIN;
@@ -2540,9 +2590,10 @@ __device__ __forceinline__ void stitch_walk(const Gw& w, const GMEM int64_t* off
     }
     // the chunk's maxima (of its own counts, plus the delta) increase: keep those above the running maximum
     int32_t first = h.n_mf;
-    for (int32_t i0 = 0; renamed == 0 && i0 < h.n_mf; i0 += kWave) {
+    // (none when its largest count is not: no record is above that)
+    for (int32_t i0 = 0; renamed == 0 && h.maxc + nd > ctl.runmax && i0 < h.n_mf; i0 += kWave) {
       const int32_t i = i0 + lane;
-      const uint64_t m = ballot(i < h.n_mf && cm[(int64_t)dir * i].value + nd > ctl.runmax);
+      const uint64_t m = ballot(i < h.n_mf && ald(&cm[(int64_t)dir * i]).value + nd > ctl.runmax);
       if (m) {
         first = i0 + __builtin_ctzll(m);
         break;
@@ -2550,11 +2601,11 @@ __device__ __forceinline__ void stitch_walk(const Gw& w, const GMEM int64_t* off
     }
     for (int32_t i = first + lane; i < h.n_mf; i += kWave) {
       const int64_t j = ctl.n_mf + (i - first);
-      const MfRec r = gload(&cm[(int64_t)dir * i]);
+      const MfRec r = ald(&cm[(int64_t)dir * i]);
       gstore(&w.mf[pool_one ? base + n - 1 - j : base + j], MfRec{r.event, r.value + nd});
     }
     if (first < h.n_mf) {
-      ctl.runmax = cm[(int64_t)dir * (h.n_mf - 1)].value + nd;
+      ctl.runmax = ald(&cm[(int64_t)dir * (h.n_mf - 1)]).value + nd;
       ctl.n_mf += h.n_mf - first;
     }
     if (h.status != XMEM_T_OK) {
@@ -2606,12 +2657,12 @@ __device__ __forceinline__ void stitch_walk(const Gw& w, const GMEM int64_t* off
       } else {
         // the end state's table, unordered: gather the keys at or above the bump in LDS
         const GMEM uint64_t* st = w.cst + (chain * K + k) * kStateWords;
-        const uint64_t cw = st[kStateKeys + 3];
+        const uint64_t cw = cld(st + kStateKeys + 3);
         const int32_t cnt = (int32_t)(uint32_t)cw;
-        c0 = st[kStateKeys]; c1 = st[kStateKeys + 1]; c2 = st[kStateKeys + 2]; c3 = cw >> 32;
+        c0 = cld(st + kStateKeys); c1 = cld(st + kStateKeys + 1); c2 = cld(st + kStateKeys + 2); c3 = cw >> 32;
         for (int32_t r0 = 0; r0 < cnt; r0 += kWave) {
           const int32_t i = r0 + lane;
-          const uint64_t x = i < cnt ? st[i] : kNoKey;
+          const uint64_t x = i < cnt ? cld(st + i) : kNoKey;
           const bool is_new = i < cnt && key_addr(x) >= sf_bump;
           const uint64_t m = ballot(is_new);
           const int pos = found + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
@@ -2740,7 +2791,7 @@ __device__ __forceinline__ int sched_first_tasks(int64_t chain, int mode, int ro
 __device__ void sched_walk(const Gw& w, const GMEM int64_t* off, int64_t chain, int64_t nchains, int win,
                            LMEM uint64_t* s_del, bool rename) {
   const int lane = threadIdx.x;
-  CCtl ctl = gload(&w.cctl[chain]);
+  CCtl ctl = ald(&w.cctl[chain]);
   const int mode = ctl.mode;
   int64_t stop;
   int status;
@@ -2758,16 +2809,14 @@ __device__ void sched_walk(const Gw& w, const GMEM int64_t* off, int64_t chain, 
   int nq = sched_first_tasks(chain, ctl.mode, ctl.rounds, n, win);  // queued now; the rest by finished chunks
   if (nq < n && __builtin_amdgcn_readfirstlane((int)(lane == 0 && sched_starved(w)))) nq = n;
   if (lane == 0) {
-    gstore(&w.cctl[chain], ctl);
+    ast(&w.cctl[chain], ctl);
     if (ctl.done) gstore(&w.hdr[chain], ChainHdr{stop, status, ctl.n_res, ctl.n_mf, 0, 0});
-    else w.cpend[chain] = n;
-    w.cpend[nchains + chain] = nk;  // no chunk of the new round has created segments or stopped yet
-    w.cpend[2 * nchains + chain] = ctl.f + nq;
-    w.cdel[chain * kDeltaWords + kRoundMask] = 0;
+    else __hip_atomic_store(w.cpend + chain, n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(w.cpend + nchains + chain, nk, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);  // no chunk of the new round has created segments or stopped yet
+    __hip_atomic_store(w.cpend + 2 * nchains + chain, ctl.f + nq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    cst(w.cdel + chain * kDeltaWords + kRoundMask, 0);
   }
-  // release: the walk's results before the chain counts as done or its next tasks appear (a
-  // one-way fence: a full one would also invalidate this XCD's L2 for every wavefront on it)
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+  stores_done();  // the walk's results, before the chain counts as done or its next tasks appear
   if (ctl.done) {
     if (lane == 0) __hip_atomic_fetch_add(w.cqc + kQDone, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     return;
@@ -2884,7 +2933,7 @@ __device__ __forceinline__ void sched_run(LMEM uint64_t* s_k) {
       task = uni64(task);
     }
     if (task == 0) return;
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");  // the frontier the chain's last walk wrote
+    loads_after();  // the frontier the chain's last walk wrote
     const int64_t chain = (int64_t)((task >> 16) & 0x7fffffffffffull);
     const int k = (int)((task >> 2) & 63);
     const int mode = (int)(task & 3);
@@ -2896,7 +2945,7 @@ __device__ __forceinline__ void sched_run(LMEM uint64_t* s_k) {
       const Gw w = typed(ws);
       const Derived d = kload(&A->d);
       const int K = w.chunks;
-      const CCtl ctl = gload(&w.cctl[chain]);
+      const CCtl ctl = ald(&w.cctl[chain]);
       nk = uni(w.cnum[chain]);
       const GMEM int32_t* bnd = w.cbound + chain * (K + 1);
       // without windows (a batch of fewer chains): a chunk of a chain's later round, which the
@@ -2911,10 +2960,7 @@ __device__ __forceinline__ void sched_run(LMEM uint64_t* s_k) {
                        AGED ? A->limit / (kSchedLimitSeconds * 1000) : 0);
       if (tp) __builtin_amdgcn_s_setprio(0);
     }
-    // release: this chunk's state, records and header before it counts as done; and, for a
-    // successor task queued below, what this task acquired (the walk's frontier), so that the
-    // successor's taker, which acquires after reading its task word, sees it too
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+    stores_done();  // this chunk's state, records and header, before it counts as done
     {
       const KARG SchedArgs* A = sched_args();
       const Ws ws = kload(&A->ws);
@@ -2926,7 +2972,7 @@ __device__ __forceinline__ void sched_run(LMEM uint64_t* s_k) {
         last = __hip_atomic_fetch_add(w.cpend + chain, -done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == done;
       }
       if (__builtin_amdgcn_readfirstlane(last)) {
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");  // the other chunks of the round
+        loads_after();  // the other chunks of the round
         sched_walk(w, gp(A->off), chain, A->nchains, WIN ? kWindow : kMaxChunks, s_k, WIN && !AGED);
       }
       // counted after the walk queued the next round, so that a waiting wavefront sees either
