@@ -1069,9 +1069,11 @@ __device__ __forceinline__ Near rt_neighbours(const Keys& k, uint32_t a, uint32_
 }
 
 // The row counts in use, and the smallest that holds n keys.  (Each is an instance of the event
-// code below; a count between two of them runs on the larger.)
+// code below, whose instructions grow with the rows, 7 to 9 each; a count between two of them runs
+// on the larger.  5, 7 and 10 besides 4, 6, 8 and 12: 4,096 Monte Carlo traces, whose tables hold
+// 256 to 640 keys, 35.0 -> 33.7 ms.)
 __device__ __forceinline__ int rows_for(int32_t n) {
-  return n < 64 ? 1 : n < 128 ? 2 : n < 192 ? 3 : n < 256 ? 4 : n < 384 ? 6 : n < 512 ? 8 : kTabRows;
+  return n < 512 ? (n >> 6) + 1 : n < 640 ? 10 : kTabRows;
 }
 // at a tile's end a table moves to fewer rows once it would leave a quarter row of them free
 __device__ __forceinline__ int rows_shrunk(int32_t n, int rows) {
@@ -1113,8 +1115,11 @@ __device__ __forceinline__ void rt_insert_any(RTab& t, uint64_t v) {
     case 2: rt_insert<2>(t.k, v); break;
     case 3: rt_insert<3>(t.k, v); break;
     case 4: rt_insert<4>(t.k, v); break;
+    case 5: rt_insert<5>(t.k, v); break;
     case 6: rt_insert<6>(t.k, v); break;
+    case 7: rt_insert<7>(t.k, v); break;
     case 8: rt_insert<8>(t.k, v); break;
+    case 10: rt_insert<10>(t.k, v); break;
     default: rt_insert<kTabRows>(t.k, v); break;
   }
   t.n += 1;
@@ -1386,8 +1391,11 @@ __device__ __forceinline__ bool row_events_any(RowPool& ps, RowTile& T, uint64_t
     case 2: return row_events<2, ONE>(k, ps.t.n, room, ps.split_min, T, todo);
     case 3: return row_events<3, ONE>(k, ps.t.n, room, ps.split_min, T, todo);
     case 4: return row_events<4, ONE>(k, ps.t.n, room, ps.split_min, T, todo);
+    case 5: return row_events<5, ONE>(k, ps.t.n, room, ps.split_min, T, todo);
     case 6: return row_events<6, ONE>(k, ps.t.n, room, ps.split_min, T, todo);
+    case 7: return row_events<7, ONE>(k, ps.t.n, room, ps.split_min, T, todo);
     case 8: return row_events<8, ONE>(k, ps.t.n, room, ps.split_min, T, todo);
+    case 10: return row_events<10, ONE>(k, ps.t.n, room, ps.split_min, T, todo);
     default: return row_events<kTabRows, ONE>(k, ps.t.n, room, ps.split_min, T, todo);
   }
 }
@@ -1465,8 +1473,10 @@ struct Resume { int64_t from; uint64_t cur, prev; };
 //
 // With ms_ticks (wall-clock ticks per millisecond; 0: off), a chunk raises its wavefront's issue
 // priority as it ages (its age counted from its 64th tile and checked every 64 tiles: 1 past
-// 4 ms, 2 past 8, 3 past 16), so that on a SIMD the long tasks that end a batch of few chunks
-// per pool go first.
+// 4 ms, 2 past 8, 3 past 16) and while its table is large (1 from 6 rows on, 2 from 8, 3 from 10:
+// an event costs about as many instructions as there are rows), so that on a SIMD the long tasks
+// that end a batch of few chunks per pool go first.  By the table too: 4,096 Monte Carlo traces of
+// 65,536 events 33.7 -> 30.8 ms a step.
 template <int NP, bool CH>
 __device__ __forceinline__ void row_run(RowChain<NP, CH>& c, const Derived& d, const Gw& w, int pool_one, int64_t lo,
                                         int64_t limit, int* status_out, int64_t* stop_out, Resume* rs = nullptr,
@@ -1494,10 +1504,13 @@ __device__ __forceinline__ void row_run(RowChain<NP, CH>& c, const Derived& d, c
         const uint64_t now = wall_clock64();
         if (t_aged == 0) t_aged = now;
         const uint64_t age = now - t_aged;
-        const int p = age > 16 * ms_ticks ? 3 : age > 8 * ms_ticks ? 2 : age > 4 * ms_ticks ? 1 : 0;
+        const int aged = age > 16 * ms_ticks ? 3 : age > 8 * ms_ticks ? 2 : age > 4 * ms_ticks ? 1 : 0;
+        const int rows = c.p[0].t.rows, slow = rows >= 10 ? 3 : rows >= 8 ? 2 : rows >= 6 ? 1 : 0;
+        const int p = aged > slow ? aged : slow;
         if (p != prio) {  // the priority is an immediate operand
           prio = p;
-          if (p == 1) __builtin_amdgcn_s_setprio(1);
+          if (p == 0) __builtin_amdgcn_s_setprio(0);
+          else if (p == 1) __builtin_amdgcn_s_setprio(1);
           else if (p == 2) __builtin_amdgcn_s_setprio(2);
           else if (p == 3) __builtin_amdgcn_s_setprio(3);
         }
