@@ -45,7 +45,9 @@ namespace {
 constexpr int kThreads = 256;             // 4 wavefronts
 constexpr int kItems = 16;                // elements per lane per tile
 constexpr int kTileN = kThreads * kItems;  // 4096
-constexpr int kBins = 256;
+constexpr int kDigit = 9;                 // bits a radix pass sorts by
+constexpr int kBins = 1 << kDigit;
+constexpr int kSteps = kTileN / 64;       // 64-record steps of a tile
 constexpr int kWaves = kThreads / 64;
 constexpr int kScanThreads = 1024;
 constexpr int64_t kPersist = INT64_MAX;
@@ -55,12 +57,10 @@ __host__ __device__ inline size_t al256(size_t x) { return (x + 255) & ~size_t(2
 __host__ __device__ inline int64_t tiles_of(int64_t n) { return (n + kTileN - 1) / kTileN; }
 
 __device__ __forceinline__ uint64_t ballot(bool p) { return __builtin_amdgcn_ballot_w64(p); }
-// a sort pass over bits [sh, sh + 8) runs only below the key width found on the device (*gate)
+// a sort pass over bits [sh, sh + kDigit) runs only below the key width found on the device (*gate)
 __device__ __forceinline__ bool gated(const int32_t* gate, int sh) { return gate && sh >= *gate; }
 
-// ---------------------------------------------------------------- generic exclusive scan of uint32
-// in[0..m) -> out[0..m) (may alias); part: tiles_of(m) words.
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+// ---------------------------------------------------------------- scans
 template <int CTRL, int ROWS>
 __device__ __forceinline__ uint32_t dpp_u32(uint32_t old, uint32_t v) {
   return (uint32_t)__builtin_amdgcn_update_dpp((int)old, (int)v, CTRL, ROWS, 0xf, false);
@@ -77,154 +77,213 @@ __device__ __forceinline__ uint32_t wave_scan_u32(uint32_t x) {
   x += dpp_u32<0x143, 0xc>(0, x);
   return x;
 }
-// A lane's kItems consecutive elements from base: four 16-byte loads where they all lie below m
-// (the scans' buffers are workspace buffers, 256-byte aligned, and base is a multiple of kItems).
-__device__ __forceinline__ void scan_load(const uint32_t* in, int64_t base, int64_t m, uint32_t (&v)[kItems]) {
-  if (base + kItems <= m) {
-    const u32x4* p = reinterpret_cast<const u32x4*>(in + base);
-#pragma unroll
-    for (int q = 0; q < kItems / 4; ++q) {
-      const u32x4 x = p[q];
-      v[4 * q] = x.x;
-      v[4 * q + 1] = x.y;
-      v[4 * q + 2] = x.z;
-      v[4 * q + 3] = x.w;
-    }
-  } else {
-#pragma unroll
-    for (int i = 0; i < kItems; ++i) v[i] = base + i < m ? in[base + i] : 0u;
-  }
-}
-__global__ __launch_bounds__(kThreads) void k_scan_reduce(const uint32_t* in, int64_t m, uint32_t* part,
-                                                          const int32_t* gate, int sh) {
-  if (gated(gate, sh)) return;
-  __shared__ uint32_t s[kWaves];
+// exclusive scan of v over the workgroup's kThreads threads; *total gets the sum (s: kWaves words)
+__device__ __forceinline__ uint32_t block_excl_scan(uint32_t v, uint32_t* s, uint32_t* total) {
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  uint32_t v[kItems];
-  scan_load(in, (int64_t)blockIdx.x * kTileN + (int64_t)threadIdx.x * kItems, m, v);
-  uint32_t acc = 0;
-#pragma unroll
-  for (int i = 0; i < kItems; ++i) acc += v[i];
-  acc = wave_scan_u32(acc);
-  if (lane == 63) s[wv] = acc;
+  const uint32_t x = wave_scan_u32(v);
+  if (lane == 63) s[wv] = x;
   __syncthreads();
-  if (threadIdx.x == 0) {
-    uint32_t t = 0;
+  uint32_t before = 0, tot = 0;
 #pragma unroll
-    for (int k = 0; k < kWaves; ++k) t += s[k];
-    part[blockIdx.x] = t;
+  for (int k = 0; k < kWaves; ++k) {
+    before += k < wv ? s[k] : 0u;
+    tot += s[k];
   }
+  __syncthreads();
+  *total = tot;
+  return before + x - v;
 }
 // exclusive scan of part[0..np) in place, one workgroup; total to *total
-__global__ __launch_bounds__(kScanThreads) void k_scan_top(uint32_t* part, int64_t np, uint32_t* total,
-                                                           const int32_t* gate, int sh) {
-  if (gated(gate, sh)) return;
-  __shared__ uint32_t s[kScanThreads];
+__global__ __launch_bounds__(kScanThreads) void k_scan_top(uint32_t* part, int64_t np, uint32_t* total) {
+  __shared__ uint32_t s[kScanThreads / 64];
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   const int64_t per = (np + kScanThreads - 1) / kScanThreads;
   const int64_t lo = (int64_t)threadIdx.x * per;
   uint32_t acc = 0;
   for (int64_t i = lo; i < lo + per && i < np; ++i) acc += part[i];
-  s[threadIdx.x] = acc;
+  const uint32_t x = wave_scan_u32(acc);
+  if (lane == 63) s[wv] = x;
   __syncthreads();
-  for (int st = 1; st < kScanThreads; st <<= 1) {  // inclusive Hillis-Steele
-    const uint32_t v = (int)threadIdx.x >= st ? s[threadIdx.x - st] : 0u;
-    __syncthreads();
-    s[threadIdx.x] += v;
-    __syncthreads();
-  }
-  uint32_t run = threadIdx.x ? s[threadIdx.x - 1] : 0u;
+  uint32_t run = x - acc;
+#pragma unroll
+  for (int k = 0; k < kScanThreads / 64; ++k) run += k < wv ? s[k] : 0u;
+  if (threadIdx.x == kScanThreads - 1 && total) *total = run + acc;
   for (int64_t i = lo; i < lo + per && i < np; ++i) {
     const uint32_t v = part[i];
     part[i] = run;
     run += v;
   }
-  if (threadIdx.x == kScanThreads - 1 && total) *total = s[kScanThreads - 1];
 }
-__global__ __launch_bounds__(kThreads) void k_scan_down(const uint32_t* in, int64_t m, const uint32_t* part,
-                                                        uint32_t* out, const int32_t* gate, int sh) {
-  if (gated(gate, sh)) return;
-  __shared__ uint32_t s[kWaves];
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  const int64_t base = (int64_t)blockIdx.x * kTileN + (int64_t)threadIdx.x * kItems;
-  uint32_t v[kItems];
-  scan_load(in, base, m, v);
-  uint32_t acc = 0;
-#pragma unroll
-  for (int i = 0; i < kItems; ++i) acc += v[i];
-  const uint32_t x = wave_scan_u32(acc);
-  if (lane == 63) s[wv] = x;
+
+// Flags of a tile's records (record kThreads i + thread of the tile: every load coalesced), as one
+// ballot per 64-record step, and the flagged records before each step.
+struct TileFlags {
+  uint64_t m[kSteps];
+  uint32_t before[kSteps + 1];  // [kSteps]: all of the tile
+};
+__device__ __forceinline__ void flags_put(TileFlags& f, int i, bool flag) {
+  const uint64_t m = ballot(flag);
+  if ((threadIdx.x & 63) == 0) f.m[i * kWaves + (threadIdx.x >> 6)] = m;
+}
+__device__ __forceinline__ void flags_scan(TileFlags& f) {
+  static_assert(kSteps == 64, "one wavefront scans the steps");
   __syncthreads();
-  uint32_t run = part[blockIdx.x] + x - acc;
-#pragma unroll
-  for (int k = 0; k < kWaves - 1; ++k) run += k < wv ? s[k] : 0u;
-  uint32_t o[kItems];
-#pragma unroll
-  for (int i = 0; i < kItems; ++i) {
-    o[i] = run;
-    run += v[i];
+  if (threadIdx.x < 64) {
+    const uint32_t c = (uint32_t)__builtin_popcountll(f.m[threadIdx.x]);
+    const uint32_t x = wave_scan_u32(c);
+    f.before[threadIdx.x] = x - c;
+    if (threadIdx.x == 63) f.before[kSteps] = x;
   }
-  if (base + kItems <= m) {  // in place too: every lane reads its elements before it writes them
-    u32x4* p = reinterpret_cast<u32x4*>(out + base);
-#pragma unroll
-    for (int q = 0; q < kItems / 4; ++q) p[q] = u32x4{o[4 * q], o[4 * q + 1], o[4 * q + 2], o[4 * q + 3]};
-  } else {
-#pragma unroll
-    for (int i = 0; i < kItems; ++i)
-      if (base + i < m) out[base + i] = o[i];
-  }
+  __syncthreads();
+}
+// flagged records of the tile before its record r <= kTileN
+__device__ __forceinline__ uint32_t flags_before(const TileFlags& f, int r) {
+  if (r >= kTileN) return f.before[kSteps];
+  return f.before[r >> 6] + (uint32_t)__builtin_popcountll(f.m[r >> 6] & ((1ull << (r & 63)) - 1));
 }
 
-struct ScanWs { uint32_t* part; uint32_t* total; };
-
-void scan_u32(const uint32_t* in, uint32_t* out, int64_t m, const ScanWs& w, hipStream_t st,
-              const int32_t* gate = nullptr, int sh = 0) {
-  if (m <= 0) return;
-  const int64_t nt = tiles_of(m);
-  k_scan_reduce<<<(unsigned)nt, kThreads, 0, st>>>(in, m, w.part, gate, sh);
-  k_scan_top<<<1, kScanThreads, 0, st>>>(w.part, nt, w.total, gate, sh);
-  k_scan_down<<<(unsigned)nt, kThreads, 0, st>>>(in, m, w.part, out, gate, sh);
+// ---------------------------------------------------------------- traces of records
+// The first index i in [0, n] with v[i] >= x (v ascending, n: none), found by one whole wavefront:
+// each round looks at 64 evenly spaced entries, where a binary search takes a dependent load a
+// halving.
+__device__ __forceinline__ int64_t wave_lower_bound(const int64_t* v, int64_t n, int64_t x) {
+  const int lane = threadIdx.x & 63;
+  int64_t lo = 0, hi = n;  // the answer is in [lo, hi]
+  while (lo < hi) {
+    const int64_t step = (hi - lo + 63) / 64;
+    const int64_t p = lo + lane * step;
+    const uint64_t m = ballot(p < hi && v[p] < x);  // a prefix of the lanes
+    if (m == 0) return lo;
+    const int64_t last = lo + (63 - __builtin_clzll(m)) * step;
+    const int64_t next = last + step;
+    lo = last + 1;
+    hi = next < hi ? next : hi;
+  }
+  return lo;
+}
+// The last trace that starts at or before record base (workgroup-wide; every thread calls it).
+__device__ __forceinline__ int64_t tile_trace(const int64_t* off, int64_t T, int64_t base) {
+  __shared__ int64_t s_t;
+  if (threadIdx.x < 64) {
+    const int64_t t = wave_lower_bound(off, T, base + 1) - 1;  // off[0] == 0
+    if (threadIdx.x == 0) s_t = t;
+  }
+  __syncthreads();
+  return s_t;
+}
+// a thread's walk over its records in ascending order: the trace of each
+struct TraceStep {
+  int64_t t, next;
+  __device__ __forceinline__ TraceStep(const int64_t* off, int64_t T, int64_t t0) : t(t0) {
+    next = t + 1 < T ? off[t + 1] : INT64_MAX;
+  }
+  __device__ __forceinline__ void to(const int64_t* off, int64_t T, int64_t k) {
+    while (k >= next) {  // empty traces included: the last trace whose first record is at or before k
+      ++t;
+      next = t + 1 < T ? off[t + 1] : INT64_MAX;
+    }
+  }
+};
+// The traces that start in the tile [base, base + kTileN) of n records, with those that start at n
+// (and the end, T) in the last tile: out[t] = at + per * (records of the tile before it) + its flagged ones.
+__device__ __forceinline__ void tile_offsets(const int64_t* off, int64_t T, int64_t n, int64_t base, const TileFlags& f,
+                                             uint32_t at, int per, int64_t* out) {
+  __shared__ int64_t s_r[2];
+  const bool last = base + kTileN >= n;
+  if (threadIdx.x < 64) {
+    const int64_t a = wave_lower_bound(off, T + 1, base), b = last ? T + 1 : wave_lower_bound(off, T + 1, base + kTileN);
+    if (threadIdx.x == 0) { s_r[0] = a; s_r[1] = b; }
+  }
+  __syncthreads();
+  for (int64_t t = s_r[0] + threadIdx.x; t < s_r[1]; t += kThreads) {
+    const int r = (int)(off[t] - base);
+    out[t] = (int64_t)at + (int64_t)per * r + flags_before(f, r);
+  }
 }
 
 // ---------------------------------------------------------------- LSD radix sort
-// digit histogram of each tile, digit-major: hist[d * ntiles + tile]
+// One record's digit into the tile's histogram.  A wavefront whose elements share one digit (the
+// high digits of keys sorted by the low ones) adds once: 64 atomics on one LDS word would be serialized.
+__device__ __forceinline__ void hist_add(uint32_t* h, bool ok, uint32_t d) {
+  const uint64_t act = ballot(ok);
+  const uint32_t d0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)d);
+  const uint64_t same = ballot(ok && d == d0);
+  if (same == act) {
+    if (act && (threadIdx.x & 63) == (uint32_t)__builtin_ctzll(act)) atomicAdd(&h[d0], (uint32_t)__builtin_popcountll(act));
+  } else if (ok) {
+    atomicAdd(&h[d], 1u);
+  }
+}
+__device__ __forceinline__ void hist_clear(uint32_t* h) {
+#pragma unroll
+  for (int i = 0; i < kBins / kThreads; ++i) h[i * kThreads + threadIdx.x] = 0;
+  __syncthreads();
+}
+// digit-major: hist[d * ntiles + tile]
+__device__ __forceinline__ void hist_store(const uint32_t* h, uint32_t* hist, int64_t ntiles) {
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < kBins / kThreads; ++i) {
+    const int d = i * kThreads + threadIdx.x;
+    hist[(int64_t)d * ntiles + blockIdx.x] = h[d];
+  }
+}
+// digit histogram of each tile
 __global__ __launch_bounds__(kThreads) void k_rs_hist(const uint64_t* keys, int64_t n, int shift, uint32_t* hist,
                                                       int64_t ntiles, const int32_t* gate) {
   if (gated(gate, shift)) return;
   __shared__ uint32_t h[kBins];
-  h[threadIdx.x] = 0;
-  __syncthreads();
+  hist_clear(h);
   const int64_t base = (int64_t)blockIdx.x * kTileN;
 #pragma unroll
   for (int i = 0; i < kItems; ++i) {
     const int64_t k = base + (int64_t)i * kThreads + threadIdx.x;
     const bool ok = k < n;
-    const uint32_t d = ok ? (uint32_t)(keys[k] >> shift) & (kBins - 1) : 0u;
-    // a wavefront whose elements share one digit (the high digits of keys sorted by the low ones)
-    // adds once: 64 atomics on one LDS word would be serialized
-    const uint64_t act = ballot(ok);
-    const uint32_t d0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)d);
-    const uint64_t same = ballot(ok && d == d0);
-    if (same == act) {
-      if (act && (threadIdx.x & 63) == (uint32_t)__builtin_ctzll(act)) atomicAdd(&h[d0], (uint32_t)__builtin_popcountll(act));
-    } else if (ok) {
-      atomicAdd(&h[d], 1u);
-    }
+    hist_add(h, ok, ok ? (uint32_t)(keys[k] >> shift) & (kBins - 1) : 0u);
   }
-  __syncthreads();
-  hist[(int64_t)threadIdx.x * ntiles + blockIdx.x] = h[threadIdx.x];
+  hist_store(h, hist, ntiles);
+}
+// one workgroup per digit: its tiles' counts become an exclusive scan, its total goes to tot
+__global__ __launch_bounds__(kThreads) void k_rs_rows(uint32_t* hist, int64_t ntiles, uint32_t* tot, const int32_t* gate,
+                                                      int shift) {
+  if (gated(gate, shift)) return;
+  __shared__ uint32_t s[kWaves];
+  uint32_t* row = hist + (int64_t)blockIdx.x * ntiles;
+  constexpr int kPer = 8;
+  uint32_t carry = 0;
+  for (int64_t b = 0; b < ntiles; b += kThreads * kPer) {
+    const int64_t i0 = b + (int64_t)threadIdx.x * kPer;
+    uint32_t v[kPer], acc = 0, total;
+#pragma unroll
+    for (int j = 0; j < kPer; ++j) {
+      v[j] = i0 + j < ntiles ? row[i0 + j] : 0u;
+      acc += v[j];
+    }
+    uint32_t run = carry + block_excl_scan(acc, s, &total);
+#pragma unroll
+    for (int j = 0; j < kPer; ++j) {
+      if (i0 + j < ntiles) row[i0 + j] = run;
+      run += v[j];
+    }
+    carry += total;
+  }
+  if (threadIdx.x == 0) tot[blockIdx.x] = carry;
 }
 
-// Stable scatter of one tile by one digit.  off[d * ntiles + tile]: where this
-// tile's elements of digit d start in the output.
+// Stable scatter of one tile by one digit.  off[d * ntiles + tile]: this tile's elements of digit d
+// go after that many of the digit's; tot[d]: the digit's elements.
 __global__ __launch_bounds__(kThreads, 4) void k_rs_scatter(const uint64_t* kin, const uint32_t* vin, uint64_t* kout,
                                                          uint32_t* vout, int64_t n, int shift, const uint32_t* off,
-                                                         int64_t ntiles, const int32_t* gate) {
+                                                         const uint32_t* tot, int64_t ntiles, const int32_t* gate) {
   if (gated(gate, shift)) return;
-  __shared__ uint32_t wcnt[kWaves][kBins];  // per-wavefront digit counts, then their exclusive scan
-  __shared__ uint32_t tbase[kBins];         // start of each digit in the tile's local order
-  __shared__ uint32_t gbase[kBins];         // start of each digit's run in the output
-  __shared__ uint64_t sk[kTileN];           // the tile in output order: keys, then values (two phases, so
-                                            // that the block's LDS allows four workgroups per CU)
+  // the tile in output order: keys, then values (two phases); before that, per-wavefront digit
+  // counts and their exclusive scan (so that the LDS allows four workgroups per CU)
+  __shared__ uint64_t sk[kTileN];
+  uint32_t(*wcnt)[kBins] = reinterpret_cast<uint32_t(*)[kBins]>(sk);
+  static_assert(sizeof(uint32_t) * kWaves * kBins <= sizeof(sk), "the counts fit in the tile");
+  __shared__ uint32_t tbase[kBins];  // start of each digit in the tile's local order
+  __shared__ uint32_t gbase[kBins];  // where the digit's run starts in the output, less tbase
+  __shared__ uint32_t s_w[kWaves];
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   const uint64_t below = (1ull << lane) - 1;
   for (int d = lane; d < kBins; d += 64) wcnt[wv][d] = 0;
@@ -240,7 +299,7 @@ __global__ __launch_bounds__(kThreads, 4) void k_rs_scatter(const uint64_t* kin,
     const uint32_t d = (uint32_t)(key[i] >> shift) & (kBins - 1);
     uint64_t peers = ballot(ok);
 #pragma unroll
-    for (int b = 0; b < 8; ++b) {
+    for (int b = 0; b < kDigit; ++b) {
       const uint64_t bb = ballot((d >> b) & 1u);
       peers &= ((d >> b) & 1u) ? bb : ~bb;
     }
@@ -252,39 +311,41 @@ __global__ __launch_bounds__(kThreads, 4) void k_rs_scatter(const uint64_t* kin,
     __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
   }
   __syncthreads();
-  {  // thread tid owns digit tid: exclusive scan over the wavefronts, tile total
-    uint32_t s = 0;
+  {  // thread tid owns digits 2 tid and 2 tid + 1: exclusive scans over the wavefronts, then over the digits
+    uint32_t cnt[2], all[2], t;
 #pragma unroll
-    for (int w = 0; w < kWaves; ++w) {
-      const uint32_t c = wcnt[w][tid];
-      wcnt[w][tid] = s;
-      s += c;
+    for (int j = 0; j < 2; ++j) {
+      const int d = 2 * tid + j;
+      uint32_t s = 0;
+#pragma unroll
+      for (int w = 0; w < kWaves; ++w) {
+        const uint32_t c = wcnt[w][d];
+        wcnt[w][d] = s;
+        s += c;
+      }
+      cnt[j] = s;
+      all[j] = tot[d];
     }
-    tbase[tid] = s;  // tile count of digit tid, scanned below
-    gbase[tid] = off[(int64_t)tid * ntiles + blockIdx.x];
-  }
-  __syncthreads();
-  if (tid < 64) {  // exclusive scan of the 256 tile counts by one wavefront (4 per lane)
-    uint32_t c[4], s = 0;
+    static_assert(kBins == 2 * kThreads, "two digits a thread");
+    const uint32_t local = block_excl_scan(cnt[0] + cnt[1], s_w, &t), global = block_excl_scan(all[0] + all[1], s_w, &t);
 #pragma unroll
-    for (int j = 0; j < 4; ++j) { c[j] = tbase[4 * tid + j]; s += c[j]; }
-    uint32_t incl = s;
-#pragma unroll
-    for (int st = 1; st < 64; st <<= 1) {
-      const uint32_t o = __shfl_up(incl, st, 64);
-      if (lane >= st) incl += o;
+    for (int j = 0; j < 2; ++j) {
+      const int d = 2 * tid + j;
+      const uint32_t tb = local + (j ? cnt[0] : 0u);
+      tbase[d] = tb;
+      gbase[d] = global + (j ? all[0] : 0u) + off[(int64_t)d * ntiles + blockIdx.x] - tb;
     }
-    uint32_t run = incl - s;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) { tbase[4 * tid + j] = run; run += c[j]; }
   }
   __syncthreads();
 #pragma unroll
   for (int i = 0; i < kItems; ++i) {  // rd becomes the element's place in the tile (all ones: no element)
     const uint32_t d = rd[i] >> 16;
     rd[i] = d < kBins ? tbase[d] + wcnt[wv][d] + (rd[i] & 0xffffu) : 0xffffffffu;
-    if (rd[i] != 0xffffffffu) sk[rd[i]] = key[i];
   }
+  __syncthreads();  // the counts are read: the keys take their place
+#pragma unroll
+  for (int i = 0; i < kItems; ++i)
+    if (rd[i] != 0xffffffffu) sk[rd[i]] = key[i];
   __syncthreads();
   const int64_t cnt = n - (int64_t)blockIdx.x * kTileN < kTileN ? n - (int64_t)blockIdx.x * kTileN : kTileN;
   // sorted place tid + kThreads j of the tile: its output index (below XMEM_PREP_MAX_RECORDS)
@@ -295,8 +356,7 @@ __global__ __launch_bounds__(kThreads, 4) void k_rs_scatter(const uint64_t* kin,
     out_at[j] = 0xffffffffu;
     if (i < cnt) {
       const uint64_t k = sk[i];
-      const uint32_t d = (uint32_t)(k >> shift) & (kBins - 1);
-      out_at[j] = gbase[d] + ((uint32_t)i - tbase[d]);
+      out_at[j] = gbase[(uint32_t)(k >> shift) & (kBins - 1)] + (uint32_t)i;
       kout[out_at[j]] = k;
     }
   }
@@ -315,42 +375,43 @@ struct SortWs {
   uint64_t *ka, *kb;
   uint32_t *va, *vb;
   uint32_t* hist;
-  ScanWs scan;
+  uint32_t* tot;  // kBins
 };
 
-// Sorts (ka, va)[0..n) by key bits [lo, hi), stably; returns true when the
+// Sorts (ka, va)[0..n) by key bits [0, hi), stably; returns true when the
 // result is in (kb, vb), false when in (ka, va).  With a gate, the passes at and
-// above bit *gate (found on the device: an even number of passes below it) exit
-// at once; hi - lo must then span an even number of passes, so that the result
-// lands where the host expects it.
-bool sort_bits(SortWs& w, int64_t n, int lo, int hi, bool in_b, hipStream_t st, const int32_t* gate = nullptr) {
+// above bit *gate (found on the device) exit at once.  hist_done: the first
+// pass's histogram is in place.
+bool sort_bits(SortWs& w, int64_t n, int hi, bool in_b, hipStream_t st, const int32_t* gate, bool hist_done = false) {
   const int64_t nt = tiles_of(n);
-  for (int sh = lo; sh < hi; sh += 8) {
+  for (int sh = 0; sh < hi; sh += kDigit) {
     uint64_t* kin = in_b ? w.kb : w.ka;
     uint32_t* vin = in_b ? w.vb : w.va;
     uint64_t* kout = in_b ? w.ka : w.kb;
     uint32_t* vout = in_b ? w.va : w.vb;
-    k_rs_hist<<<(unsigned)nt, kThreads, 0, st>>>(kin, n, sh, w.hist, nt, gate);
-    scan_u32(w.hist, w.hist, (int64_t)kBins * nt, w.scan, st, gate, sh);
-    k_rs_scatter<<<(unsigned)nt, kThreads, 0, st>>>(kin, vin, kout, vout, n, sh, w.hist, nt, gate);
+    if (sh > 0 || !hist_done) k_rs_hist<<<(unsigned)nt, kThreads, 0, st>>>(kin, n, sh, w.hist, nt, gate);
+    k_rs_rows<<<kBins, kThreads, 0, st>>>(w.hist, nt, w.tot, gate, sh);
+    k_rs_scatter<<<(unsigned)nt, kThreads, 0, st>>>(kin, vin, kout, vout, n, sh, w.hist, w.tot, nt, gate);
     in_b = !in_b;
   }
   return in_b;
 }
+constexpr int kAllBits = (64 + kDigit - 1) / kDigit * kDigit;
 
-int bits_for(int64_t maxval) {  // bits needed for values 0..maxval, rounded up to a pass
+int passes_for(int64_t maxval) {  // passes that values 0..maxval take
   int b = 0;
-  while (b < 64 && (maxval >> b) != 0) ++b;
-  return (b + 7) / 8 * 8;
+  while (b < 63 && (maxval >> b) != 0) ++b;
+  return (b + kDigit - 1) / kDigit;
 }
 
 // ---------------------------------------------------------------- workspace
 struct PrepWs {
   SortWs s;
-  uint32_t* tid;     // n: trace of each record
-  uint32_t* u;       // n: flags, then their exclusive scan
+  uint32_t* part;    // tiles: flagged records of each tile, then their exclusive scan
+  uint32_t* total;   // 1: their sum
+  uint32_t* tid;     // n: trace of each record (separate key layouts), or the attribution's kept flags
   int64_t* t64;      // n: per-record int64 scratch (free time of an allocation / retimed free of a block),
-                     // or the attribution's parameter-size hash sets (2 u32 slots per parameter block)
+                     // or the attribution's parameter-size hash sets (2 u32 slots per block)
   uint32_t* apos;    // n: position of an allocation word within its trace
   int32_t* bad;      // 1
   uint64_t* kr;      // 8: a sort key's range on the device (min, max, OR of its values XOR a reference, gate),
@@ -369,10 +430,10 @@ size_t carve(void* base, int64_t T, int64_t n, PrepWs* w) {
   x.s.va = reinterpret_cast<uint32_t*>(take(4 * n));
   x.s.vb = reinterpret_cast<uint32_t*>(take(4 * n));
   x.s.hist = reinterpret_cast<uint32_t*>(take(4 * hist_n));
-  x.s.scan.part = reinterpret_cast<uint32_t*>(take(4 * (tiles_of(hist_n > n ? hist_n : n) + 1)));
-  x.s.scan.total = reinterpret_cast<uint32_t*>(take(4));
+  x.s.tot = reinterpret_cast<uint32_t*>(take(4 * kBins));
+  x.part = reinterpret_cast<uint32_t*>(take(4 * nt));
+  x.total = reinterpret_cast<uint32_t*>(take(4));
   x.tid = reinterpret_cast<uint32_t*>(take(4 * n));
-  x.u = reinterpret_cast<uint32_t*>(take(4 * (n + 1)));
   x.t64 = reinterpret_cast<int64_t*>(take(8 * n));
   x.apos = reinterpret_cast<uint32_t*>(take(4 * n));
   x.bad = reinterpret_cast<int32_t*>(take(4));
@@ -382,64 +443,67 @@ size_t carve(void* base, int64_t T, int64_t n, PrepWs* w) {
   return o;
 }
 
-// ---------------------------------------------------------------- shared small kernels
-// offsets valid: off[0] == 0, non-decreasing, off[T] == n (n < 0: any end)
-__global__ void k_check_offsets(const int64_t* off, int64_t T, int64_t n, int32_t* bad) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i == 0 && (off[0] != 0 || (n >= 0 && off[T] != n))) atomicOr(bad, 1);
-  if (i < T && off[i + 1] < off[i]) atomicOr(bad, 1);
+// ---------------------------------------------------------------- the start of a call
+// One of a call's offset arrays: valid when off[0] == 0, non-decreasing, off[T] == n (n < 0: any end).
+struct Offsets { const int64_t* off; int64_t n; };
+__device__ __forceinline__ bool offsets_bad(const Offsets& o, int64_t T, int64_t i) {
+  if (!o.off) return false;
+  return (i == 0 && (o.off[0] != 0 || (o.n >= 0 && o.off[T] != o.n))) || (i < T && o.off[i + 1] < o.off[i]);
 }
-__global__ void k_zero_i32(int32_t* p) { *p = 0; }
-// trace of each of n records (binary search in off[0..T])
-// The trace of each record: per workgroup of kThreads, kTileN consecutive records (coalesced,
-// record base + kThreads i + thread); one binary search for the trace of the first, then each
-// thread steps over the trace boundaries its records pass (the next trace's offset in a register).
-__global__ __launch_bounds__(kThreads) void k_trace_of(const int64_t* off, int64_t T, int64_t n, const int32_t* bad,
-                                                       uint32_t* tid) {
-  __shared__ int64_t s_t;
-  const int64_t base = (int64_t)blockIdx.x * kTileN;
-  if (base >= n || *bad) return;
-  if (threadIdx.x == 0) {
-    int64_t lo = 0, hi = T - 1;
-    while (lo < hi) {
-      const int64_t mid = (lo + hi + 1) >> 1;
-      if (off[mid] <= base) lo = mid; else hi = mid - 1;
-    }
-    s_t = lo;
+// Checks the offsets, clears the key range and zeroes zero[0..T).  One workgroup (at most
+// kBeginTraces traces) also settles the rest: *bad, the status, and zero output offsets when the
+// batch is rejected or empty.  More workgroups find *bad zeroed, and k_finish settles it.
+constexpr int64_t kBeginTraces = 16384;
+__global__ __launch_bounds__(kScanThreads) void k_begin(Offsets a, Offsets b, Offsets c, int64_t T, bool empty, int64_t* zero,
+                                                       uint64_t* kr, int32_t* bad, int32_t* status, int64_t* out) {
+  __shared__ int s_bad;
+  if (threadIdx.x == 0) s_bad = 0;
+  __syncthreads();
+  bool mine = false;
+  for (int64_t i = (int64_t)blockIdx.x * kScanThreads + threadIdx.x; i <= T; i += (int64_t)gridDim.x * kScanThreads) {
+    mine = mine || offsets_bad(a, T, i) || offsets_bad(b, T, i) || offsets_bad(c, T, i);
+    if (zero && i < T) zero[i] = 0;
+  }
+  if (mine) s_bad = 1;
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    kr[0] = ~0ull;
+    kr[1] = kr[2] = kr[3] = 0;
   }
   __syncthreads();
-  int64_t t = s_t, next = t + 1 < T ? off[t + 1] : INT64_MAX;
-#pragma unroll 4
-  for (int i = 0; i < kItems; ++i) {
-    const int64_t k = base + (int64_t)i * kThreads + threadIdx.x;
-    if (k >= n) break;
-    while (k >= next) {  // empty traces included: the last trace whose first record is at or before k
-      ++t;
-      next = t + 1 < T ? off[t + 1] : INT64_MAX;
-    }
-    tid[k] = (uint32_t)t;
+  if (gridDim.x > 1) {
+    if (threadIdx.x == 0 && s_bad) atomicOr(bad, 1);
+    return;
   }
+  if (threadIdx.x == 0) {
+    *bad = s_bad;
+    *status = s_bad ? XMEM_T_BAD_BATCH : 0;
+  }
+  if (s_bad || empty)
+    for (int64_t i = threadIdx.x; i <= T; i += kScanThreads) out[i] = 0;
 }
-__global__ void k_fill_offsets_zero(int64_t* off, int64_t T, const int32_t* bad, int32_t* status) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+__global__ void k_zero_i32(int32_t* p) { *p = 0; }
+__global__ __launch_bounds__(kThreads) void k_finish(int64_t T, bool empty, const int32_t* bad, int32_t* status, int64_t* out) {
+  const int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
   if (i == 0) *status = *bad ? XMEM_T_BAD_BATCH : 0;
-  if (*bad && i <= T) off[i] = 0;
+  if ((*bad || empty) && i <= T) out[i] = 0;
 }
 
 unsigned grid_of(int64_t n, int t) { return (unsigned)((n + t - 1) / t > 0 ? (n + t - 1) / t : 1); }
 
-// ---------------------------------------------------------------- lifecycles (Section 3.2)
-// keys: address for every record, value = record index
+void begin(Offsets a, Offsets b, Offsets c, int64_t T, bool empty, int64_t* zero, const PrepWs& w, int32_t* status,
+           int64_t* out, hipStream_t st) {
+  const unsigned g = T <= kBeginTraces ? 1u : grid_of(T + 1, kScanThreads);
+  if (g > 1) k_zero_i32<<<1, 1, 0, st>>>(w.bad);
+  k_begin<<<g, kScanThreads, 0, st>>>(a, b, c, T, empty, zero, w.kr, w.bad, status, out);
+}
+void finish(int64_t T, bool empty, const PrepWs& w, int32_t* status, int64_t* out, hipStream_t st) {
+  if (T > kBeginTraces) k_finish<<<grid_of(T + 1, kThreads), kThreads, 0, st>>>(T, empty, w.bad, status, out);
+}
+
 // ---------------------------------------------------------------- key ranges
 // A sort key spans fewer bits than its 64: kr receives the minimum and maximum of the keys that
 // take part, and the OR of each XOR a reference value, whose trailing zeros all differences share.
 // The key then sorts as (key - min) >> trailing zeros, over the passes its width needs.
-__global__ void k_range_init(uint64_t* kr) {
-  kr[0] = ~0ull;
-  kr[1] = 0;
-  kr[2] = 0;
-  kr[3] = 0;
-}
 // a thread's running part of a range
 struct RangePart {
   uint64_t mn = ~0ull, mx = 0, ox = 0;
@@ -478,7 +542,7 @@ __device__ __forceinline__ void range_commit(uint64_t* kr, RangePart p) {
   }
 }
 // the shift and the pass gate of a range: bits of (max - min) >> shift, as an even number of
-// 8-bit passes (so that a gated sort ends in the buffer it started from)
+// passes (so that a gated sort ends in the buffer it started from)
 __device__ __forceinline__ int range_shift(const uint64_t* kr, bool use_tz) {
   return use_tz && kr[2] != 0 ? __builtin_ctzll(kr[2]) : 0;
 }
@@ -488,8 +552,8 @@ __device__ __forceinline__ int range_bits(const uint64_t* kr, int shift) {
   return span ? 64 - __builtin_clzll(span) : 0;
 }
 __device__ __forceinline__ int32_t range_gate(const uint64_t* kr, int shift) {
-  const int passes = (range_bits(kr, shift) + 7) / 8;
-  return 8 * (passes + (passes & 1));
+  const int passes = (range_bits(kr, shift) + kDigit - 1) / kDigit;
+  return kDigit * (passes + (passes & 1));
 }
 
 // addresses of the allocation and free records (0-byte events take no part)
@@ -522,30 +586,49 @@ __global__ __launch_bounds__(kThreads) void k_life_range(const xmem_raw_event* r
 // for a free.  Otherwise the address alone (0 for 0-byte records), sorted in an even number of
 // passes, then again by trace (k_life_trace_keys); the value is the record index.
 constexpr uint64_t kJoint = 1, kJointBuf = 2;
-// Also each record's allocation flag (bytes > 0), scanned after the pairing to number the blocks.
-__global__ void k_life_keys(const xmem_raw_event* raw, const uint32_t* tid, int64_t n, int64_t T, int tbits,
-                            bool second_odd, const int32_t* bad, uint64_t* kr, uint64_t* key, uint32_t* val,
-                            int32_t* gate, int32_t* gate2, uint32_t* flag) {
-  const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (k >= n || *bad) return;
+// Per tile also its allocations (part), and with them the first pass's digit histogram.
+__global__ __launch_bounds__(kThreads) void k_life_keys(const xmem_raw_event* raw, const int64_t* off, int64_t n, int64_t T,
+                                                        int tbits, bool second_odd, const int32_t* bad, uint64_t* kr,
+                                                        uint64_t* key, uint32_t* val, uint32_t* tid, int32_t* gate,
+                                                        int32_t* gate2, uint32_t* hist, int64_t ntiles, uint32_t* part) {
+  if (*bad) return;
+  __shared__ uint32_t h[kBins];
+  __shared__ uint32_t s_cnt;
+  if (threadIdx.x == 0) s_cnt = 0;
+  hist_clear(h);
+  const int64_t base = (int64_t)blockIdx.x * kTileN;
+  TraceStep tr(off, T, tile_trace(off, T, base));
   const int sh = range_shift(kr, true), b = range_bits(kr, sh);
+  const uint64_t lowest = kr[0];
   const bool joint = n <= INT32_MAX && b + tbits <= 64;
-  if (k == 0) {
-    const int jp = (b + tbits + 7) / 8;  // passes of the joint sort
-    *gate = joint ? 8 * jp : range_gate(kr, sh);
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    const int jp = (b + tbits + kDigit - 1) / kDigit;  // passes of the joint sort
+    *gate = joint ? kDigit * jp : range_gate(kr, sh);
     *gate2 = joint ? 0 : 64;
     kr[5] = (joint ? kJoint : 0) | ((joint ? (jp & 1) : second_odd) ? kJointBuf : 0) | ((uint64_t)b << 8);
   }
-  const xmem_raw_event r = raw[k];
-  const uint64_t a = (r.addr - kr[0]) >> sh;
-  flag[k] = r.bytes > 0 ? 1u : 0u;
-  if (joint) {
-    key[k] = r.bytes != 0 ? ((uint64_t)tid[k] << b) | a : (uint64_t)T << b;
-    val[k] = (uint32_t)k | (r.bytes < 0 ? 0x80000000u : 0u);
-  } else {
-    key[k] = r.bytes != 0 ? a : 0;
-    val[k] = (uint32_t)k;
+  uint32_t allocs = 0;
+#pragma unroll 4
+  for (int i = 0; i < kItems; ++i) {
+    const int64_t k = base + (int64_t)i * kThreads + threadIdx.x;
+    const bool ok = k < n;
+    uint64_t x = 0;
+    if (ok) {
+      tr.to(off, T, k);
+      const uint64_t addr = raw[k].addr;
+      const int64_t bytes = raw[k].bytes;
+      const uint64_t a = (addr - lowest) >> sh;
+      x = joint ? (bytes != 0 ? ((uint64_t)tr.t << b) | a : (uint64_t)T << b) : bytes != 0 ? a : 0;
+      key[k] = x;
+      val[k] = (uint32_t)k | (joint && bytes < 0 ? 0x80000000u : 0u);
+      if (!joint) tid[k] = (uint32_t)tr.t;
+      allocs += bytes > 0 ? 1u : 0u;
+    }
+    hist_add(h, ok, (uint32_t)x & (kBins - 1));
   }
+  atomicAdd(&s_cnt, allocs);
+  hist_store(h, hist, ntiles);
+  if (threadIdx.x == 0) part[blockIdx.x] = s_cnt;
 }
 // keys after the address sort: trace of the record (T for 0-byte events, which sort last)
 __global__ void k_life_trace_keys(const xmem_raw_event* raw, const uint32_t* tid, int64_t n, int64_t T,
@@ -607,30 +690,37 @@ __global__ void k_life_pair(const xmem_raw_event* raw, const uint32_t* tid, cons
     if (!closes) atomicAdd((unsigned long long*)&unmatched[tid[k]], 1ull);
   }
 }
-__global__ void k_life_emit(const xmem_raw_event* raw, const int32_t* cat, int64_t n, const int32_t* bad,
-                            const uint32_t* bidx, const int64_t* tfree, xmem_block* blocks) {
-  const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (k >= n || *bad) return;
-  const xmem_raw_event r = raw[k];
-  if (r.bytes <= 0) return;
-  xmem_block b;
-  b.size = r.bytes;
-  b.t_alloc = r.ts;
-  b.t_free = tfree[k];
-  b.category = cat ? cat[k] : XMEM_CAT_OTHER;
-  b.pad = 0;
-  blocks[bidx[k]] = b;
-}
-// block offsets: allocations before each trace start (exclusive scan of the flags)
-__global__ void k_life_offsets(const int64_t* off, int64_t T, int64_t n, const int32_t* bad, const uint32_t* scan,
-                               const uint32_t* total, int64_t* boff) {
-  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t > T || *bad) return;
-  boff[t] = off[t] < n ? (int64_t)scan[off[t]] : (int64_t)*total;
-}
-__global__ void k_zero_i64(int64_t* p, int64_t n) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) p[i] = 0;
+// the blocks in allocation order (part: allocations before each tile), and the traces' offsets
+__global__ __launch_bounds__(kThreads) void k_life_emit(const xmem_raw_event* raw, const int32_t* cat, const int64_t* off,
+                                                        int64_t T, int64_t n, const int32_t* bad, const uint32_t* part,
+                                                        const int64_t* tfree, xmem_block* blocks, int64_t* boff) {
+  if (*bad) return;
+  __shared__ TileFlags f;
+  const int64_t base = (int64_t)blockIdx.x * kTileN;
+  int64_t bytes[kItems];
+#pragma unroll
+  for (int i = 0; i < kItems; ++i) {
+    const int64_t k = base + (int64_t)i * kThreads + threadIdx.x;
+    bytes[i] = k < n ? raw[k].bytes : 0;
+    flags_put(f, i, bytes[i] > 0);
+  }
+  flags_scan(f);
+  const uint32_t at = part[blockIdx.x];
+#pragma unroll 4
+  for (int i = 0; i < kItems; ++i) {
+    const int r = i * kThreads + threadIdx.x;
+    const int64_t k = base + r;
+    if (bytes[i] > 0) {
+      xmem_block b;
+      b.size = bytes[i];
+      b.t_alloc = raw[k].ts;
+      b.t_free = tfree[k];
+      b.category = cat ? cat[k] : XMEM_CAT_OTHER;
+      b.pad = 0;
+      blocks[at + flags_before(f, r)] = b;
+    }
+  }
+  tile_offsets(off, T, n, base, f, at, 0, boff);
 }
 
 // ---------------------------------------------------------------- attribution (Section 3.2)
@@ -640,131 +730,151 @@ __device__ __forceinline__ int64_t win_parent(const xmem_window* w, int64_t i) {
   return (p >= 0 && p < i) ? p : -1;
 }
 // per window: the end of its nearest enclosing component (kPersist: none), and whether it lies in
-// an optimizer.step() phase (itself or an enclosing window is a component of category optimizer)
-__global__ void k_att_comp_end(const xmem_window* win, const int64_t* woff, int64_t T, int64_t nw, const int32_t* bad,
-                               int64_t* comp_end, uint32_t* in_step) {
-  const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (g >= nw || *bad) return;
-  int64_t lo = 0, hi = T - 1;
-  while (lo < hi) {
-    const int64_t mid = (lo + hi + 1) >> 1;
-    if (woff[mid] <= g) lo = mid; else hi = mid - 1;
+// an optimizer.step() phase (itself or an enclosing window is a component of category optimizer);
+// and two empty slots of the parameter-size sets per block
+__global__ __launch_bounds__(kThreads) void k_att_windows(const xmem_window* win, const int64_t* woff, int64_t T, int64_t nw,
+                                                          int64_t nb, const int32_t* bad, int64_t* comp_end,
+                                                          uint32_t* in_step, uint64_t* tab) {
+  if (*bad) return;
+  const int64_t base = (int64_t)blockIdx.x * kTileN;
+#pragma unroll
+  for (int i = 0; i < kItems; ++i) {
+    const int64_t k = base + (int64_t)i * kThreads + threadIdx.x;
+    if (k < nb) tab[k] = 0;
   }
-  const xmem_window* w = win + woff[lo];
-  int64_t c = win_parent(w, g - woff[lo]);
-  while (c >= 0 && w[c].kind != XMEM_WIN_COMPONENT) c = win_parent(w, c);
-  comp_end[g] = c >= 0 ? w[c].end : kPersist;
-  uint32_t step = 0;
-  for (int64_t a = g - woff[lo]; a >= 0 && !step; a = win_parent(w, a))
-    step = w[a].kind == XMEM_WIN_COMPONENT && w[a].category == XMEM_CAT_OPTIMIZER;
-  in_step[g] = step;
-}
-constexpr int64_t kStepCandidate = int64_t(1) << 32;  // role bit: a product allocated in an optimizer.step() phase
-// the window each block links to (index in its trace, -1 if none), its role by the operator rule
-// (with kStepCandidate for a product in an optimizer.step() phase), and whether it is a product of
-// a parameter operator (pflag)
-__global__ void k_att_blocks(const xmem_block* blocks, const uint32_t* btid, int64_t nb, const xmem_window* win,
-                             const int64_t* woff, const int64_t* comp_end, const uint32_t* in_step,
-                             const int32_t* bad, int32_t* bwin, uint32_t* flag, int64_t* role, uint32_t* pflag) {
-  const int64_t b = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (b >= nb || *bad) return;
-  const uint32_t t = btid[b];
-  const int64_t base = woff[t], n = woff[t + 1] - base;
-  const xmem_window* w = win + base;
-  const int64_t ta = blocks[b].t_alloc, tf = blocks[b].t_free;
-  int64_t lo = 0, hi = n;  // last window that starts no later than the allocation
-  while (lo < hi) {
-    const int64_t mid = (lo + hi) >> 1;
-    if (w[mid].start <= ta) lo = mid + 1; else hi = mid;
-  }
-  int64_t i = lo - 1;
-  while (i >= 0 && w[i].end < ta) i = win_parent(w, i);  // up to the innermost window containing it
-  const bool step = i >= 0 && in_step[base + i];
-  int32_t link = -1;
-  int64_t cat = XMEM_CAT_OTHER;
-  bool product = false;
-  for (; i >= 0; i = win_parent(w, i)) {
-    const xmem_window x = w[i];
-    if (x.kind != XMEM_WIN_OPERATOR) continue;
-    if (x.start < ta && tf < x.end) { link = (int32_t)i; break; }  // (i) a temporary: strictly inside the window
-    if (tf > comp_end[base + i]) {                                   // (ii) a product
-      link = (int32_t)i;
-      cat = x.category;
-      product = true;
-      break;
+  if (base >= nw) return;
+  TraceStep tr(woff, T, tile_trace(woff, T, base));
+#pragma unroll 2
+  for (int i = 0; i < kItems; ++i) {
+    const int64_t g = base + (int64_t)i * kThreads + threadIdx.x;
+    if (g >= nw) break;
+    tr.to(woff, T, g);
+    const xmem_window* w = win + woff[tr.t];
+    const int64_t me = g - woff[tr.t];
+    // one climb for both: up to the nearest component for its end, on to the root for the phase
+    int64_t end = kPersist;
+    bool found = false;
+    uint32_t step = w[me].kind == XMEM_WIN_COMPONENT && w[me].category == XMEM_CAT_OPTIMIZER;
+    for (int64_t a = win_parent(w, me); a >= 0 && !(found && step); a = win_parent(w, a)) {
+      const bool comp = w[a].kind == XMEM_WIN_COMPONENT;
+      if (comp && !found) {
+        end = w[a].end;
+        found = true;
+      }
+      step |= comp && w[a].category == XMEM_CAT_OPTIMIZER;
     }
+    comp_end[g] = end;
+    in_step[g] = step;
   }
-  if (bwin) bwin[b] = link;
-  flag[b] = link >= 0 ? 1u : 0u;
-  role[b] = cat | (product && step ? kStepCandidate : 0);
-  pflag[b] = product && cat == XMEM_CAT_PARAMETER ? 1u : 0u;
 }
 // Section 3.3 item 5: the parameter sizes of each trace as an open-addressing hash set of block
-// indices + 1 (0: empty), two slots per parameter block at [2 * first, 2 * end) of the trace's
-// parameters in the exclusive scan pscan of pflag.  At most half full, so every probe sequence
-// reaches an empty slot.
+// indices + 1 (0: empty), at two slots per block of the trace, so at most half full: every probe
+// sequence reaches an empty slot.
 struct ParamSet { int64_t base, cap; };
-__device__ __forceinline__ ParamSet param_set(const int64_t* boff, int64_t nb, const uint32_t* pscan,
-                                              const uint32_t* total, uint32_t t) {
-  const int64_t lo = boff[t], hi = boff[t + 1];
-  const int64_t ps = lo < nb ? pscan[lo] : *total, pe = hi < nb ? pscan[hi] : *total;
-  return ParamSet{2 * ps, 2 * (pe - ps)};
+__device__ __forceinline__ ParamSet param_set(const int64_t* boff, int64_t t) {
+  return ParamSet{2 * boff[t], 2 * (boff[t + 1] - boff[t])};
 }
 __device__ __forceinline__ uint64_t size_hash(int64_t size) {
   return ((uint64_t)size * 0x9E3779B97F4A7C15ull) >> 32;
 }
-__global__ void k_opt_flags_keep(const uint32_t* pflag, int64_t nb, const int32_t* bad, uint32_t* copy) {
-  const int64_t b = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (b >= nb || *bad) return;
-  copy[b] = pflag[b];
-}
-// each parameter block clears its two slots of its trace's set
-__global__ void k_opt_clear(const uint32_t* pflag_scan, const uint32_t* pflag, int64_t nb, const int32_t* bad,
-                            uint32_t* tab) {
-  const int64_t b = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (b >= nb || *bad || !pflag[b]) return;
-  tab[2 * (int64_t)pflag_scan[b]] = 0;
-  tab[2 * (int64_t)pflag_scan[b] + 1] = 0;
-}
-__global__ void k_opt_insert(const xmem_block* blocks, const uint32_t* btid, const int64_t* boff, int64_t nb,
-                             const uint32_t* pflag, const uint32_t* pscan, const uint32_t* total, const int32_t* bad,
-                             uint32_t* tab) {
-  const int64_t b = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (b >= nb || *bad || !pflag[b]) return;
-  const ParamSet ps = param_set(boff, nb, pscan, total, btid[b]);
-  const int64_t size = blocks[b].size;
-  for (int64_t s = (int64_t)(size_hash(size) % (uint64_t)ps.cap);; s = s + 1 == ps.cap ? 0 : s + 1) {
-    const uint32_t old = atomicCAS(&tab[ps.base + s], 0u, (uint32_t)(b + 1));
-    if (old == 0 || blocks[old - 1].size == size) return;  // inserted, or the size is there already
-  }
-}
-// a product in an optimizer.step() phase whose size is a parameter's becomes an optimizer state
-__global__ void k_opt_mark(const xmem_block* blocks, const uint32_t* btid, const int64_t* boff, int64_t nb,
-                           const uint32_t* pscan, const uint32_t* total, const int32_t* bad, const uint32_t* tab,
-                           int64_t* role) {
-  const int64_t b = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (b >= nb || *bad) return;
-  const int64_t r = role[b];
-  if (!(r & kStepCandidate)) return;
-  int64_t out = r & ~kStepCandidate;
-  const ParamSet ps = param_set(boff, nb, pscan, total, btid[b]);
-  if (ps.cap > 0) {
-    const int64_t size = blocks[b].size;
-    for (int64_t s = (int64_t)(size_hash(size) % (uint64_t)ps.cap);; s = s + 1 == ps.cap ? 0 : s + 1) {
-      const uint32_t v = tab[ps.base + s];
-      if (v == 0) break;
-      if (blocks[v - 1].size == size) { out = XMEM_CAT_OPTIMIZER; break; }
+constexpr uint32_t kKept = 1u << 31, kStepCandidate = 1u << 30;  // role word: linked; a product in an optimizer.step() phase
+// The window each block links to (index in its trace, -1 if none) and its role by the operator rule
+// (role: the category below kStepCandidate's bit); a parameter's size goes into its trace's set.
+// Per tile its kept blocks (part).
+__global__ __launch_bounds__(kThreads) void k_att_blocks(const xmem_block* blocks, const int64_t* boff, int64_t T, int64_t nb,
+                                                         const xmem_window* win, const int64_t* woff,
+                                                         const int64_t* comp_end, const uint32_t* in_step,
+                                                         const int32_t* bad, int32_t* bwin, uint32_t* role, int32_t* cats,
+                                                         uint32_t* tab, uint32_t* part) {
+  if (*bad) return;
+  __shared__ uint32_t s_cnt;
+  if (threadIdx.x == 0) s_cnt = 0;
+  const int64_t base = (int64_t)blockIdx.x * kTileN;
+  TraceStep tr(boff, T, tile_trace(boff, T, base));  // (its barrier orders s_cnt too)
+  uint32_t kept = 0;
+  for (int i = 0; i < kItems; ++i) {
+    const int64_t b = base + (int64_t)i * kThreads + threadIdx.x;
+    if (b >= nb) break;
+    tr.to(boff, T, b);
+    const int64_t wbase = woff[tr.t], n = woff[tr.t + 1] - wbase;
+    const xmem_window* w = win + wbase;
+    const int64_t ta = blocks[b].t_alloc, tf = blocks[b].t_free, size = blocks[b].size;
+    int64_t lo = 0, hi = n;  // last window that starts no later than the allocation
+    while (lo < hi) {
+      const int64_t mid = (lo + hi) >> 1;
+      if (w[mid].start <= ta) lo = mid + 1; else hi = mid;
+    }
+    int64_t j = lo - 1;
+    while (j >= 0 && w[j].end < ta) j = win_parent(w, j);  // up to the innermost window containing it
+    const bool step = j >= 0 && in_step[wbase + j];
+    int32_t link = -1, cat = XMEM_CAT_OTHER;
+    bool product = false;
+    for (; j >= 0; j = win_parent(w, j)) {
+      const xmem_window x = w[j];
+      if (x.kind != XMEM_WIN_OPERATOR) continue;
+      if (x.start < ta && tf < x.end) { link = (int32_t)j; break; }  // (i) a temporary: strictly inside the window
+      if (tf > comp_end[wbase + j]) {                                  // (ii) a product
+        link = (int32_t)j;
+        cat = x.category;
+        product = true;
+        break;
+      }
+    }
+    if (bwin) bwin[b] = link;
+    role[b] = (link >= 0 ? kKept : 0u) | (product && step ? kStepCandidate : 0u);
+    cats[b] = cat;
+    kept += link >= 0 ? 1u : 0u;
+    if (product && cat == XMEM_CAT_PARAMETER) {
+      const ParamSet ps = param_set(boff, tr.t);
+      for (int64_t s = (int64_t)(size_hash(size) % (uint64_t)ps.cap);; s = s + 1 == ps.cap ? 0 : s + 1) {
+        const uint32_t old = atomicCAS(&tab[ps.base + s], 0u, (uint32_t)(b + 1));
+        if (old == 0 || blocks[old - 1].size == size) break;  // inserted, or the size is there already
+      }
     }
   }
-  role[b] = out;
+  atomicAdd(&s_cnt, kept);
+  __syncthreads();
+  if (threadIdx.x == 0) part[blockIdx.x] = s_cnt;
 }
-__global__ void k_att_emit(const xmem_block* blocks, int64_t nb, const int32_t* bad, const uint32_t* flag,
-                           const uint32_t* idx, const int64_t* role, xmem_block* kept) {
-  const int64_t b = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (b >= nb || *bad || !flag[b]) return;
-  xmem_block x = blocks[b];
-  x.category = (int32_t)(role[b] & ~kStepCandidate);
-  kept[idx[b]] = x;
+// The kept blocks in order with their roles (a product in an optimizer.step() phase whose size is a
+// parameter's is an optimizer state), and the traces' offsets.
+__global__ __launch_bounds__(kThreads) void k_att_emit(const xmem_block* blocks, const int64_t* boff, int64_t T, int64_t nb,
+                                                       const int32_t* bad, const uint32_t* role, const int32_t* cats,
+                                                       const uint32_t* tab, const uint32_t* part, xmem_block* kept,
+                                                       int64_t* koff) {
+  if (*bad) return;
+  __shared__ TileFlags f;
+  const int64_t base = (int64_t)blockIdx.x * kTileN;
+  uint32_t rl[kItems];
+#pragma unroll
+  for (int i = 0; i < kItems; ++i) {
+    const int64_t b = base + (int64_t)i * kThreads + threadIdx.x;
+    rl[i] = b < nb ? role[b] : 0u;
+    flags_put(f, i, rl[i] & kKept);
+  }
+  flags_scan(f);
+  const uint32_t at = part[blockIdx.x];
+  TraceStep tr(boff, T, tile_trace(boff, T, base));
+#pragma unroll 4
+  for (int i = 0; i < kItems; ++i) {
+    const int r = i * kThreads + threadIdx.x;
+    const int64_t b = base + r;
+    if (rl[i] & kKept) {
+      xmem_block x = blocks[b];
+      x.category = cats[b];
+      if (rl[i] & kStepCandidate) {
+        tr.to(boff, T, b);
+        const ParamSet ps = param_set(boff, tr.t);
+        for (int64_t s = (int64_t)(size_hash(x.size) % (uint64_t)ps.cap);; s = s + 1 == ps.cap ? 0 : s + 1) {
+          const uint32_t v = tab[ps.base + s];
+          if (v == 0) break;
+          if (blocks[v - 1].size == x.size) { x.category = XMEM_CAT_OPTIMIZER; break; }
+        }
+      }
+      kept[at + flags_before(f, r)] = x;
+    }
+  }
+  tile_offsets(boff, T, nb, base, f, at, 0, koff);
 }
 
 // ---------------------------------------------------------------- orchestration (Section 3.3)
@@ -777,104 +887,118 @@ __device__ __forceinline__ int64_t next_marker(const int64_t* v, int64_t lo, int
   }
   return a < hi ? v[a] : kPersist;
 }
-// retimed free of each block, and the two sort records of each block
-// (2b: allocation, 2b+1: free); first key group: the rank at equal times
-__global__ void k_orch_retime(const xmem_block* blocks, const uint32_t* btid, int64_t nb, const int64_t* steps,
-                              const int64_t* soff, const int64_t* zg, const int64_t* zoff, const int32_t* bad,
-                              int64_t* tfr, uint64_t* key, uint32_t* val) {
-  const int64_t b = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (b >= nb || *bad) return;
-  const xmem_block x = blocks[b];
-  const uint32_t t = btid[b];
-  int64_t f = x.t_free;
-  switch (x.category) {
-    case XMEM_CAT_PARAMETER:
-    case XMEM_CAT_OPTIMIZER:
-      f = kPersist;
-      break;
-    case XMEM_CAT_BATCH: {
-      const int64_t e = next_marker(steps, soff[t], soff[t + 1], x.t_alloc);
-      f = f < e ? f : e;
-      break;
-    }
-    case XMEM_CAT_GRADIENT:
-      f = next_marker(zg, zoff[t], zoff[t + 1], x.t_alloc);
-      break;
-    default:
-      break;
-  }
-  if (f != kPersist && f < x.t_alloc) f = x.t_alloc;
-  tfr[b] = f;
-  key[2 * b] = 1;                          // allocation
-  key[2 * b + 1] = f == x.t_alloc ? 2 : 0;  // free of a block allocated at that time, or of an earlier one
-  val[2 * b] = (uint32_t)(2 * b);
-  val[2 * b + 1] = (uint32_t)(2 * b + 1);
-}
-// the times of the allocation and free records (sign bit flipped: signed order as unsigned); a
-// persistent block's free takes no part (it sorts last by its trace key)
-__global__ __launch_bounds__(kThreads) void k_orch_range(const xmem_block* blocks, const int64_t* tfr, int64_t nb,
-                                                         const int32_t* bad, uint64_t* kr) {
+// Retimed free of each block; the range of the times (sign bit flipped: signed order as unsigned) of
+// the allocation and free records that take part (a persistent block's free does not: it sorts
+// last by its trace); per tile the blocks that are freed (part).
+__global__ __launch_bounds__(kThreads) void k_orch_retime(const xmem_block* blocks, const int64_t* boff, int64_t T, int64_t nb,
+                                                          const int64_t* steps, const int64_t* soff, const int64_t* zg,
+                                                          const int64_t* zoff, const int32_t* bad, int64_t* tfr, uint64_t* kr,
+                                                          uint32_t* part) {
   if (*bad) return;
+  __shared__ uint32_t s_cnt;
+  if (threadIdx.x == 0) s_cnt = 0;
+  const int64_t base = (int64_t)blockIdx.x * kTileN;
+  TraceStep tr(boff, T, tile_trace(boff, T, base));  // (its barrier orders s_cnt too)
   RangePart p;
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  for (int64_t b0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; b0 < nb; b0 += kRangeUnroll * stride) {
-    int64_t ta[kRangeUnroll], tf[kRangeUnroll];
-#pragma unroll
-    for (int u = 0; u < kRangeUnroll; ++u) {
-      const int64_t b = b0 + u * stride;
-      ta[u] = b < nb ? blocks[b].t_alloc : 0;
-      tf[u] = b < nb ? tfr[b] : kPersist;
+  uint32_t freed = 0;
+#pragma unroll 4
+  for (int i = 0; i < kItems; ++i) {
+    const int64_t b = base + (int64_t)i * kThreads + threadIdx.x;
+    if (b >= nb) break;
+    tr.to(boff, T, b);
+    const xmem_block x = blocks[b];
+    int64_t f = x.t_free;
+    switch (x.category) {
+      case XMEM_CAT_PARAMETER:
+      case XMEM_CAT_OPTIMIZER:
+        f = kPersist;
+        break;
+      case XMEM_CAT_BATCH: {
+        const int64_t e = next_marker(steps, soff[tr.t], soff[tr.t + 1], x.t_alloc);
+        f = f < e ? f : e;
+        break;
+      }
+      case XMEM_CAT_GRADIENT:
+        f = next_marker(zg, zoff[tr.t], zoff[tr.t + 1], x.t_alloc);
+        break;
+      default:
+        break;
     }
-#pragma unroll
-    for (int u = 0; u < kRangeUnroll; ++u) {
-      p.add(b0 + u * stride < nb, (uint64_t)ta[u] ^ (1ull << 63), 0);
-      p.add(tf[u] != kPersist, (uint64_t)tf[u] ^ (1ull << 63), 0);
-    }
+    if (f != kPersist && f < x.t_alloc) f = x.t_alloc;
+    tfr[b] = f;
+    p.add(true, (uint64_t)x.t_alloc ^ (1ull << 63), 0);
+    p.add(f != kPersist, (uint64_t)f ^ (1ull << 63), 0);
+    freed += f != kPersist ? 1u : 0u;
   }
-  range_commit(kr, p);
+  atomicAdd(&s_cnt, freed);
+  range_commit(kr, p);  // (its barrier orders s_cnt too)
+  if (threadIdx.x == 0) part[blockIdx.x] = s_cnt;
 }
-// The orchestration sort's layout, chosen on the device from the time range (kr[5]: bit 0 set
-// for the joint key, bit 1 when the sorted records end in the second buffer, bits 8.. the time
-// bits tb).  Joint key, when trace, time and rank fit in 64 bits together:
-// (trace << (tb + 2)) | (time << 2) | rank, the free of a persistent block last (T << (tb + 2));
-// one sort of tbits + tb + 2 bits.  Otherwise three key groups as separate sorts: the rank
-// (k_orch_retime), the time in an even number of passes, then the trace.  The host launches
-// the same kernels either way; the gates skip the passes a layout does not take: gate[0] the
-// time sort (or the joint sort), gate[1] the rank sort, gate[2] the trace sort.
-__global__ void k_orch_mode(uint64_t* kr, int tbits, bool trace_odd, int32_t* gate) {
+// The sort records of each block (2b: its allocation, 2b + 1: its free) and the traces' word offsets.
+// The layout is chosen on the device from the time range (kr[5]: bit 0 set for the joint key, bit 1
+// when the sorted records end in the second buffer, bits 8.. the time bits tb).  Joint key, when
+// trace, time and rank fit in 64 bits together: (trace << (tb + 2)) | (time << 2) | rank, the free of a
+// persistent block last (T << (tb + 2)); one sort of tbits + tb + 2 bits, from the second buffer.
+// Rank at equal times: a free of an earlier block 0, an allocation 1, a free of a block allocated at
+// that time 2.  Otherwise three key groups as separate sorts: the rank (here, in the first buffer),
+// the time in an even number of passes, then the trace.  The host launches the same kernels either
+// way; the gates skip the passes a layout does not take: gate[0] the time sort (or the joint sort),
+// gate[1] the rank sort, gate[2] the trace sort.
+__global__ __launch_bounds__(kThreads) void k_orch_keys(const xmem_block* blocks, const int64_t* boff, int64_t T, int64_t nb,
+                                                        const int64_t* tfr, int tbits, bool trace_odd, const int32_t* bad,
+                                                        uint64_t* kr, int32_t* gate, uint64_t* ka, uint32_t* va,
+                                                        uint64_t* kb, uint32_t* vb, uint32_t* tid, const uint32_t* part,
+                                                        uint32_t* total, int64_t* eoff) {
+  if (*bad) return;
+  __shared__ TileFlags f;
+  const int64_t base = (int64_t)blockIdx.x * kTileN;
   const int tb = range_bits(kr, 0);
   const bool joint = tbits + tb + 2 <= 64;
-  const int jp = (tbits + tb + 2 + 7) / 8;
-  gate[0] = joint ? 8 * jp : range_gate(kr, 0);
-  gate[1] = joint ? 0 : 64;
-  gate[2] = joint ? 0 : 64;
-  // the time sort starts in the second buffer; the separate layout then takes the trace passes
-  const bool in_b = joint ? !(jp & 1) : !trace_odd;
-  kr[5] = (joint ? kJoint : 0) | (in_b ? kJointBuf : 0) | ((uint64_t)tb << 8);
-}
-// second key group: the time, rebased to the batch's earliest; with the joint key, the whole key
-// of every record (in record order, into the buffer the time sort starts from)
-__global__ void k_orch_time_keys(const xmem_block* blocks, const uint32_t* btid, const int64_t* tfr, int64_t n,
-                                 int64_t T, const int32_t* bad, const uint64_t* kr, uint32_t* val, uint64_t* key) {
-  const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (p >= n || *bad) return;
-  const uint64_t meta = kr[5];
-  if (meta & kJoint) {
-    const int tb = (int)(meta >> 8);
-    const int64_t b = p >> 1;
-    const int64_t ta = blocks[b].t_alloc, f = tfr[b];
-    uint64_t k;
-    if (p & 1) {
-      k = f == kPersist ? (uint64_t)T << (tb + 2)
-                        : ((uint64_t)btid[b] << (tb + 2)) | ((((uint64_t)f ^ (1ull << 63)) - kr[0]) << 2) |
-                              (f == ta ? 2u : 0u);
-    } else {
-      k = ((uint64_t)btid[b] << (tb + 2)) | ((((uint64_t)ta ^ (1ull << 63)) - kr[0]) << 2) | 1u;
-    }
-    key[p] = k;
-    val[p] = (uint32_t)p;
-    return;
+  const uint64_t lowest = kr[0];
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    const int jp = (tbits + tb + 2 + kDigit - 1) / kDigit;
+    gate[0] = joint ? kDigit * jp : range_gate(kr, 0);
+    gate[1] = joint ? 0 : 64;
+    gate[2] = joint ? 0 : 64;
+    // the time sort starts in the second buffer; the separate layout then takes the trace passes
+    const bool in_b = joint ? !(jp & 1) : !trace_odd;
+    kr[5] = (joint ? kJoint : 0) | (in_b ? kJointBuf : 0) | ((uint64_t)tb << 8);
+    *total += (uint32_t)nb;  // words: an allocation each, and the frees counted so far
   }
+  TraceStep tr(boff, T, tile_trace(boff, T, base));
+#pragma unroll 4
+  for (int i = 0; i < kItems; ++i) {
+    const int64_t b = base + (int64_t)i * kThreads + threadIdx.x;
+    const bool ok = b < nb;
+    const int64_t fr = ok ? tfr[b] : kPersist;
+    flags_put(f, i, fr != kPersist);
+    if (ok) {
+      tr.to(boff, T, b);
+      const int64_t ta = blocks[b].t_alloc;
+      if (joint) {
+        const uint64_t t = (uint64_t)tr.t << (tb + 2);
+        kb[2 * b] = t | ((((uint64_t)ta ^ (1ull << 63)) - lowest) << 2) | 1u;
+        kb[2 * b + 1] = fr == kPersist ? (uint64_t)T << (tb + 2)
+                                       : t | ((((uint64_t)fr ^ (1ull << 63)) - lowest) << 2) | (fr == ta ? 2u : 0u);
+        vb[2 * b] = (uint32_t)(2 * b);
+        vb[2 * b + 1] = (uint32_t)(2 * b + 1);
+      } else {
+        ka[2 * b] = 1;
+        ka[2 * b + 1] = fr == ta ? 2 : 0;
+        va[2 * b] = (uint32_t)(2 * b);
+        va[2 * b + 1] = (uint32_t)(2 * b + 1);
+        tid[b] = (uint32_t)tr.t;
+      }
+    }
+  }
+  flags_scan(f);
+  tile_offsets(boff, T, nb, base, f, (uint32_t)base + part[blockIdx.x], 1, eoff);
+}
+// second key group of the separate layout: the time, rebased to the batch's earliest
+__global__ void k_orch_time_keys(const xmem_block* blocks, const int64_t* tfr, int64_t n, const int32_t* bad,
+                                 const uint64_t* kr, const uint32_t* val, uint64_t* key) {
+  const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (p >= n || *bad || (kr[5] & kJoint)) return;
   const uint32_t r = val[p];
   const int64_t tm = (r & 1) ? tfr[r >> 1] : blocks[r >> 1].t_alloc;
   key[p] = ((r & 1) && tm == kPersist) ? 0 : ((uint64_t)tm ^ (1ull << 63)) - kr[0];
@@ -887,29 +1011,24 @@ __global__ void k_orch_trace_keys(const uint32_t* btid, const int64_t* tfr, int6
   const uint32_t r = val[p];
   key[p] = ((r & 1) && tfr[r >> 1] == kPersist) ? (uint64_t)T : (uint64_t)btid[r >> 1];
 }
-// words per block: 1 + (a free after retiming)
-__global__ void k_orch_counts(const int64_t* tfr, int64_t nb, const int32_t* bad, uint32_t* cnt) {
-  const int64_t b = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (b >= nb || *bad) return;
-  cnt[b] = tfr[b] == kPersist ? 1u : 2u;
-}
-__global__ void k_orch_offsets(const int64_t* boff, int64_t T, int64_t nb, const int32_t* bad, const uint32_t* scan,
-                               const uint32_t* total, int64_t* eoff) {
-  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t > T || *bad) return;
-  eoff[t] = boff[t] < nb ? (int64_t)scan[boff[t]] : (int64_t)*total;
-}
-// position of each allocation's word within its trace (the joint key holds the trace)
-__global__ void k_orch_apos(const uint32_t* btid, const int64_t* eoff, const uint32_t* total, const int32_t* bad,
-                            const uint64_t* kr, const uint64_t* ka, const uint32_t* va, const uint64_t* kb,
-                            const uint32_t* vb, uint32_t* apos) {
-  const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (*bad || p >= (int64_t)*total) return;
-  const uint64_t meta = kr[5];
-  const uint32_t r = ((meta & kJointBuf) ? vb : va)[p];
-  if (r & 1) return;
-  const uint64_t t = (meta & kJoint) ? ((meta & kJointBuf) ? kb : ka)[p] >> ((int)(meta >> 8) + 2) : btid[r >> 1];
-  apos[r >> 1] = (uint32_t)(p - eoff[t]);
+// position of each allocation's word within its trace
+__global__ __launch_bounds__(kThreads) void k_orch_apos(const int64_t* eoff, int64_t T, const uint32_t* total,
+                                                        const int32_t* bad, const uint64_t* kr, const uint32_t* va,
+                                                        const uint32_t* vb, uint32_t* apos) {
+  const int64_t base = (int64_t)blockIdx.x * kTileN;
+  if (*bad || base >= (int64_t)*total) return;
+  const int64_t m = (int64_t)*total;
+  const uint32_t* val = (kr[5] & kJointBuf) ? vb : va;
+  TraceStep tr(eoff, T, tile_trace(eoff, T, base));
+#pragma unroll 4
+  for (int i = 0; i < kItems; ++i) {
+    const int64_t p = base + (int64_t)i * kThreads + threadIdx.x;
+    if (p >= m) break;
+    const uint32_t r = val[p];
+    if (r & 1) continue;
+    tr.to(eoff, T, p);
+    apos[r >> 1] = (uint32_t)(p - eoff[tr.t]);
+  }
 }
 __global__ void k_orch_words(const xmem_block* blocks, const uint32_t* total, const int32_t* bad, const uint64_t* kr,
                              const uint32_t* va, const uint32_t* vb, const uint32_t* apos, uint64_t* events) {
@@ -942,36 +1061,30 @@ int xmem_lifecycles(const xmem_raw_event* d_raw, const int32_t* d_category, cons
   PrepWs w;
   carve(d_workspace, n_traces, total_raw, &w);
   const int64_t T = n_traces, n = total_raw;
-  k_zero_i32<<<1, 1, 0, st>>>(w.bad);
-  k_check_offsets<<<grid_of(T + 1, 256), 256, 0, st>>>(d_raw_offsets, T, n, w.bad);
-  if (d_unmatched_frees && T > 0) k_zero_i64<<<grid_of(T, 256), 256, 0, st>>>(d_unmatched_frees, T);
-  if (n > 0 && T > 0) {
-    k_trace_of<<<(unsigned)tiles_of(n), kThreads, 0, st>>>(d_raw_offsets, T, n, w.bad, w.tid);
+  const bool empty = n == 0 || T == 0;
+  begin({d_raw_offsets, n}, {nullptr, 0}, {nullptr, 0}, T, empty, d_unmatched_frees, w, d_status, d_block_offsets, st);
+  if (!empty) {
+    const int64_t nt = tiles_of(n);
     int32_t* gate = reinterpret_cast<int32_t*>(w.kr + 3);
     int32_t* gate2 = reinterpret_cast<int32_t*>(w.kr + 4);
     int tbits = 0;
     while (tbits < 63 && (T >> tbits) != 0) ++tbits;  // bits of the trace field (0..T)
-    const bool second_odd = (bits_for(T) / 8) & 1;
-    k_range_init<<<1, 1, 0, st>>>(w.kr);
+    const int tp = passes_for(T);
     k_life_range<<<(unsigned)std::min<int64_t>(kRangeBlocks, grid_of(n, kThreads)), kThreads, 0, st>>>(d_raw, n, w.bad, w.kr);
-    k_life_keys<<<grid_of(n, 256), 256, 0, st>>>(d_raw, w.tid, n, T, tbits, second_odd, w.bad, w.kr, w.s.ka, w.s.va,
-                                                 gate, gate2, w.u);
+    k_life_keys<<<(unsigned)nt, kThreads, 0, st>>>(d_raw, d_raw_offsets, n, T, tbits, tp & 1, w.bad, w.kr, w.s.ka, w.s.va,
+                                                   w.tid, gate, gate2, w.s.hist, nt, w.part);
+    k_scan_top<<<1, kScanThreads, 0, st>>>(w.part, nt, w.total);
     // by (trace, address), or by address in an even number of passes; stream order kept
-    sort_bits(w.s, n, 0, 64, false, st, gate);
+    sort_bits(w.s, n, kAllBits, false, st, gate, true);
     // the separate layout only: then by trace (from the buffer the even passes end in)
     k_life_trace_keys<<<grid_of(n, 256), 256, 0, st>>>(d_raw, w.tid, n, T, w.bad, w.kr, w.s.va, w.s.ka);
-    sort_bits(w.s, n, 0, bits_for(T), false, st, gate2);
+    sort_bits(w.s, n, tp * kDigit, false, st, gate2);
     k_life_pair<<<grid_of(n, 256), 256, 0, st>>>(d_raw, w.tid, w.kr, w.s.ka, w.s.va, w.s.kb, w.s.vb, n, T, w.bad,
                                                  w.t64, d_unmatched_frees);
-    ScanWs sw{w.s.scan.part, w.s.scan.total};
-    scan_u32(w.u, w.u, n, sw, st);
-    k_life_emit<<<grid_of(n, 256), 256, 0, st>>>(d_raw, d_category, n, w.bad, w.u, w.t64, d_blocks);
-    k_life_offsets<<<grid_of(T + 1, 256), 256, 0, st>>>(d_raw_offsets, T, n, w.bad, w.u, w.s.scan.total,
-                                                        d_block_offsets);
-  } else {
-    k_zero_i64<<<grid_of(T + 1, 256), 256, 0, st>>>(d_block_offsets, T + 1);
+    k_life_emit<<<(unsigned)nt, kThreads, 0, st>>>(d_raw, d_category, d_raw_offsets, T, n, w.bad, w.part, w.t64, d_blocks,
+                                                   d_block_offsets);
   }
-  k_fill_offsets_zero<<<grid_of(T + 1, 256), 256, 0, st>>>(d_block_offsets, T, w.bad, d_status);
+  finish(T, empty, w, d_status, d_block_offsets, st);
   return hipGetLastError() == hipSuccess ? XMEM_OK : XMEM_EHIP;
 }
 
@@ -990,37 +1103,24 @@ int xmem_attribute(const xmem_block* d_blocks, const int64_t* d_block_offsets, i
   hipStream_t st = static_cast<hipStream_t>(hip_stream);
   PrepWs w;
   carve(d_workspace, T, n, &w);
-  int64_t* comp_end = reinterpret_cast<int64_t*>(w.s.ka);  // n words each: the sort buffers are free here
-  int64_t* role = reinterpret_cast<int64_t*>(w.s.kb);
+  int64_t* comp_end = reinterpret_cast<int64_t*>(w.s.ka);  // the sort buffers are free here: per window
   uint32_t* in_step = w.apos;                                  // per window
-  uint32_t* pflag = w.s.vb;                                    // per block, then its exclusive scan
-  uint32_t* tab = reinterpret_cast<uint32_t*>(w.t64);          // 2n slots: the parameter-size sets
-  k_zero_i32<<<1, 1, 0, st>>>(w.bad);
-  k_check_offsets<<<grid_of(T + 1, 256), 256, 0, st>>>(d_block_offsets, T, nb, w.bad);
-  k_check_offsets<<<grid_of(T + 1, 256), 256, 0, st>>>(d_window_offsets, T, nw, w.bad);
-  if (nb > 0 && T > 0) {
-    if (nw > 0)
-      k_att_comp_end<<<grid_of(nw, 256), 256, 0, st>>>(d_windows, d_window_offsets, T, nw, w.bad, comp_end, in_step);
-    k_trace_of<<<(unsigned)tiles_of(nb), kThreads, 0, st>>>(d_block_offsets, T, nb, w.bad, w.tid);
-    k_att_blocks<<<grid_of(nb, 256), 256, 0, st>>>(d_blocks, w.tid, nb, d_windows, d_window_offsets, comp_end, in_step,
-                                                   w.bad, d_block_window, w.u, role, pflag);
-    ScanWs sw{w.s.scan.part, w.s.scan.total};
-    // Section 3.3 item 5: parameter sizes per trace, then the products of the optimizer.step() phases
-    k_opt_flags_keep<<<grid_of(nb, 256), 256, 0, st>>>(pflag, nb, w.bad, w.s.va);
-    scan_u32(pflag, pflag, nb, sw, st);
-    k_opt_clear<<<grid_of(nb, 256), 256, 0, st>>>(pflag, w.s.va, nb, w.bad, tab);
-    k_opt_insert<<<grid_of(nb, 256), 256, 0, st>>>(d_blocks, w.tid, d_block_offsets, nb, w.s.va, pflag,
-                                                   w.s.scan.total, w.bad, tab);
-    k_opt_mark<<<grid_of(nb, 256), 256, 0, st>>>(d_blocks, w.tid, d_block_offsets, nb, pflag, w.s.scan.total, w.bad,
-                                                 tab, role);
-    scan_u32(w.u, w.s.va, nb, sw, st);
-    k_att_emit<<<grid_of(nb, 256), 256, 0, st>>>(d_blocks, nb, w.bad, w.u, w.s.va, role, d_kept);
-    k_life_offsets<<<grid_of(T + 1, 256), 256, 0, st>>>(d_block_offsets, T, nb, w.bad, w.s.va, w.s.scan.total,
-                                                        d_kept_offsets);
-  } else {
-    k_zero_i64<<<grid_of(T + 1, 256), 256, 0, st>>>(d_kept_offsets, T + 1);
+  int32_t* cats = reinterpret_cast<int32_t*>(w.s.va);          // per block
+  uint64_t* tab = reinterpret_cast<uint64_t*>(w.t64);          // per block: two slots of the parameter-size sets
+  const bool empty = nb == 0 || T == 0;
+  begin({d_block_offsets, nb}, {d_window_offsets, nw}, {nullptr, 0}, T, empty, nullptr, w, d_status, d_kept_offsets, st);
+  if (!empty) {
+    const int64_t nt = tiles_of(nb);
+    k_att_windows<<<(unsigned)tiles_of(n), kThreads, 0, st>>>(d_windows, d_window_offsets, T, nw, nb, w.bad, comp_end, in_step,
+                                                              tab);
+    k_att_blocks<<<(unsigned)nt, kThreads, 0, st>>>(d_blocks, d_block_offsets, T, nb, d_windows, d_window_offsets, comp_end,
+                                                    in_step, w.bad, d_block_window, w.tid, cats,
+                                                    reinterpret_cast<uint32_t*>(tab), w.part);
+    k_scan_top<<<1, kScanThreads, 0, st>>>(w.part, nt, w.total);
+    k_att_emit<<<(unsigned)nt, kThreads, 0, st>>>(d_blocks, d_block_offsets, T, nb, w.bad, w.tid, cats,
+                                                  reinterpret_cast<uint32_t*>(tab), w.part, d_kept, d_kept_offsets);
   }
-  k_fill_offsets_zero<<<grid_of(T + 1, 256), 256, 0, st>>>(d_kept_offsets, T, w.bad, d_status);
+  finish(T, empty, w, d_status, d_kept_offsets, st);
   return hipGetLastError() == hipSuccess ? XMEM_OK : XMEM_EHIP;
 }
 
@@ -1039,40 +1139,30 @@ int xmem_orchestrate(const xmem_block* d_blocks, const int64_t* d_block_offsets,
   hipStream_t st = static_cast<hipStream_t>(hip_stream);
   PrepWs w;
   carve(d_workspace, T, n, &w);
-  k_zero_i32<<<1, 1, 0, st>>>(w.bad);
-  k_check_offsets<<<grid_of(T + 1, 256), 256, 0, st>>>(d_block_offsets, T, nb, w.bad);
-  k_check_offsets<<<grid_of(T + 1, 256), 256, 0, st>>>(d_step_offsets, T, -1, w.bad);
-  k_check_offsets<<<grid_of(T + 1, 256), 256, 0, st>>>(d_zero_grad_offsets, T, -1, w.bad);
-  if (nb > 0 && T > 0) {
-    k_trace_of<<<(unsigned)tiles_of(nb), kThreads, 0, st>>>(d_block_offsets, T, nb, w.bad, w.tid);
-    k_orch_retime<<<grid_of(nb, 256), 256, 0, st>>>(d_blocks, w.tid, nb, d_step_ts, d_step_offsets, d_zero_grad_ts,
-                                                    d_zero_grad_offsets, w.bad, w.t64, w.s.ka, w.s.va);
+  const bool empty = nb == 0 || T == 0;
+  begin({d_block_offsets, nb}, {d_step_offsets, -1}, {d_zero_grad_offsets, -1}, T, empty, nullptr, w, d_status, d_event_offsets,
+        st);
+  if (!empty) {
+    const int64_t nt = tiles_of(nb);
     // gate[0]: the time (or joint) sort, gate[1]: the rank sort, gate[2]: the trace sort
     int32_t* gate = reinterpret_cast<int32_t*>(w.kr + 3);
     int tbits = 0;
     while (tbits < 63 && (T >> tbits) != 0) ++tbits;  // bits of the trace field (0..T)
-    k_range_init<<<1, 1, 0, st>>>(w.kr);
-    k_orch_range<<<(unsigned)std::min<int64_t>(kRangeBlocks, grid_of(nb, kThreads)), kThreads, 0, st>>>(d_blocks, w.t64, nb,
-                                                                                                  w.bad, w.kr);
-    k_orch_mode<<<1, 1, 0, st>>>(w.kr, tbits, (bits_for(T) / 8) & 1, gate);
-    sort_bits(w.s, n, 0, 8, false, st, gate + 1);  // rank at equal times (separate layout)
-    k_orch_time_keys<<<grid_of(n, 256), 256, 0, st>>>(d_blocks, w.tid, w.t64, n, T, w.bad, w.kr, w.s.vb, w.s.kb);
-    sort_bits(w.s, n, 0, 64, true, st, gate);  // time (its span only), or the joint key
+    const int tp = passes_for(T);
+    k_orch_retime<<<(unsigned)nt, kThreads, 0, st>>>(d_blocks, d_block_offsets, T, nb, d_step_ts, d_step_offsets,
+                                                     d_zero_grad_ts, d_zero_grad_offsets, w.bad, w.t64, w.kr, w.part);
+    k_scan_top<<<1, kScanThreads, 0, st>>>(w.part, nt, w.total);
+    k_orch_keys<<<(unsigned)nt, kThreads, 0, st>>>(d_blocks, d_block_offsets, T, nb, w.t64, tbits, tp & 1, w.bad, w.kr, gate,
+                                                   w.s.ka, w.s.va, w.s.kb, w.s.vb, w.tid, w.part, w.total, d_event_offsets);
+    sort_bits(w.s, n, kDigit, false, st, gate + 1);  // rank at equal times (separate layout)
+    k_orch_time_keys<<<grid_of(n, 256), 256, 0, st>>>(d_blocks, w.t64, n, w.bad, w.kr, w.s.vb, w.s.kb);
+    sort_bits(w.s, n, kAllBits, true, st, gate);  // time (its span only), or the joint key
     k_orch_trace_keys<<<grid_of(n, 256), 256, 0, st>>>(w.tid, w.t64, n, T, w.bad, w.kr, w.s.vb, w.s.kb);
-    sort_bits(w.s, n, 0, bits_for(T), true, st, gate + 2);  // trace; persistent blocks' frees last
-    k_orch_counts<<<grid_of(nb, 256), 256, 0, st>>>(w.t64, nb, w.bad, w.u);
-    ScanWs sw{w.s.scan.part, w.s.scan.total};
-    scan_u32(w.u, w.u, nb, sw, st);
-    k_orch_offsets<<<grid_of(T + 1, 256), 256, 0, st>>>(d_block_offsets, T, nb, w.bad, w.u, w.s.scan.total,
-                                                        d_event_offsets);
-    k_orch_apos<<<grid_of(n, 256), 256, 0, st>>>(w.tid, d_event_offsets, w.s.scan.total, w.bad, w.kr, w.s.ka, w.s.va,
-                                                 w.s.kb, w.s.vb, w.apos);
-    k_orch_words<<<grid_of(n, 256), 256, 0, st>>>(d_blocks, w.s.scan.total, w.bad, w.kr, w.s.va, w.s.vb, w.apos,
-                                                  d_events);
-  } else {
-    k_zero_i64<<<grid_of(T + 1, 256), 256, 0, st>>>(d_event_offsets, T + 1);
+    sort_bits(w.s, n, tp * kDigit, true, st, gate + 2);  // trace; persistent blocks' frees last
+    k_orch_apos<<<(unsigned)tiles_of(n), kThreads, 0, st>>>(d_event_offsets, T, w.total, w.bad, w.kr, w.s.va, w.s.vb, w.apos);
+    k_orch_words<<<grid_of(n, 256), 256, 0, st>>>(d_blocks, w.total, w.bad, w.kr, w.s.va, w.s.vb, w.apos, d_events);
   }
-  k_fill_offsets_zero<<<grid_of(T + 1, 256), 256, 0, st>>>(d_event_offsets, T, w.bad, d_status);
+  finish(T, empty, w, d_status, d_event_offsets, st);
   return hipGetLastError() == hipSuccess ? XMEM_OK : XMEM_EHIP;
 }
 
