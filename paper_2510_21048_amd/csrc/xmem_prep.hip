@@ -1,10 +1,10 @@
 // xmem_prep.hip -- trace preparation upstream of the Memory Simulator, on MI355X (gfx950).
 //
 //   xmem_lifecycles   Section 3.2: pair raw allocator events by address into
-//                     memory blocks.  A stable sort by (trace, address) puts
-//                     every address's events next to each other in stream
-//                     order; an allocation is closed by the event right after
-//                     it when that is a free at the same address.
+//                     memory blocks.  A stable sort by a hash of (trace, address)
+//                     puts every address's events next to each other in stream
+//                     order; an allocation is closed by the next event of its
+//                     address when that is a free.
 //   xmem_attribute    Section 3.2: link each block to the operator window it
 //                     belongs to.  Per block: a binary search for the last
 //                     window of its trace that starts no later than the
@@ -20,18 +20,21 @@
 //                     time, rank) gives the Simulator's event order, and a
 //                     scatter writes the event words.
 //
-// Both are HBM-bound.  The sort is an LSD radix sort of (64-bit key, 32-bit
-// value) pairs, 8 bits a pass, in three kernels per pass; an address or time key
-// is first rebased to its batch's minimum (and shifted past the trailing zero
-// bits its values share), so that it takes only the passes its span needs:
+// Long batches are HBM-bound, short ones bound by launches.  The sort is an LSD radix sort of
+// (64-bit key, 32-bit value) pairs, 9 bits a pass (35 bits of (trace, time) in four passes, where
+// 8-bit digits took five), in three kernels per pass:
 //   k_rs_hist     digit histogram of each 4096-element tile;
-//   k_scan_*      exclusive scan of the digit-major histogram (tile offsets);
-//   k_rs_scatter  each wavefront ranks its 64-element steps with eight
+//   k_rs_rows     one workgroup per digit: exclusive scan of its tiles' counts;
+//   k_rs_scatter  each wavefront ranks its 64-element steps with nine
 //                 ballots (lanes with the same digit; stable by lane order),
 //                 the tile is reordered by digit in LDS, and each digit's run
 //                 is written to consecutive addresses.
-// Keys are rebuilt between key groups from the values (record indices), so
-// a composite key (trace, time, rank) costs one pass per 8 bits it uses.
+// The pairing needs equal keys to meet, not an order, so it sorts by 18, 27 or 36 bits of a hash:
+// the passes are known on the host, whatever the addresses span.  The orchestration sorts by time,
+// rebased to its batch's minimum, over the passes its span needs.  Up to 8,192 records are sorted
+// by one workgroup in one launch, and no flags are scanned: per tile counts, added up by the
+// kernels that use them.  One profile of 4,001 events takes 15 launches instead of 148: 535 -> 211 us
+// for the three steps (with their host calls); 128 profiles of 65,536 events 2,045 -> 1,656 us.
 #include <hip/hip_runtime.h>
 #include <algorithm>
 #include <stddef.h>
@@ -50,6 +53,10 @@ constexpr int kBins = 1 << kDigit;
 constexpr int kSteps = kTileN / 64;       // 64-record steps of a tile
 constexpr int kWaves = kThreads / 64;
 constexpr int kScanThreads = 1024;
+// the kernels that work on records (not the sort's passes): a tile per workgroup of 1024, whose
+// chains of dependent loads (window climbs, marker searches) need the wavefronts
+constexpr int kRecThreads = 1024;
+constexpr int kRecItems = kTileN / kRecThreads;
 constexpr int64_t kPersist = INT64_MAX;
 constexpr uint64_t kFree = 1ull << 63;
 
@@ -93,8 +100,8 @@ __device__ __forceinline__ uint32_t block_excl_scan(uint32_t v, uint32_t* s, uin
   *total = tot;
   return before + x - v;
 }
-// exclusive scan of part[0..np) in place, one workgroup; total to *total
-__global__ __launch_bounds__(kScanThreads) void k_scan_top(uint32_t* part, int64_t np, uint32_t* total) {
+// exclusive scan of part[0..np) in place, one workgroup
+__global__ __launch_bounds__(kScanThreads) void k_scan_top(uint32_t* part, int64_t np) {
   __shared__ uint32_t s[kScanThreads / 64];
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   const int64_t per = (np + kScanThreads - 1) / kScanThreads;
@@ -107,7 +114,6 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_top(uint32_t* part, int64
   uint32_t run = x - acc;
 #pragma unroll
   for (int k = 0; k < kScanThreads / 64; ++k) run += k < wv ? s[k] : 0u;
-  if (threadIdx.x == kScanThreads - 1 && total) *total = run + acc;
   for (int64_t i = lo; i < lo + per && i < np; ++i) {
     const uint32_t v = part[i];
     part[i] = run;
@@ -115,7 +121,7 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_top(uint32_t* part, int64
   }
 }
 
-// Flags of a tile's records (record kThreads i + thread of the tile: every load coalesced), as one
+// Flags of a tile's records (record kRecThreads i + thread of the tile: every load coalesced), as one
 // ballot per 64-record step, and the flagged records before each step.
 struct TileFlags {
   uint64_t m[kSteps];
@@ -123,7 +129,7 @@ struct TileFlags {
 };
 __device__ __forceinline__ void flags_put(TileFlags& f, int i, bool flag) {
   const uint64_t m = ballot(flag);
-  if ((threadIdx.x & 63) == 0) f.m[i * kWaves + (threadIdx.x >> 6)] = m;
+  if ((threadIdx.x & 63) == 0) f.m[i * (kRecThreads / 64) + (threadIdx.x >> 6)] = m;
 }
 __device__ __forceinline__ void flags_scan(TileFlags& f) {
   static_assert(kSteps == 64, "one wavefront scans the steps");
@@ -140,6 +146,24 @@ __device__ __forceinline__ void flags_scan(TileFlags& f) {
 __device__ __forceinline__ uint32_t flags_before(const TileFlags& f, int r) {
   if (r >= kTileN) return f.before[kSteps];
   return f.before[r >> 6] + (uint32_t)__builtin_popcountll(f.m[r >> 6] & ((1ull << (r & 63)) - 1));
+}
+
+// What the tiles before this one hold: part scanned by k_scan_top, or, up to kPartTiles tiles,
+// added up here (one load a thread instead of a launch).  Every thread of the kRecThreads calls it.
+constexpr int64_t kPartTiles = kRecThreads;
+__device__ __forceinline__ uint32_t tile_before(const uint32_t* part, int64_t ntiles) {
+  if (ntiles > kPartTiles) return part[blockIdx.x];
+  __shared__ uint32_t s[kRecThreads / 64];
+  const uint32_t x = wave_scan_u32((int)threadIdx.x < (int)blockIdx.x ? part[threadIdx.x] : 0u);
+  if ((threadIdx.x & 63) == 63) s[threadIdx.x >> 6] = x;
+  __syncthreads();
+  uint32_t t = 0;
+#pragma unroll
+  for (int k = 0; k < kRecThreads / 64; ++k) t += s[k];
+  return t;
+}
+void scan_parts(uint32_t* part, int64_t ntiles, hipStream_t st) {
+  if (ntiles > kPartTiles) k_scan_top<<<1, kScanThreads, 0, st>>>(part, ntiles);
 }
 
 // ---------------------------------------------------------------- traces of records
@@ -195,7 +219,7 @@ __device__ __forceinline__ void tile_offsets(const int64_t* off, int64_t T, int6
     if (threadIdx.x == 0) { s_r[0] = a; s_r[1] = b; }
   }
   __syncthreads();
-  for (int64_t t = s_r[0] + threadIdx.x; t < s_r[1]; t += kThreads) {
+  for (int64_t t = s_r[0] + threadIdx.x; t < s_r[1]; t += kRecThreads) {
     const int r = (int)(off[t] - base);
     out[t] = (int64_t)at + (int64_t)per * r + flags_before(f, r);
   }
@@ -215,20 +239,25 @@ __device__ __forceinline__ void hist_add(uint32_t* h, bool ok, uint32_t d) {
   }
 }
 __device__ __forceinline__ void hist_clear(uint32_t* h) {
-#pragma unroll
-  for (int i = 0; i < kBins / kThreads; ++i) h[i * kThreads + threadIdx.x] = 0;
+  for (int d = threadIdx.x; d < kBins; d += blockDim.x) h[d] = 0;
   __syncthreads();
 }
 // digit-major: hist[d * ntiles + tile]
 __device__ __forceinline__ void hist_store(const uint32_t* h, uint32_t* hist, int64_t ntiles) {
   __syncthreads();
-#pragma unroll
-  for (int i = 0; i < kBins / kThreads; ++i) {
-    const int d = i * kThreads + threadIdx.x;
-    hist[(int64_t)d * ntiles + blockIdx.x] = h[d];
-  }
+  for (int d = threadIdx.x; d < kBins; d += blockDim.x) hist[(int64_t)d * ntiles + blockIdx.x] = h[d];
+}
+// The digit of a key: its own bits, or (HASHED) those of a hash of it without its lowest bit, where
+// the order of different keys does not matter but only that equal ones meet (kHashBits bits spread
+// evenly, so the passes are known beforehand, whatever the keys span).
+constexpr int kHashBits = 4 * kDigit;
+template <bool HASHED>
+__device__ __forceinline__ uint32_t digit_of(uint64_t key, int shift) {
+  const uint64_t x = HASHED ? ((key | 1) * 0x9E3779B97F4A7C15ull) >> (64 - kHashBits) : key;
+  return (uint32_t)(x >> shift) & (kBins - 1);
 }
 // digit histogram of each tile
+template <bool HASHED>
 __global__ __launch_bounds__(kThreads) void k_rs_hist(const uint64_t* keys, int64_t n, int shift, uint32_t* hist,
                                                       int64_t ntiles, const int32_t* gate) {
   if (gated(gate, shift)) return;
@@ -239,7 +268,7 @@ __global__ __launch_bounds__(kThreads) void k_rs_hist(const uint64_t* keys, int6
   for (int i = 0; i < kItems; ++i) {
     const int64_t k = base + (int64_t)i * kThreads + threadIdx.x;
     const bool ok = k < n;
-    hist_add(h, ok, ok ? (uint32_t)(keys[k] >> shift) & (kBins - 1) : 0u);
+    hist_add(h, ok, ok ? digit_of<HASHED>(keys[k], shift) : 0u);
   }
   hist_store(h, hist, ntiles);
 }
@@ -272,6 +301,7 @@ __global__ __launch_bounds__(kThreads) void k_rs_rows(uint32_t* hist, int64_t nt
 
 // Stable scatter of one tile by one digit.  off[d * ntiles + tile]: this tile's elements of digit d
 // go after that many of the digit's; tot[d]: the digit's elements.
+template <bool HASHED>
 __global__ __launch_bounds__(kThreads, 4) void k_rs_scatter(const uint64_t* kin, const uint32_t* vin, uint64_t* kout,
                                                          uint32_t* vout, int64_t n, int shift, const uint32_t* off,
                                                          const uint32_t* tot, int64_t ntiles, const int32_t* gate) {
@@ -296,7 +326,7 @@ __global__ __launch_bounds__(kThreads, 4) void k_rs_scatter(const uint64_t* kin,
     const bool ok = k < n;
     key[i] = ok ? kin[k] : 0;
     val[i] = ok ? vin[k] : 0;
-    const uint32_t d = (uint32_t)(key[i] >> shift) & (kBins - 1);
+    const uint32_t d = digit_of<HASHED>(key[i], shift);
     uint64_t peers = ballot(ok);
 #pragma unroll
     for (int b = 0; b < kDigit; ++b) {
@@ -356,7 +386,7 @@ __global__ __launch_bounds__(kThreads, 4) void k_rs_scatter(const uint64_t* kin,
     out_at[j] = 0xffffffffu;
     if (i < cnt) {
       const uint64_t k = sk[i];
-      out_at[j] = gbase[(uint32_t)(k >> shift) & (kBins - 1)] + (uint32_t)i;
+      out_at[j] = gbase[digit_of<HASHED>(k, shift)] + (uint32_t)i;
       kout[out_at[j]] = k;
     }
   }
@@ -378,20 +408,21 @@ struct SortWs {
   uint32_t* tot;  // kBins
 };
 
-// Sorts (ka, va)[0..n) by key bits [0, hi), stably; returns true when the
+// Sorts (ka, va)[0..n) by key bits [lo, hi), stably; returns true when the
 // result is in (kb, vb), false when in (ka, va).  With a gate, the passes at and
 // above bit *gate (found on the device) exit at once.  hist_done: the first
 // pass's histogram is in place.
-bool sort_bits(SortWs& w, int64_t n, int hi, bool in_b, hipStream_t st, const int32_t* gate, bool hist_done = false) {
+template <bool HASHED>
+bool sort_bits(SortWs& w, int64_t n, int lo, int hi, bool in_b, hipStream_t st, const int32_t* gate, bool hist_done = false) {
   const int64_t nt = tiles_of(n);
-  for (int sh = 0; sh < hi; sh += kDigit) {
+  for (int sh = lo; sh < hi; sh += kDigit) {
     uint64_t* kin = in_b ? w.kb : w.ka;
     uint32_t* vin = in_b ? w.vb : w.va;
     uint64_t* kout = in_b ? w.ka : w.kb;
     uint32_t* vout = in_b ? w.va : w.vb;
-    if (sh > 0 || !hist_done) k_rs_hist<<<(unsigned)nt, kThreads, 0, st>>>(kin, n, sh, w.hist, nt, gate);
+    if (sh > lo || !hist_done) k_rs_hist<HASHED><<<(unsigned)nt, kThreads, 0, st>>>(kin, n, sh, w.hist, nt, gate);
     k_rs_rows<<<kBins, kThreads, 0, st>>>(w.hist, nt, w.tot, gate, sh);
-    k_rs_scatter<<<(unsigned)nt, kThreads, 0, st>>>(kin, vin, kout, vout, n, sh, w.hist, w.tot, nt, gate);
+    k_rs_scatter<HASHED><<<(unsigned)nt, kThreads, 0, st>>>(kin, vin, kout, vout, n, sh, w.hist, w.tot, nt, gate);
     in_b = !in_b;
   }
   return in_b;
@@ -402,6 +433,81 @@ int passes_for(int64_t maxval) {  // passes that values 0..maxval take
   int b = 0;
   while (b < 63 && (maxval >> b) != 0) ++b;
   return (b + kDigit - 1) / kDigit;
+}
+
+// The same sort of at most kOneRecords records by one workgroup, pass after pass in one launch (a
+// pass of the kernels above costs its three launches, 3 to 4 us each, however few the records).
+// Sorts from (ka, va) or (kb, vb) by bits [lo, hi) and returns where the result lies.  Every
+// thread calls it.
+constexpr int kOneThreads = 1024, kOneWaves = kOneThreads / 64, kOneItems = 8;
+constexpr int64_t kOneRecords = kOneThreads * kOneItems;
+struct OneLds {
+  uint32_t cnt[kOneWaves][kBins];  // a wavefront's digit counts, then where its run of each digit starts
+  uint32_t w[kOneWaves];
+};
+template <bool HASHED>
+__device__ __forceinline__ bool sort_one(OneLds& s, uint64_t* ka, uint32_t* va, uint64_t* kb, uint32_t* vb, int n, int lo,
+                                         int hi, bool in_b) {
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  const uint64_t below = (1ull << lane) - 1;
+  for (int sh = lo; sh < hi; sh += kDigit) {
+    const uint64_t* kin = in_b ? kb : ka;
+    const uint32_t* vin = in_b ? vb : va;
+    uint64_t* kout = in_b ? ka : kb;
+    uint32_t* vout = in_b ? va : vb;
+    for (int d = lane; d < kBins; d += 64) s.cnt[wv][d] = 0;
+    uint64_t key[kOneItems];
+    uint32_t val[kOneItems], rd[kOneItems];  // rank in the wavefront's digit run | digit << 16
+#pragma unroll
+    for (int i = 0; i < kOneItems; ++i) {  // each wavefront its 512 consecutive records
+      const int k = wv * (64 * kOneItems) + i * 64 + lane;
+      const bool ok = k < n;
+      key[i] = ok ? kin[k] : 0;
+      val[i] = ok ? vin[k] : 0;
+      const uint32_t d = digit_of<HASHED>(key[i], sh);
+      uint64_t peers = ballot(ok);
+#pragma unroll
+      for (int b = 0; b < kDigit; ++b) {
+        const uint64_t bb = ballot((d >> b) & 1u);
+        peers &= ((d >> b) & 1u) ? bb : ~bb;
+      }
+      const uint32_t before = (uint32_t)__builtin_popcountll(peers & below), c = s.cnt[wv][d];
+      rd[i] = (c + before) | (d << 16);
+      __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+      if (ok && before == 0) s.cnt[wv][d] = c + (uint32_t)__builtin_popcountll(peers);
+      __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+    }
+    __syncthreads();
+    {  // thread tid owns digit tid: a scan over the digits, then over the wavefronts
+      uint32_t c = 0;
+      if (tid < kBins)
+        for (int q = 0; q < kOneWaves; ++q) c += s.cnt[q][tid];
+      const uint32_t x = wave_scan_u32(c);
+      if (lane == 63) s.w[wv] = x;
+      __syncthreads();
+      if (tid < kBins) {
+        uint32_t run = x - c;
+        for (int k = 0; k < wv; ++k) run += s.w[k];
+        for (int q = 0; q < kOneWaves; ++q) {
+          const uint32_t m = s.cnt[q][tid];
+          s.cnt[q][tid] = run;
+          run += m;
+        }
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < kOneItems; ++i) {
+      if (wv * (64 * kOneItems) + i * 64 + lane < n) {
+        const uint32_t at = s.cnt[wv][rd[i] >> 16] + (rd[i] & 0xffffu);
+        kout[at] = key[i];
+        vout[at] = val[i];
+      }
+    }
+    __syncthreads();
+    in_b = !in_b;
+  }
+  return in_b;
 }
 
 // ---------------------------------------------------------------- workspace
@@ -517,7 +623,7 @@ constexpr int kRangeBlocks = 1024;  // workgroups of a range kernel (grid-stride
 constexpr int kRangeUnroll = 8;     // records a range kernel's thread loads at once
 // the workgroup's parts combined (wavefront butterflies, then LDS), then one atomic per word
 __device__ __forceinline__ void range_commit(uint64_t* kr, RangePart p) {
-  __shared__ uint64_t s[3][kThreads / 64];
+  __shared__ uint64_t s[3][kRecThreads / 64];
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) {
     const uint64_t a = __shfl_xor(p.mn, o, 64), b = __shfl_xor(p.mx, o, 64), c = __shfl_xor(p.ox, o, 64);
@@ -529,7 +635,7 @@ __device__ __forceinline__ void range_commit(uint64_t* kr, RangePart p) {
   if ((threadIdx.x & 63) == 0) { s[0][wv] = p.mn; s[1][wv] = p.mx; s[2][wv] = p.ox; }
   __syncthreads();
   if (threadIdx.x == 0) {
-    for (int k = 1; k < kThreads / 64; ++k) {
+    for (int k = 1; k < (int)blockDim.x / 64; ++k) {
       p.mn = s[0][k] < p.mn ? s[0][k] : p.mn;
       p.mx = s[1][k] > p.mx ? s[1][k] : p.mx;
       p.ox |= s[2][k];
@@ -556,41 +662,24 @@ __device__ __forceinline__ int32_t range_gate(const uint64_t* kr, int shift) {
   return kDigit * (passes + (passes & 1));
 }
 
-// addresses of the allocation and free records (0-byte events take no part)
-__global__ __launch_bounds__(kThreads) void k_life_range(const xmem_raw_event* raw, int64_t n, const int32_t* bad,
-                                                         uint64_t* kr) {
-  if (*bad) return;
-  RangePart p;
-  const uint64_t ref = raw[0].addr;
-  // kRangeUnroll records per step, their loads all issued before any is used
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  for (int64_t k0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; k0 < n; k0 += kRangeUnroll * stride) {
-    uint64_t a[kRangeUnroll];
-    int64_t by[kRangeUnroll];
-#pragma unroll
-    for (int u = 0; u < kRangeUnroll; ++u) {
-      const int64_t k = k0 + u * stride;
-      a[u] = k < n ? raw[k].addr : 0;
-      by[u] = k < n ? raw[k].bytes : 0;
-    }
-#pragma unroll
-    for (int u = 0; u < kRangeUnroll; ++u) p.add(by[u] != 0, a[u], ref);
-  }
-  range_commit(kr, p);
+constexpr uint64_t kJoint = 1, kJointBuf = 2;  // orchestration: the sort's layout (kr[5], k_orch_keys)
+// A record's key: equal exactly for the allocations and frees of one (trace, address), but for the
+// lowest bit, which marks a free.  (trace, address) itself when the address is below 2^47 and the
+// trace below 2^15; else (kWide) 61 bits mixed from both, whose equality the pairing verifies on
+// the records.  A 0-byte record takes no part: a key of its own (kNone).
+constexpr uint64_t kNone = 3ull << 62, kWide = 1ull << 63;
+__device__ __forceinline__ uint64_t life_key(uint64_t t, uint64_t addr, int64_t bytes, int64_t k) {
+  const uint64_t free = bytes < 0 ? 1u : 0u;
+  if (bytes == 0) return kNone | ((uint64_t)k << 1);
+  if (addr < (1ull << 47) && t < (1ull << 15)) return (t << 48) | (addr << 1) | free;
+  uint64_t x = (addr ^ (t * 0xD6E8FEB86659FD93ull)) * 0xD6E8FEB86659FD93ull;
+  x = (x ^ (x >> 32)) * 0xD6E8FEB86659FD93ull;
+  return kWide | (((x ^ (x >> 32)) & ((1ull << 61) - 1)) << 1) | free;
 }
-// The lifecycle sort's layout, chosen on the device from the address range (kr[5]: bit 0 set
-// for the joint key, bit 1 the buffer that ends up holding the sorted pairs, bits 8.. the
-// address bits b).  Joint key, when the trace and the address fit in 64 bits together and
-// record indices in 31: (trace << b) | address, rebased and shifted, with 0-byte records last
-// (T << b); one sort of b + trace bits, and the value carries the record index with bit 31 set
-// for a free.  Otherwise the address alone (0 for 0-byte records), sorted in an even number of
-// passes, then again by trace (k_life_trace_keys); the value is the record index.
-constexpr uint64_t kJoint = 1, kJointBuf = 2;
-// Per tile also its allocations (part), and with them the first pass's digit histogram.
-__global__ __launch_bounds__(kThreads) void k_life_keys(const xmem_raw_event* raw, const int64_t* off, int64_t n, int64_t T,
-                                                        int tbits, bool second_odd, const int32_t* bad, uint64_t* kr,
-                                                        uint64_t* key, uint32_t* val, uint32_t* tid, int32_t* gate,
-                                                        int32_t* gate2, uint32_t* hist, int64_t ntiles, uint32_t* part) {
+// Keys and record indices, per tile its allocations (part), and the first pass's digit histogram.
+__global__ __launch_bounds__(kRecThreads) void k_life_keys(const xmem_raw_event* raw, const int64_t* off, int64_t n, int64_t T,
+                                                           const int32_t* bad, uint64_t* key, uint32_t* val, int shift,
+                                                           uint32_t* hist, int64_t ntiles, uint32_t* part) {
   if (*bad) return;
   __shared__ uint32_t h[kBins];
   __shared__ uint32_t s_cnt;
@@ -598,117 +687,116 @@ __global__ __launch_bounds__(kThreads) void k_life_keys(const xmem_raw_event* ra
   hist_clear(h);
   const int64_t base = (int64_t)blockIdx.x * kTileN;
   TraceStep tr(off, T, tile_trace(off, T, base));
-  const int sh = range_shift(kr, true), b = range_bits(kr, sh);
-  const uint64_t lowest = kr[0];
-  const bool joint = n <= INT32_MAX && b + tbits <= 64;
-  if (blockIdx.x == 0 && threadIdx.x == 0) {
-    const int jp = (b + tbits + kDigit - 1) / kDigit;  // passes of the joint sort
-    *gate = joint ? kDigit * jp : range_gate(kr, sh);
-    *gate2 = joint ? 0 : 64;
-    kr[5] = (joint ? kJoint : 0) | ((joint ? (jp & 1) : second_odd) ? kJointBuf : 0) | ((uint64_t)b << 8);
-  }
   uint32_t allocs = 0;
-#pragma unroll 4
-  for (int i = 0; i < kItems; ++i) {
-    const int64_t k = base + (int64_t)i * kThreads + threadIdx.x;
+#pragma unroll
+  for (int i = 0; i < kRecItems; ++i) {
+    const int64_t k = base + (int64_t)i * kRecThreads + threadIdx.x;
     const bool ok = k < n;
     uint64_t x = 0;
     if (ok) {
       tr.to(off, T, k);
-      const uint64_t addr = raw[k].addr;
       const int64_t bytes = raw[k].bytes;
-      const uint64_t a = (addr - lowest) >> sh;
-      x = joint ? (bytes != 0 ? ((uint64_t)tr.t << b) | a : (uint64_t)T << b) : bytes != 0 ? a : 0;
+      x = life_key((uint64_t)tr.t, raw[k].addr, bytes, k);
       key[k] = x;
-      val[k] = (uint32_t)k | (joint && bytes < 0 ? 0x80000000u : 0u);
-      if (!joint) tid[k] = (uint32_t)tr.t;
+      val[k] = (uint32_t)k;
       allocs += bytes > 0 ? 1u : 0u;
     }
-    hist_add(h, ok, (uint32_t)x & (kBins - 1));
+    hist_add(h, ok, digit_of<true>(x, shift));
   }
   atomicAdd(&s_cnt, allocs);
   hist_store(h, hist, ntiles);
   if (threadIdx.x == 0) part[blockIdx.x] = s_cnt;
 }
-// keys after the address sort: trace of the record (T for 0-byte events, which sort last)
-__global__ void k_life_trace_keys(const xmem_raw_event* raw, const uint32_t* tid, int64_t n, int64_t T,
-                                  const int32_t* bad, const uint64_t* kr, const uint32_t* val, uint64_t* key) {
-  const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (p >= n || *bad || (kr[5] & kJoint)) return;
-  const uint32_t k = val[p];
-  key[p] = raw[k].bytes == 0 ? (uint64_t)T : (uint64_t)tid[k];
+__global__ __launch_bounds__(kOneThreads) void k_life_sort_one(int64_t n, int shift0, const int32_t* bad, uint64_t* ka,
+                                                               uint32_t* va, uint64_t* kb, uint32_t* vb) {
+  if (*bad) return;
+  __shared__ OneLds s;
+  sort_one<true>(s, ka, va, kb, vb, (int)n, shift0, kHashBits, false);
 }
-// in (trace, address, stream) order: an allocation is closed by the next
-// record when it is a free of the same trace and address.  With the joint key both
-// come from the sorted keys and values, and only a closing free's time is read.
-__global__ void k_life_pair(const xmem_raw_event* raw, const uint32_t* tid, const uint64_t* kr, const uint64_t* ka,
-                            const uint32_t* va, const uint64_t* kb, const uint32_t* vb, int64_t n, int64_t T,
-                            const int32_t* bad, int64_t* tfree, int64_t* unmatched) {
+// whether records i and j (keys equal but for the lowest bit) are of one trace and address
+__device__ __forceinline__ bool life_same(const xmem_raw_event* raw, const int64_t* off, int64_t T, uint64_t key, uint32_t i,
+                                          uint32_t j) {
+  if (!(key & kWide)) return true;
+  if (raw[i].addr != raw[j].addr) return false;
+  // of one trace: no trace starts in (min, max]
+  const int64_t a = i < j ? i : j, b = i < j ? j : i;
+  int64_t lo = 0, hi = T;  // the first trace that starts past a
+  while (lo < hi) {
+    const int64_t mid = (lo + hi) >> 1;
+    if (off[mid] > a) hi = mid; else lo = mid + 1;
+  }
+  return lo >= T || off[lo] > b;
+}
+// Sorted by the key's hash, stably: the records of one key meet in stream order, among those of
+// the few other keys with the same hash (bits below shift0 unsorted).  An allocation is closed by
+// the next record of its key when that is a free.
+__global__ void k_life_pair(const xmem_raw_event* raw, const int64_t* off, int64_t T, const uint64_t* key,
+                            const uint32_t* val, int64_t n, int shift0, const int32_t* bad, int64_t* tfree,
+                            int64_t* unmatched) {
   const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (p >= n || *bad) return;
-  const uint64_t meta = kr[5];
-  const uint32_t* val = (meta & kJointBuf) ? vb : va;
-  if (meta & kJoint) {
-    const uint64_t* key = (meta & kJointBuf) ? kb : ka;
-    const int b = (int)(meta >> 8);
-    const uint64_t x = key[p];
-    const uint64_t t = x >> b;
-    if (t >= (uint64_t)T) return;  // 0-byte records
-    const uint32_t v = val[p];
-    const uint32_t k = v & 0x7fffffffu;
-    if (!(v >> 31)) {
-      int64_t f = kPersist;
-      if (p + 1 < n && key[p + 1] == x) {
-        const uint32_t vn = val[p + 1];
-        if (vn >> 31) f = raw[vn & 0x7fffffffu].ts;
-      }
-      tfree[k] = f;
-    } else if (unmatched) {
-      const bool closes = p > 0 && key[p - 1] == x && !(val[p - 1] >> 31);
-      if (!closes) atomicAdd((unsigned long long*)&unmatched[t], 1ull);
-    }
-    return;
-  }
+  const uint64_t x = key[p];
+  if ((x & kNone) == kNone) return;
+  const uint64_t run = ((x | 1) * 0x9E3779B97F4A7C15ull) >> (64 - kHashBits + shift0);
   const uint32_t k = val[p];
-  const xmem_raw_event r = raw[k];
-  if (r.bytes == 0) return;
-  const bool has_next = p + 1 < n, has_prev = p > 0;
-  const uint32_t kn = has_next ? val[p + 1] : 0, kp = has_prev ? val[p - 1] : 0;
-  if (r.bytes > 0) {
+  if (!(x & 1)) {
     int64_t f = kPersist;
-    if (has_next) {
-      const xmem_raw_event q = raw[kn];
-      if (q.bytes < 0 && q.addr == r.addr && tid[kn] == tid[k]) f = q.ts;
+    for (int64_t q = p + 1; q < n; ++q) {
+      const uint64_t y = key[q];
+      if ((y | 1) == (x | 1)) {
+        const uint32_t kn = val[q];
+        if (life_same(raw, off, T, x, k, kn)) {
+          if (y & 1) f = raw[kn].ts;
+          break;
+        }
+      } else if (((y | 1) * 0x9E3779B97F4A7C15ull) >> (64 - kHashBits + shift0) != run) {
+        break;
+      }
     }
     tfree[k] = f;
   } else if (unmatched) {
     bool closes = false;
-    if (has_prev) {
-      const xmem_raw_event q = raw[kp];
-      closes = q.bytes > 0 && q.addr == r.addr && tid[kp] == tid[k];
+    for (int64_t q = p - 1; q >= 0; --q) {
+      const uint64_t y = key[q];
+      if ((y | 1) == (x | 1)) {
+        const uint32_t kp = val[q];
+        if (life_same(raw, off, T, x, k, kp)) {
+          closes = !(y & 1);
+          break;
+        }
+      } else if (((y | 1) * 0x9E3779B97F4A7C15ull) >> (64 - kHashBits + shift0) != run) {
+        break;
+      }
     }
-    if (!closes) atomicAdd((unsigned long long*)&unmatched[tid[k]], 1ull);
+    if (!closes) {
+      int64_t lo = 0, hi = T - 1;  // the last trace that starts at or before the record
+      while (lo < hi) {
+        const int64_t mid = (lo + hi + 1) >> 1;
+        if (off[mid] <= (int64_t)k) lo = mid; else hi = mid - 1;
+      }
+      atomicAdd((unsigned long long*)&unmatched[lo], 1ull);
+    }
   }
 }
 // the blocks in allocation order (part: allocations before each tile), and the traces' offsets
-__global__ __launch_bounds__(kThreads) void k_life_emit(const xmem_raw_event* raw, const int32_t* cat, const int64_t* off,
+__global__ __launch_bounds__(kRecThreads) void k_life_emit(const xmem_raw_event* raw, const int32_t* cat, const int64_t* off,
                                                         int64_t T, int64_t n, const int32_t* bad, const uint32_t* part,
                                                         const int64_t* tfree, xmem_block* blocks, int64_t* boff) {
   if (*bad) return;
   __shared__ TileFlags f;
   const int64_t base = (int64_t)blockIdx.x * kTileN;
-  int64_t bytes[kItems];
+  int64_t bytes[kRecItems];
 #pragma unroll
-  for (int i = 0; i < kItems; ++i) {
-    const int64_t k = base + (int64_t)i * kThreads + threadIdx.x;
+  for (int i = 0; i < kRecItems; ++i) {
+    const int64_t k = base + (int64_t)i * kRecThreads + threadIdx.x;
     bytes[i] = k < n ? raw[k].bytes : 0;
     flags_put(f, i, bytes[i] > 0);
   }
   flags_scan(f);
-  const uint32_t at = part[blockIdx.x];
+  const uint32_t at = tile_before(part, gridDim.x);
 #pragma unroll 4
-  for (int i = 0; i < kItems; ++i) {
-    const int r = i * kThreads + threadIdx.x;
+  for (int i = 0; i < kRecItems; ++i) {
+    const int r = i * kRecThreads + threadIdx.x;
     const int64_t k = base + r;
     if (bytes[i] > 0) {
       xmem_block b;
@@ -732,21 +820,21 @@ __device__ __forceinline__ int64_t win_parent(const xmem_window* w, int64_t i) {
 // per window: the end of its nearest enclosing component (kPersist: none), and whether it lies in
 // an optimizer.step() phase (itself or an enclosing window is a component of category optimizer);
 // and two empty slots of the parameter-size sets per block
-__global__ __launch_bounds__(kThreads) void k_att_windows(const xmem_window* win, const int64_t* woff, int64_t T, int64_t nw,
+__global__ __launch_bounds__(kRecThreads) void k_att_windows(const xmem_window* win, const int64_t* woff, int64_t T, int64_t nw,
                                                           int64_t nb, const int32_t* bad, int64_t* comp_end,
                                                           uint32_t* in_step, uint64_t* tab) {
   if (*bad) return;
   const int64_t base = (int64_t)blockIdx.x * kTileN;
 #pragma unroll
-  for (int i = 0; i < kItems; ++i) {
-    const int64_t k = base + (int64_t)i * kThreads + threadIdx.x;
+  for (int i = 0; i < kRecItems; ++i) {
+    const int64_t k = base + (int64_t)i * kRecThreads + threadIdx.x;
     if (k < nb) tab[k] = 0;
   }
   if (base >= nw) return;
   TraceStep tr(woff, T, tile_trace(woff, T, base));
 #pragma unroll 2
-  for (int i = 0; i < kItems; ++i) {
-    const int64_t g = base + (int64_t)i * kThreads + threadIdx.x;
+  for (int i = 0; i < kRecItems; ++i) {
+    const int64_t g = base + (int64_t)i * kRecThreads + threadIdx.x;
     if (g >= nw) break;
     tr.to(woff, T, g);
     const xmem_window* w = win + woff[tr.t];
@@ -781,7 +869,7 @@ constexpr uint32_t kKept = 1u << 31, kStepCandidate = 1u << 30;  // role word: l
 // The window each block links to (index in its trace, -1 if none) and its role by the operator rule
 // (role: the category below kStepCandidate's bit); a parameter's size goes into its trace's set.
 // Per tile its kept blocks (part).
-__global__ __launch_bounds__(kThreads) void k_att_blocks(const xmem_block* blocks, const int64_t* boff, int64_t T, int64_t nb,
+__global__ __launch_bounds__(kRecThreads) void k_att_blocks(const xmem_block* blocks, const int64_t* boff, int64_t T, int64_t nb,
                                                          const xmem_window* win, const int64_t* woff,
                                                          const int64_t* comp_end, const uint32_t* in_step,
                                                          const int32_t* bad, int32_t* bwin, uint32_t* role, int32_t* cats,
@@ -792,8 +880,8 @@ __global__ __launch_bounds__(kThreads) void k_att_blocks(const xmem_block* block
   const int64_t base = (int64_t)blockIdx.x * kTileN;
   TraceStep tr(boff, T, tile_trace(boff, T, base));  // (its barrier orders s_cnt too)
   uint32_t kept = 0;
-  for (int i = 0; i < kItems; ++i) {
-    const int64_t b = base + (int64_t)i * kThreads + threadIdx.x;
+  for (int i = 0; i < kRecItems; ++i) {
+    const int64_t b = base + (int64_t)i * kRecThreads + threadIdx.x;
     if (b >= nb) break;
     tr.to(boff, T, b);
     const int64_t wbase = woff[tr.t], n = woff[tr.t + 1] - wbase;
@@ -838,26 +926,26 @@ __global__ __launch_bounds__(kThreads) void k_att_blocks(const xmem_block* block
 }
 // The kept blocks in order with their roles (a product in an optimizer.step() phase whose size is a
 // parameter's is an optimizer state), and the traces' offsets.
-__global__ __launch_bounds__(kThreads) void k_att_emit(const xmem_block* blocks, const int64_t* boff, int64_t T, int64_t nb,
+__global__ __launch_bounds__(kRecThreads) void k_att_emit(const xmem_block* blocks, const int64_t* boff, int64_t T, int64_t nb,
                                                        const int32_t* bad, const uint32_t* role, const int32_t* cats,
                                                        const uint32_t* tab, const uint32_t* part, xmem_block* kept,
                                                        int64_t* koff) {
   if (*bad) return;
   __shared__ TileFlags f;
   const int64_t base = (int64_t)blockIdx.x * kTileN;
-  uint32_t rl[kItems];
+  uint32_t rl[kRecItems];
 #pragma unroll
-  for (int i = 0; i < kItems; ++i) {
-    const int64_t b = base + (int64_t)i * kThreads + threadIdx.x;
+  for (int i = 0; i < kRecItems; ++i) {
+    const int64_t b = base + (int64_t)i * kRecThreads + threadIdx.x;
     rl[i] = b < nb ? role[b] : 0u;
     flags_put(f, i, rl[i] & kKept);
   }
   flags_scan(f);
-  const uint32_t at = part[blockIdx.x];
+  const uint32_t at = tile_before(part, gridDim.x);
   TraceStep tr(boff, T, tile_trace(boff, T, base));
 #pragma unroll 4
-  for (int i = 0; i < kItems; ++i) {
-    const int r = i * kThreads + threadIdx.x;
+  for (int i = 0; i < kRecItems; ++i) {
+    const int r = i * kRecThreads + threadIdx.x;
     const int64_t b = base + r;
     if (rl[i] & kKept) {
       xmem_block x = blocks[b];
@@ -890,7 +978,7 @@ __device__ __forceinline__ int64_t next_marker(const int64_t* v, int64_t lo, int
 // Retimed free of each block; the range of the times (sign bit flipped: signed order as unsigned) of
 // the allocation and free records that take part (a persistent block's free does not: it sorts
 // last by its trace); per tile the blocks that are freed (part).
-__global__ __launch_bounds__(kThreads) void k_orch_retime(const xmem_block* blocks, const int64_t* boff, int64_t T, int64_t nb,
+__global__ __launch_bounds__(kRecThreads) void k_orch_retime(const xmem_block* blocks, const int64_t* boff, int64_t T, int64_t nb,
                                                           const int64_t* steps, const int64_t* soff, const int64_t* zg,
                                                           const int64_t* zoff, const int32_t* bad, int64_t* tfr, uint64_t* kr,
                                                           uint32_t* part) {
@@ -902,8 +990,8 @@ __global__ __launch_bounds__(kThreads) void k_orch_retime(const xmem_block* bloc
   RangePart p;
   uint32_t freed = 0;
 #pragma unroll 4
-  for (int i = 0; i < kItems; ++i) {
-    const int64_t b = base + (int64_t)i * kThreads + threadIdx.x;
+  for (int i = 0; i < kRecItems; ++i) {
+    const int64_t b = base + (int64_t)i * kRecThreads + threadIdx.x;
     if (b >= nb) break;
     tr.to(boff, T, b);
     const xmem_block x = blocks[b];
@@ -944,7 +1032,7 @@ __global__ __launch_bounds__(kThreads) void k_orch_retime(const xmem_block* bloc
 // the time in an even number of passes, then the trace.  The host launches the same kernels either
 // way; the gates skip the passes a layout does not take: gate[0] the time sort (or the joint sort),
 // gate[1] the rank sort, gate[2] the trace sort.
-__global__ __launch_bounds__(kThreads) void k_orch_keys(const xmem_block* blocks, const int64_t* boff, int64_t T, int64_t nb,
+__global__ __launch_bounds__(kRecThreads) void k_orch_keys(const xmem_block* blocks, const int64_t* boff, int64_t T, int64_t nb,
                                                         const int64_t* tfr, int tbits, bool trace_odd, const int32_t* bad,
                                                         uint64_t* kr, int32_t* gate, uint64_t* ka, uint32_t* va,
                                                         uint64_t* kb, uint32_t* vb, uint32_t* tid, const uint32_t* part,
@@ -963,12 +1051,11 @@ __global__ __launch_bounds__(kThreads) void k_orch_keys(const xmem_block* blocks
     // the time sort starts in the second buffer; the separate layout then takes the trace passes
     const bool in_b = joint ? !(jp & 1) : !trace_odd;
     kr[5] = (joint ? kJoint : 0) | (in_b ? kJointBuf : 0) | ((uint64_t)tb << 8);
-    *total += (uint32_t)nb;  // words: an allocation each, and the frees counted so far
   }
   TraceStep tr(boff, T, tile_trace(boff, T, base));
 #pragma unroll 4
-  for (int i = 0; i < kItems; ++i) {
-    const int64_t b = base + (int64_t)i * kThreads + threadIdx.x;
+  for (int i = 0; i < kRecItems; ++i) {
+    const int64_t b = base + (int64_t)i * kRecThreads + threadIdx.x;
     const bool ok = b < nb;
     const int64_t fr = ok ? tfr[b] : kPersist;
     flags_put(f, i, fr != kPersist);
@@ -992,7 +1079,9 @@ __global__ __launch_bounds__(kThreads) void k_orch_keys(const xmem_block* blocks
     }
   }
   flags_scan(f);
-  tile_offsets(boff, T, nb, base, f, (uint32_t)base + part[blockIdx.x], 1, eoff);
+  const uint32_t frees = tile_before(part, gridDim.x);
+  if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) *total = (uint32_t)nb + frees + f.before[kSteps];
+  tile_offsets(boff, T, nb, base, f, (uint32_t)base + frees, 1, eoff);
 }
 // second key group of the separate layout: the time, rebased to the batch's earliest
 __global__ void k_orch_time_keys(const xmem_block* blocks, const int64_t* tfr, int64_t n, const int32_t* bad,
@@ -1011,8 +1100,36 @@ __global__ void k_orch_trace_keys(const uint32_t* btid, const int64_t* tfr, int6
   const uint32_t r = val[p];
   key[p] = ((r & 1) && tfr[r >> 1] == kPersist) ? (uint64_t)T : (uint64_t)btid[r >> 1];
 }
+// Few records: whichever sorts the layout takes, by one workgroup; the result lies where kr[5] says.
+__global__ __launch_bounds__(kOneThreads) void k_orch_sort_one(const xmem_block* blocks, const uint32_t* btid,
+                                                               const int64_t* tfr, int64_t n, int64_t T, int tp,
+                                                               const int32_t* bad, const uint64_t* kr, const int32_t* gate,
+                                                               uint64_t* ka, uint32_t* va, uint64_t* kb, uint32_t* vb) {
+  if (*bad) return;
+  __shared__ OneLds s;
+  if (kr[5] & kJoint) {
+    sort_one<false>(s, ka, va, kb, vb, (int)n, 0, gate[0], true);
+    return;
+  }
+  sort_one<false>(s, ka, va, kb, vb, (int)n, 0, kDigit, false);  // the rank, to (kb, vb)
+  __syncthreads();
+  for (int64_t p = threadIdx.x; p < n; p += kOneThreads) {
+    const uint32_t r = vb[p];
+    const int64_t tm = (r & 1) ? tfr[r >> 1] : blocks[r >> 1].t_alloc;
+    kb[p] = ((r & 1) && tm == kPersist) ? 0 : ((uint64_t)tm ^ (1ull << 63)) - kr[0];
+  }
+  __syncthreads();
+  sort_one<false>(s, ka, va, kb, vb, (int)n, 0, gate[0], true);  // the time, an even number of passes
+  __syncthreads();
+  for (int64_t p = threadIdx.x; p < n; p += kOneThreads) {
+    const uint32_t r = vb[p];
+    kb[p] = ((r & 1) && tfr[r >> 1] == kPersist) ? (uint64_t)T : (uint64_t)btid[r >> 1];
+  }
+  __syncthreads();
+  sort_one<false>(s, ka, va, kb, vb, (int)n, 0, tp * kDigit, true);
+}
 // position of each allocation's word within its trace
-__global__ __launch_bounds__(kThreads) void k_orch_apos(const int64_t* eoff, int64_t T, const uint32_t* total,
+__global__ __launch_bounds__(kRecThreads) void k_orch_apos(const int64_t* eoff, int64_t T, const uint32_t* total,
                                                         const int32_t* bad, const uint64_t* kr, const uint32_t* va,
                                                         const uint32_t* vb, uint32_t* apos) {
   const int64_t base = (int64_t)blockIdx.x * kTileN;
@@ -1021,8 +1138,8 @@ __global__ __launch_bounds__(kThreads) void k_orch_apos(const int64_t* eoff, int
   const uint32_t* val = (kr[5] & kJointBuf) ? vb : va;
   TraceStep tr(eoff, T, tile_trace(eoff, T, base));
 #pragma unroll 4
-  for (int i = 0; i < kItems; ++i) {
-    const int64_t p = base + (int64_t)i * kThreads + threadIdx.x;
+  for (int i = 0; i < kRecItems; ++i) {
+    const int64_t p = base + (int64_t)i * kRecThreads + threadIdx.x;
     if (p >= m) break;
     const uint32_t r = val[p];
     if (r & 1) continue;
@@ -1065,23 +1182,19 @@ int xmem_lifecycles(const xmem_raw_event* d_raw, const int32_t* d_category, cons
   begin({d_raw_offsets, n}, {nullptr, 0}, {nullptr, 0}, T, empty, d_unmatched_frees, w, d_status, d_block_offsets, st);
   if (!empty) {
     const int64_t nt = tiles_of(n);
-    int32_t* gate = reinterpret_cast<int32_t*>(w.kr + 3);
-    int32_t* gate2 = reinterpret_cast<int32_t*>(w.kr + 4);
-    int tbits = 0;
-    while (tbits < 63 && (T >> tbits) != 0) ++tbits;  // bits of the trace field (0..T)
-    const int tp = passes_for(T);
-    k_life_range<<<(unsigned)std::min<int64_t>(kRangeBlocks, grid_of(n, kThreads)), kThreads, 0, st>>>(d_raw, n, w.bad, w.kr);
-    k_life_keys<<<(unsigned)nt, kThreads, 0, st>>>(d_raw, d_raw_offsets, n, T, tbits, tp & 1, w.bad, w.kr, w.s.ka, w.s.va,
-                                                   w.tid, gate, gate2, w.s.hist, nt, w.part);
-    k_scan_top<<<1, kScanThreads, 0, st>>>(w.part, nt, w.total);
-    // by (trace, address), or by address in an even number of passes; stream order kept
-    sort_bits(w.s, n, kAllBits, false, st, gate, true);
-    // the separate layout only: then by trace (from the buffer the even passes end in)
-    k_life_trace_keys<<<grid_of(n, 256), 256, 0, st>>>(d_raw, w.tid, n, T, w.bad, w.kr, w.s.va, w.s.ka);
-    sort_bits(w.s, n, tp * kDigit, false, st, gate2);
-    k_life_pair<<<grid_of(n, 256), 256, 0, st>>>(d_raw, w.tid, w.kr, w.s.ka, w.s.va, w.s.kb, w.s.vb, n, T, w.bad,
-                                                 w.t64, d_unmatched_frees);
-    k_life_emit<<<(unsigned)nt, kThreads, 0, st>>>(d_raw, d_category, d_raw_offsets, T, n, w.bad, w.part, w.t64, d_blocks,
+    // digits of the hash: enough that a key shares all of them with few others
+    const int shift0 = kHashBits - kDigit * (n <= (1 << 17) ? 2 : n <= (1 << 25) ? 3 : 4);
+    k_life_keys<<<(unsigned)nt, kRecThreads, 0, st>>>(d_raw, d_raw_offsets, n, T, w.bad, w.s.ka, w.s.va, shift0, w.s.hist, nt,
+                                                      w.part);
+    scan_parts(w.part, nt, st);
+    bool in_b = ((kHashBits - shift0) / kDigit) & 1;
+    if (n <= kOneRecords)
+      k_life_sort_one<<<1, kOneThreads, 0, st>>>(n, shift0, w.bad, w.s.ka, w.s.va, w.s.kb, w.s.vb);
+    else
+      in_b = sort_bits<true>(w.s, n, shift0, kHashBits, false, st, nullptr, true);
+    k_life_pair<<<grid_of(n, 256), 256, 0, st>>>(d_raw, d_raw_offsets, T, in_b ? w.s.kb : w.s.ka, in_b ? w.s.vb : w.s.va, n,
+                                                 shift0, w.bad, w.t64, d_unmatched_frees);
+    k_life_emit<<<(unsigned)nt, kRecThreads, 0, st>>>(d_raw, d_category, d_raw_offsets, T, n, w.bad, w.part, w.t64, d_blocks,
                                                    d_block_offsets);
   }
   finish(T, empty, w, d_status, d_block_offsets, st);
@@ -1111,13 +1224,13 @@ int xmem_attribute(const xmem_block* d_blocks, const int64_t* d_block_offsets, i
   begin({d_block_offsets, nb}, {d_window_offsets, nw}, {nullptr, 0}, T, empty, nullptr, w, d_status, d_kept_offsets, st);
   if (!empty) {
     const int64_t nt = tiles_of(nb);
-    k_att_windows<<<(unsigned)tiles_of(n), kThreads, 0, st>>>(d_windows, d_window_offsets, T, nw, nb, w.bad, comp_end, in_step,
+    k_att_windows<<<(unsigned)tiles_of(n), kRecThreads, 0, st>>>(d_windows, d_window_offsets, T, nw, nb, w.bad, comp_end, in_step,
                                                               tab);
-    k_att_blocks<<<(unsigned)nt, kThreads, 0, st>>>(d_blocks, d_block_offsets, T, nb, d_windows, d_window_offsets, comp_end,
+    k_att_blocks<<<(unsigned)nt, kRecThreads, 0, st>>>(d_blocks, d_block_offsets, T, nb, d_windows, d_window_offsets, comp_end,
                                                     in_step, w.bad, d_block_window, w.tid, cats,
                                                     reinterpret_cast<uint32_t*>(tab), w.part);
-    k_scan_top<<<1, kScanThreads, 0, st>>>(w.part, nt, w.total);
-    k_att_emit<<<(unsigned)nt, kThreads, 0, st>>>(d_blocks, d_block_offsets, T, nb, w.bad, w.tid, cats,
+    scan_parts(w.part, nt, st);
+    k_att_emit<<<(unsigned)nt, kRecThreads, 0, st>>>(d_blocks, d_block_offsets, T, nb, w.bad, w.tid, cats,
                                                   reinterpret_cast<uint32_t*>(tab), w.part, d_kept, d_kept_offsets);
   }
   finish(T, empty, w, d_status, d_kept_offsets, st);
@@ -1149,17 +1262,22 @@ int xmem_orchestrate(const xmem_block* d_blocks, const int64_t* d_block_offsets,
     int tbits = 0;
     while (tbits < 63 && (T >> tbits) != 0) ++tbits;  // bits of the trace field (0..T)
     const int tp = passes_for(T);
-    k_orch_retime<<<(unsigned)nt, kThreads, 0, st>>>(d_blocks, d_block_offsets, T, nb, d_step_ts, d_step_offsets,
+    k_orch_retime<<<(unsigned)nt, kRecThreads, 0, st>>>(d_blocks, d_block_offsets, T, nb, d_step_ts, d_step_offsets,
                                                      d_zero_grad_ts, d_zero_grad_offsets, w.bad, w.t64, w.kr, w.part);
-    k_scan_top<<<1, kScanThreads, 0, st>>>(w.part, nt, w.total);
-    k_orch_keys<<<(unsigned)nt, kThreads, 0, st>>>(d_blocks, d_block_offsets, T, nb, w.t64, tbits, tp & 1, w.bad, w.kr, gate,
+    scan_parts(w.part, nt, st);
+    k_orch_keys<<<(unsigned)nt, kRecThreads, 0, st>>>(d_blocks, d_block_offsets, T, nb, w.t64, tbits, tp & 1, w.bad, w.kr, gate,
                                                    w.s.ka, w.s.va, w.s.kb, w.s.vb, w.tid, w.part, w.total, d_event_offsets);
-    sort_bits(w.s, n, kDigit, false, st, gate + 1);  // rank at equal times (separate layout)
-    k_orch_time_keys<<<grid_of(n, 256), 256, 0, st>>>(d_blocks, w.t64, n, w.bad, w.kr, w.s.vb, w.s.kb);
-    sort_bits(w.s, n, kAllBits, true, st, gate);  // time (its span only), or the joint key
-    k_orch_trace_keys<<<grid_of(n, 256), 256, 0, st>>>(w.tid, w.t64, n, T, w.bad, w.kr, w.s.vb, w.s.kb);
-    sort_bits(w.s, n, tp * kDigit, true, st, gate + 2);  // trace; persistent blocks' frees last
-    k_orch_apos<<<(unsigned)tiles_of(n), kThreads, 0, st>>>(d_event_offsets, T, w.total, w.bad, w.kr, w.s.va, w.s.vb, w.apos);
+    if (n <= kOneRecords) {
+      k_orch_sort_one<<<1, kOneThreads, 0, st>>>(d_blocks, w.tid, w.t64, n, T, tp, w.bad, w.kr, gate, w.s.ka, w.s.va, w.s.kb,
+                                                 w.s.vb);
+    } else {
+      sort_bits<false>(w.s, n, 0, kDigit, false, st, gate + 1);  // rank at equal times (separate layout)
+      k_orch_time_keys<<<grid_of(n, 256), 256, 0, st>>>(d_blocks, w.t64, n, w.bad, w.kr, w.s.vb, w.s.kb);
+      sort_bits<false>(w.s, n, 0, kAllBits, true, st, gate);  // time (its span only), or the joint key
+      k_orch_trace_keys<<<grid_of(n, 256), 256, 0, st>>>(w.tid, w.t64, n, T, w.bad, w.kr, w.s.vb, w.s.kb);
+      sort_bits<false>(w.s, n, 0, tp * kDigit, true, st, gate + 2);  // trace; persistent blocks' frees last
+    }
+    k_orch_apos<<<(unsigned)tiles_of(n), kRecThreads, 0, st>>>(d_event_offsets, T, w.total, w.bad, w.kr, w.s.va, w.s.vb, w.apos);
     k_orch_words<<<grid_of(n, 256), 256, 0, st>>>(d_blocks, w.total, w.bad, w.kr, w.s.va, w.s.vb, w.apos, d_events);
   }
   finish(T, empty, w, d_status, d_event_offsets, st);
