@@ -53,6 +53,7 @@ constexpr int kBins = 1 << kDigit;
 constexpr int kSteps = kTileN / 64;       // 64-record steps of a tile
 constexpr int kWaves = kThreads / 64;
 constexpr int kScanThreads = 1024;
+constexpr int kXcds = 8;
 // the kernels that work on records (not the sort's passes): a tile per workgroup of 1024, whose
 // chains of dependent loads (window climbs, marker searches) need the wavefronts
 constexpr int kRecThreads = 1024;
@@ -306,6 +307,11 @@ __global__ __launch_bounds__(kThreads, 4) void k_rs_scatter(const uint64_t* kin,
                                                          uint32_t* vout, int64_t n, int shift, const uint32_t* off,
                                                          const uint32_t* tot, int64_t ntiles, const int32_t* gate) {
   if (gated(gate, shift)) return;
+  // workgroups go round-robin over the 8 XCDs: each takes a contiguous eighth of the tiles, so that
+  // the lines shared by the runs of neighbouring tiles fill up in one L2 (128 profiles of 65,536
+  // events: 1,658 -> 1,610 us for the three steps)
+  const int64_t tile = (int64_t)(blockIdx.x % kXcds) * (gridDim.x / kXcds) + blockIdx.x / kXcds;
+  if (tile >= ntiles) return;
   // the tile in output order: keys, then values (two phases); before that, per-wavefront digit
   // counts and their exclusive scan (so that the LDS allows four workgroups per CU)
   __shared__ uint64_t sk[kTileN];
@@ -317,7 +323,7 @@ __global__ __launch_bounds__(kThreads, 4) void k_rs_scatter(const uint64_t* kin,
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   const uint64_t below = (1ull << lane) - 1;
   for (int d = lane; d < kBins; d += 64) wcnt[wv][d] = 0;
-  const int64_t base = (int64_t)blockIdx.x * kTileN + (int64_t)wv * (kTileN / kWaves);
+  const int64_t base = tile * kTileN + (int64_t)wv * (kTileN / kWaves);
   uint64_t key[kItems];
   uint32_t val[kItems], rd[kItems];  // rank in the wavefront's digit run | digit << 16 (kBins: no element)
 #pragma unroll
@@ -363,7 +369,7 @@ __global__ __launch_bounds__(kThreads, 4) void k_rs_scatter(const uint64_t* kin,
       const int d = 2 * tid + j;
       const uint32_t tb = local + (j ? cnt[0] : 0u);
       tbase[d] = tb;
-      gbase[d] = global + (j ? all[0] : 0u) + off[(int64_t)d * ntiles + blockIdx.x] - tb;
+      gbase[d] = global + (j ? all[0] : 0u) + off[(int64_t)d * ntiles + tile] - tb;
     }
   }
   __syncthreads();
@@ -377,7 +383,7 @@ __global__ __launch_bounds__(kThreads, 4) void k_rs_scatter(const uint64_t* kin,
   for (int i = 0; i < kItems; ++i)
     if (rd[i] != 0xffffffffu) sk[rd[i]] = key[i];
   __syncthreads();
-  const int64_t cnt = n - (int64_t)blockIdx.x * kTileN < kTileN ? n - (int64_t)blockIdx.x * kTileN : kTileN;
+  const int64_t cnt = n - tile * kTileN < kTileN ? n - tile * kTileN : kTileN;
   // sorted place tid + kThreads j of the tile: its output index (below XMEM_PREP_MAX_RECORDS)
   uint32_t out_at[kItems];
 #pragma unroll
@@ -422,7 +428,7 @@ bool sort_bits(SortWs& w, int64_t n, int lo, int hi, bool in_b, hipStream_t st, 
     uint32_t* vout = in_b ? w.va : w.vb;
     if (sh > lo || !hist_done) k_rs_hist<HASHED><<<(unsigned)nt, kThreads, 0, st>>>(kin, n, sh, w.hist, nt, gate);
     k_rs_rows<<<kBins, kThreads, 0, st>>>(w.hist, nt, w.tot, gate, sh);
-    k_rs_scatter<HASHED><<<(unsigned)nt, kThreads, 0, st>>>(kin, vin, kout, vout, n, sh, w.hist, w.tot, nt, gate);
+    k_rs_scatter<HASHED><<<(unsigned)((nt + kXcds - 1) / kXcds * kXcds), kThreads, 0, st>>>(kin, vin, kout, vout, n, sh, w.hist, w.tot, nt, gate);
     in_b = !in_b;
   }
   return in_b;
@@ -1182,8 +1188,10 @@ int xmem_lifecycles(const xmem_raw_event* d_raw, const int32_t* d_category, cons
   begin({d_raw_offsets, n}, {nullptr, 0}, {nullptr, 0}, T, empty, d_unmatched_frees, w, d_status, d_block_offsets, st);
   if (!empty) {
     const int64_t nt = tiles_of(n);
-    // digits of the hash: enough that a key shares all of them with few others
-    const int shift0 = kHashBits - kDigit * (n <= (1 << 17) ? 2 : n <= (1 << 25) ? 3 : 4);
+    // digits of the hash: enough that a key shares all of them with few others.  320,160 events in
+    // two digits rather than three: 1,027 -> 1,014 us for a whole estimate; 8.4M in two rather than
+    // three: 1,610 -> 1,665 us (the pairing then looks past more of the others)
+    const int shift0 = kHashBits - kDigit * (n <= (1 << 20) ? 2 : n <= (1 << 25) ? 3 : 4);
     k_life_keys<<<(unsigned)nt, kRecThreads, 0, st>>>(d_raw, d_raw_offsets, n, T, w.bad, w.s.ka, w.s.va, shift0, w.s.hist, nt,
                                                       w.part);
     scan_parts(w.part, nt, st);
