@@ -1633,6 +1633,7 @@ __device__ __forceinline__ int chain_step(C& c, const Derived& d, const Gw& w, G
                                           const uint64_t& fwd_prev) {
   auto& ps = c.p[PI];
   const int64_t e = ts + j;
+  pool_room(c, ps);
   if ((opw >> kKindShift) == kKindAlloc) {
     uint64_t b;
     const int st = pool_alloc(c, ps, d, w, opw & kUnitsMask, e, &b);
@@ -1703,10 +1704,24 @@ __device__ __forceinline__ void chain_run(C& c, const Derived& d, const Gw& w, i
     const bool mine = (ts + lane < limit) && (cur_op >> kKindShift) != 0 &&
                       (NP == 2 || ((cur_op & kPoolBit) ? 1 : 0) == pool_one);
     uint64_t todo = ballot(mine && (!resumed || ts + lane >= skip));
+    uint64_t pairs;  // allocations that the chain's next event frees again
+    {
+      const int64_t fe = (int64_t)(0xffffffffu - cur_link);
+      const uint64_t after = (ballot(mine) >> lane) >> 1;
+      const int64_t next = after ? ts + lane + 1 + __builtin_ctzll(after | (1ull << 63)) : -1;
+      pairs = ballot(mine && (cur_op >> kKindShift) == kKindAlloc && cur_link != 0 && fe == next);
+    }
     while (todo) {
       const int j = __builtin_ctzll(todo);
       todo &= todo - 1;
       const uint64_t opw = rl64(cur_op, j);
+      if ((pairs >> j) & 1) {
+        const bool one = NP == 1 || !(opw & kPoolBit);
+        if (one ? pool_pair(c, c.p[0], opw & kUnitsMask) : pool_pair(c, c.p[NP - 1], opw & kUnitsMask)) {
+          todo &= todo - 1;
+          continue;
+        }
+      }
       const uint32_t lk = rl(cur_link, j);
       int st;
       if (NP == 1 || !(opw & kPoolBit)) st = chain_step<NP, 0>(c, d, w, mkey, ts, j, opw, lk, cur_mb, fwd_cur, fwd_prev);
@@ -3057,14 +3072,17 @@ __global__ void k_combo_adopt(int64_t nchains, Ws ws) {
 // this workgroup's slot of the workspace.  An LDS directory holds each page's
 // first key, id and count in key order, and one register per lane holds the
 // first key of every 64th directory entry, so a key is located with two
-// ballots.  A full page splits; a page that falls below half merges with a
-// neighbour or takes keys from it, so every page but a lone one is at least
-// half full.  A set that would need more pages than its directory holds hands
-// the chain to the 64-bit kernel (status kRetry).
+// ballots.  A full page splits; a page that falls below a quarter merges with a
+// neighbour or takes keys from it, and where the directory is full, neighbours
+// that fit in one page are merged, so a set always holds half a page of keys
+// for each directory entry.  A set that would need more pages than its
+// directory holds hands the chain to the 64-bit kernel (status kRetry).
 constexpr int kPage = 64;
 constexpr int32_t kBigDir1 = 4096;  // directory entries per set: chains of one pool (two sets)
 constexpr int32_t kBigDir2 = 2048;  // directory entries per set: chains of both pools (four sets)
 constexpr int kBigSlots = 64;       // chains the paged kernel replays at once
+constexpr int kCacheSlots = 120;    // pages a workgroup keeps in LDS: what the directories leave of 160 KB
+static_assert(kCacheSlots / 2 <= kWave, "a lane for each of a set's slots");
 constexpr int64_t kBigSlotKeys = 4 * (int64_t)(kBigDir2 + 2) * kPage;
 static_assert(2 * (int64_t)(kBigDir1 + 2) * kPage <= kBigSlotKeys, "slot holds both layouts");
 static_assert(kBigDir1 <= 64 * kWave, "one summary register covers the directory");
@@ -3072,19 +3090,55 @@ static_assert(kBigSlotKeys == kBigSlotKeysHost && kBigSlots == 64, "the workspac
 
 __device__ __forceinline__ int msb64(uint64_t m) { return 63 - __builtin_clzll(m); }
 
+// What bounds an event on the paged sets is a chain of dependent accesses: with one page kept at hand
+// each event loaded 1.4 pages, and waited for them and for the stores before them (16.8M events,
+// 62,000 free blocks: 1.67 us an event on 126 CUs; now 1.04).  So each set keeps its last pages in
+// LDS: slot i < ways holds the page of lane i's tag, and the page in use is in a register too.  First
+// in, first out (the address-ordered set sweeps more pages than fit: with 120 slots in all a second
+// chance would keep no more); a page that changed is written back when it leaves.
 struct Pss {
-  LMEM uint64_t* dkey;   // first key of directory entry i < np, ascending
+  LMEM uint64_t* dkey;   // first key of directory entry i < np, ascending; kNoKey past them
   LMEM uint32_t* dpg;    // entry i < np: page id | count << 16; the last nfree words: free page ids
   GMEM uint64_t* pages;  // page p: key l at pages[kPage * p + l], ascending, kNoKey past the count
+  LMEM uint64_t* slots;  // the kept pages
   uint64_t S;            // lane r: dkey[64 r] (kNoKey past the directory)
-  uint64_t cv;           // keys of page cpid: the last page loaded or stored
-  int32_t cpid, np, nfree, bump, cap, nkeys;
+  uint64_t cv;           // keys of page cpid, which slot cslot holds
+  uint32_t tag, dirty;   // lane i: the page in slot i (-1: none); whether it differs from memory
+  int32_t cpid, cslot, hand, ways, np, nfree, bump, cap, nkeys;
 };
+// the next slot, given to page pid (the page it held is written back)
+__device__ __forceinline__ void cache_take(Pss& P, int32_t pid) {
+  const int lane = threadIdx.x;
+  const int32_t s = P.hand;
+  P.hand = s + 1 == P.ways ? 0 : s + 1;
+  if (rl(P.dirty, s)) P.pages[(int64_t)kPage * (int32_t)rl(P.tag, s) + lane] = P.slots[kPage * s + lane];
+  P.tag = lane == s ? (uint32_t)pid : P.tag;
+  P.dirty = lane == s ? 0u : P.dirty;
+  P.cslot = s;
+  P.cpid = pid;
+}
+// every kept page that differs from memory is written back
+__device__ __forceinline__ void cache_flush(Pss& P) {
+  const int lane = threadIdx.x;
+  for (uint64_t m = ballot(P.dirty != 0); m; m &= m - 1) {
+    const int s = __builtin_ctzll(m);
+    P.pages[(int64_t)kPage * (int32_t)rl(P.tag, s) + lane] = P.slots[kPage * s + lane];
+  }
+  P.dirty = 0;
+  wave_order();
+}
 
-__device__ __forceinline__ void pss_init(Pss& P, LMEM uint64_t* dkey, LMEM uint32_t* dpg, GMEM uint64_t* pages,
-                                         int32_t cap) {
-  P.dkey = dkey; P.dpg = dpg; P.pages = pages;
-  P.S = kNoKey; P.cv = kNoKey; P.cpid = -1;
+// an empty set on the pages from `pages` on, keeping up to ways <= 64 of them in `slots`
+__device__ __forceinline__ void pss_init(Pss& P, LMEM uint64_t* dkey, LMEM uint32_t* dpg, int32_t entries,
+                                         GMEM uint64_t* pages, LMEM uint64_t* slots, int32_t ways, int32_t cap) {
+  for (int32_t k = threadIdx.x; k < entries; k += kWave) dkey[k] = kNoKey;
+  wave_order();
+  P.dkey = dkey; P.dpg = dpg; P.pages = pages; P.slots = slots;
+  P.S = kNoKey; P.cv = kNoKey;
+  P.tag = ~0u; P.dirty = 0;
+  P.cpid = -1;
+  P.cslot = P.hand = 0;
+  P.ways = ways;
   P.np = P.nfree = P.bump = P.nkeys = 0;
   P.cap = cap;
 }
@@ -3094,39 +3148,53 @@ __device__ __forceinline__ void pss_summary(Pss& P) {
 }
 struct Ent { int32_t pid, cnt; };
 __device__ __forceinline__ Ent pss_decode(const Pss& P, uint32_t e) {
-  const int32_t pid = (int32_t)(e & 0xffffu);
-  return Ent{pid <= P.cap + 1 ? pid : P.cap + 1, (int32_t)(e >> 16)};  // ids stay inside the set's pages
+  const int32_t pid = (int32_t)(e & 0xffffu), last = P.cap + 1;
+  return Ent{pid < last ? pid : last, (int32_t)(e >> 16)};  // ids stay inside the set's pages
 }
 __device__ __forceinline__ Ent pss_ent(const Pss& P, int32_t i) { return pss_decode(P, uni(P.dpg[i])); }
-// last directory entry whose first key is <= x (-1 if none), and that entry: the row's first keys
-// and page words are read together, so the entry costs no second LDS round trip
-__device__ __forceinline__ int32_t pss_locate(const Pss& P, uint64_t x, Ent* en) {
-  const uint64_t m = ballot(P.S <= x);
-  if (!m) return -1;
-  const int32_t r0 = 64 * msb64(m);
-  const int32_t k = r0 + (int32_t)threadIdx.x;
-  const uint64_t dk = k < P.np ? P.dkey[k] : kNoKey;
-  const uint32_t dp = k < P.np ? P.dpg[k] : 0u;
-  const int l = msb64(ballot(dk <= x));
-  *en = pss_decode(P, rl(dp, l));
-  return r0 + l;
-}
 __device__ __forceinline__ void pss_set(Pss& P, int32_t i, uint64_t first, int32_t pid, int32_t cnt) {
   if (threadIdx.x == 0) { P.dkey[i] = first; P.dpg[i] = (uint32_t)pid | ((uint32_t)cnt << 16); }
   if ((i & 63) == 0) P.S = (int)threadIdx.x == (i >> 6) ? first : P.S;
   wave_order();
 }
+__device__ __forceinline__ void pss_count(Pss& P, int32_t i, int32_t pid, int32_t cnt) {
+  if (threadIdx.x == 0) P.dpg[i] = (uint32_t)pid | ((uint32_t)cnt << 16);
+  wave_order();
+}
 __device__ __forceinline__ uint64_t page_get(Pss& P, int32_t pid) {
   if (pid != P.cpid) {
-    P.cv = P.pages[(int64_t)kPage * pid + threadIdx.x];
-    P.cpid = pid;
+    const uint64_t m = ballot(P.tag == (uint32_t)pid);
+    if (m) {
+      P.cslot = __builtin_ctzll(m);
+      P.cpid = pid;
+      P.cv = P.slots[kPage * P.cslot + threadIdx.x];
+    } else {
+      const uint64_t v = P.pages[(int64_t)kPage * pid + threadIdx.x];
+      cache_take(P, pid);
+      P.slots[kPage * P.cslot + threadIdx.x] = v;
+      P.cv = v;
+    }
   }
   return P.cv;
 }
-__device__ __forceinline__ void page_put(Pss& P, int32_t pid, uint64_t v) {
-  P.pages[(int64_t)kPage * pid + threadIdx.x] = v;
+// the page in use becomes v
+__device__ __forceinline__ void page_store(Pss& P, uint64_t v) {
+  P.slots[kPage * P.cslot + threadIdx.x] = v;
+  P.dirty = (int)threadIdx.x == P.cslot ? 1u : P.dirty;
   P.cv = v;
-  P.cpid = pid;
+}
+// page pid becomes v
+__device__ __forceinline__ void page_put(Pss& P, int32_t pid, uint64_t v) {
+  if (pid != P.cpid) {
+    const uint64_t m = ballot(P.tag == (uint32_t)pid);
+    if (m) {
+      P.cslot = __builtin_ctzll(m);
+      P.cpid = pid;
+    } else {
+      cache_take(P, pid);
+    }
+  }
+  page_store(P, v);
 }
 __device__ __forceinline__ int32_t page_new(Pss& P) {
   if (P.nfree > 0) {
@@ -3140,6 +3208,9 @@ __device__ __forceinline__ void page_drop(Pss& P, int32_t pid) {
   P.nfree += 1;
   if (threadIdx.x == 0) P.dpg[P.cap + 2 - P.nfree] = (uint32_t)pid;
   wave_order();
+  const bool h = P.tag == (uint32_t)pid;
+  P.tag = h ? ~0u : P.tag;
+  P.dirty = h ? 0u : P.dirty;
   if (P.cpid == pid) P.cpid = -1;
 }
 // the page with key v at lane pos removed; lane 63 becomes empty
@@ -3155,31 +3226,48 @@ __device__ __forceinline__ uint64_t page_ins(uint64_t v, int pos, uint64_t x) {
   const uint64_t dn = from_lower_lane(v);
   return lane > pos ? dn : (lane == pos ? x : v);
 }
-// entries [i, np) move up one (rows from the last, each read before it is written)
+// entries [i, np) move up one (four rows at once, from the last; each read before it is written)
 __device__ __forceinline__ void dir_shift_up(LMEM uint64_t* dkey, LMEM uint32_t* dpg, int32_t np, int32_t i) {
   const int32_t lane = threadIdx.x;
-  for (int32_t r0 = ((np - 1) >> 6) << 6; r0 >= (i & ~63); r0 -= 64) {
-    const int32_t k = r0 + lane;
-    const bool mv = k >= i && k < np;
-    const uint64_t a = mv ? dkey[k] : 0;
-    const uint32_t b = mv ? dpg[k] : 0;
+  for (int32_t r0 = ((np - 1) >> 6) << 6; r0 >= (i & ~63); r0 -= 256) {
+    uint64_t a[4];
+    uint32_t b[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int32_t k = r0 - 64 * q + lane;
+      a[q] = dkey[k >= 0 ? k : 0];
+      b[q] = dpg[k >= 0 ? k : 0];
+    }
     wave_order();
-    if (mv) { dkey[k + 1] = a; dpg[k + 1] = b; }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int32_t k = r0 - 64 * q + lane;
+      if (k >= i && k < np) { dkey[k + 1] = a[q]; dpg[k + 1] = b[q]; }
+    }
     wave_order();
   }
 }
-// entries [i + 1, np) move down one (rows from the first)
+// entries [i + 1, np) move down one (four rows at once, from the first); entry np - 1 becomes empty
 __device__ __forceinline__ void dir_shift_down(LMEM uint64_t* dkey, LMEM uint32_t* dpg, int32_t np, int32_t i) {
   const int32_t lane = threadIdx.x;
-  for (int32_t r0 = (i + 1) & ~63; r0 < np; r0 += 64) {
-    const int32_t k = r0 + lane;
-    const bool mv = k > i && k < np;
-    const uint64_t a = mv ? dkey[k] : 0;
-    const uint32_t b = mv ? dpg[k] : 0;
+  for (int32_t r0 = (i + 1) & ~63; r0 < np; r0 += 256) {
+    uint64_t a[4];
+    uint32_t b[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int32_t k = r0 + 64 * q + lane;
+      a[q] = dkey[k < np ? k : np - 1];
+      b[q] = dpg[k < np ? k : np - 1];
+    }
     wave_order();
-    if (mv) { dkey[k - 1] = a; dpg[k - 1] = b; }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int32_t k = r0 + 64 * q + lane;
+      if (k > i && k < np) { dkey[k - 1] = a[q]; dpg[k - 1] = b[q]; }
+    }
     wave_order();
   }
+  if (lane == 0) dkey[np - 1] = kNoKey;
 }
 __device__ __forceinline__ void pss_dir_insert(Pss& P, int32_t i, uint64_t first, int32_t pid, int32_t cnt) {
   dir_shift_up(P.dkey, P.dpg, P.np, i);
@@ -3195,34 +3283,42 @@ __device__ __forceinline__ void pss_dir_remove(Pss& P, int32_t i) {
   pss_summary(P);
 }
 
-// first key >= x (kNoKey if none)
-__device__ __forceinline__ uint64_t pss_first_ge(Pss& P, uint64_t x) {
-  if (P.np == 0) return kNoKey;
-  Ent en;
-  const int32_t i = pss_locate(P, x, &en);
-  if (i < 0) return rl64(P.S, 0);  // x is below every key
+// A place in a set: directory entry i (its page pid, of cnt keys v: the page in use) and lane pos in it.
+struct Cur {
+  int32_t i, pid, cnt, pos;
+  uint64_t v;
+};
+// Where x belongs in a set that isn't empty: in the last page whose first key is <= x (the first page
+// where there is none), before its first key >= x.  The directory row's first keys and page words are
+// read together, so the entry costs no second LDS round trip.
+__device__ __forceinline__ Cur pss_seek(Pss& P, uint64_t x) {
+  const uint64_t m = ballot(P.S <= x);
+  const int32_t r0 = m ? 64 * msb64(m) : 0;
+  const int32_t k = r0 + (int32_t)threadIdx.x;
+  const uint64_t dk = P.dkey[k];
+  const uint32_t dp = P.dpg[k];
+  const uint64_t m2 = ballot(dk <= x);
+  const int l = m2 ? msb64(m2) : 0;
+  const Ent en = pss_decode(P, rl(dp, l));
   const uint64_t v = page_get(P, en.pid);
-  const uint64_t m = ballot(v >= x);
-  const int pos = m ? __builtin_ctzll(m) : kPage;
-  if (pos < en.cnt) return rl64(v, pos);
-  return i + 1 < P.np ? uni64(P.dkey[i + 1]) : kNoKey;
+  return Cur{r0 + l, en.pid, en.cnt, (int32_t)__builtin_popcountll(ballot(v < x)), v};
 }
-// last key <= x (kNoKey if none)
-__device__ __forceinline__ uint64_t pss_last_le(Pss& P, uint64_t x) {
-  if (P.np == 0) return kNoKey;
-  Ent en;
-  const int32_t i = pss_locate(P, x, &en);
-  if (i < 0) return kNoKey;
-  const uint64_t v = page_get(P, en.pid);
-  return rl64(v, msb64(ballot(v <= x)));  // the page's first key is <= x
+// the place of the first key >= x; false if there is none
+__device__ __forceinline__ bool pss_first_ge(Pss& P, uint64_t x, Cur* cu) {
+  if (P.np == 0) return false;
+  *cu = pss_seek(P, x);
+  if (cu->pos < cu->cnt) return true;
+  if (cu->i + 1 >= P.np) return false;
+  const Ent en = pss_ent(P, cu->i + 1);
+  *cu = Cur{cu->i + 1, en.pid, en.cnt, 0, page_get(P, en.pid)};
+  return true;
 }
 
-constexpr int kOpErase = 0, kOpInsert = 1, kOpRekey = 2;
-
-// Page i (keys w, count cnt) fell below half: merge it with a neighbour, or even
-// the two out when together they fill more than a page.
-__device__ __forceinline__ void pss_rebalance(Pss& P, LMEM uint64_t* stage, int32_t i, uint64_t w, int32_t pid,
-                                              int32_t cnt) {
+// Page i (keys w, count cnt) fell below a quarter: merge it with a neighbour, or even the two out
+// when together they fill more than three quarters of a page (pages just split or evened out are
+// some changes away from the next).
+__device__ __forceinline__ void pss_rebalance(Pss& P, LMEM uint64_t* stage, int32_t i, uint64_t w,
+                                              int32_t pid, int32_t cnt) {
   const int lane = threadIdx.x;
   const int32_t j = i + 1 < P.np ? i + 1 : i - 1;
   const Ent ej = pss_ent(P, j);
@@ -3236,7 +3332,7 @@ __device__ __forceinline__ void pss_rebalance(Pss& P, LMEM uint64_t* stage, int3
   if (lane < cl) stage[lane] = vl;
   if (lane < cr) stage[cl + lane] = vr;
   wave_order();
-  if (tot <= kPage) {
+  if (tot <= kPage * 3 / 4) {
     const uint64_t m = lane < tot ? stage[lane] : kNoKey;
     wave_order();
     page_put(P, pl, m);
@@ -3254,100 +3350,106 @@ __device__ __forceinline__ void pss_rebalance(Pss& P, LMEM uint64_t* stage, int3
     pss_set(P, r, rl64(b, 0), pr, tot - h);
   }
 }
-
-// One update of a set: erase x, insert x, or replace x by y (y sorts where x
-// did).  Erased and replaced keys are present; inserted keys are not.  False
-// when an insert needs a page the directory has no entry for.
-__device__ __forceinline__ bool pss_op(Pss& P, LMEM uint64_t* stage, int kind, uint64_t x, uint64_t y) {
+// The directory is full: neighbours that fit in one page are merged.
+__device__ __forceinline__ void pss_compact(Pss& P, LMEM uint64_t* stage) {
   const int lane = threadIdx.x;
-  if (P.np == 0) {  // only an insert reaches an empty set
-    const int32_t pid = page_new(P);
-    page_put(P, pid, lane == 0 ? x : kNoKey);
-    pss_dir_insert(P, 0, x, pid, 1);
-    P.nkeys += 1;
-    return true;
+  for (int32_t i = 0; i + 1 < P.np;) {
+    const Ent a = pss_ent(P, i), b = pss_ent(P, i + 1);
+    if (a.cnt + b.cnt > kPage) { ++i; continue; }
+    const uint64_t va = page_get(P, a.pid);
+    if (lane < a.cnt) stage[lane] = va;
+    const uint64_t vb = page_get(P, b.pid);
+    if (lane < b.cnt) stage[a.cnt + lane] = vb;
+    wave_order();
+    const uint64_t m = lane < a.cnt + b.cnt ? stage[lane] : kNoKey;
+    wave_order();
+    page_put(P, a.pid, m);
+    pss_set(P, i, rl64(m, 0), a.pid, a.cnt + b.cnt);
+    page_drop(P, b.pid);
+    pss_dir_remove(P, i + 1);
   }
-  Ent en;
-  int32_t i = pss_locate(P, x, &en);
-  if (i < 0) {  // an insert below every key
-    i = 0;
-    en = pss_ent(P, 0);
+}
+
+// the key at cu leaves the set
+__device__ __forceinline__ void pss_erase_at(Pss& P, LMEM uint64_t* stage, const Cur& cu) {
+  const int32_t cnt = cu.cnt - 1;
+  P.nkeys -= 1;
+  if (cnt == 0) {  // the page emptied
+    page_drop(P, cu.pid);
+    pss_dir_remove(P, cu.i);
+    return;
   }
-  const uint64_t v = page_get(P, en.pid);
-  if (kind != kOpInsert) {
-    const uint64_t hit = ballot(v == x);
-    const int pos = hit ? __builtin_ctzll(hit) : kPage - 1;
-    if (kind == kOpRekey) {
-      const uint64_t nv = lane == pos ? y : v;
-      page_put(P, en.pid, nv);
-      if (pos == 0) pss_set(P, i, y, en.pid, en.cnt);
-      return true;
-    }
-    const uint64_t nv = page_del(v, pos);
-    const int32_t cnt = en.cnt - 1;
-    P.nkeys -= 1;
-    if (cnt == 0) {  // a lone page emptied
-      page_drop(P, en.pid);
-      pss_dir_remove(P, i);
-      return true;
-    }
-    page_put(P, en.pid, nv);
-    pss_set(P, i, rl64(nv, 0), en.pid, cnt);
-    if (cnt < kPage / 2 && P.np > 1) pss_rebalance(P, stage, i, nv, en.pid, cnt);
-    return true;
-  }
-  const int pos = __builtin_popcountll(ballot(v < x));
-  if (en.cnt < kPage) {
-    const uint64_t nv = page_ins(v, pos, x);
-    page_put(P, en.pid, nv);
-    pss_set(P, i, rl64(nv, 0), en.pid, en.cnt + 1);
+  const uint64_t nv = page_del(cu.v, cu.pos);
+  page_store(P, nv);
+  if (cu.pos == 0) pss_set(P, cu.i, rl64(nv, 0), cu.pid, cnt);
+  else pss_count(P, cu.i, cu.pid, cnt);
+  if (cnt < kPage / 4 && P.np > 1) pss_rebalance(P, stage, cu.i, nv, cu.pid, cnt);
+}
+// the key at cu becomes y, which sorts where it did
+__device__ __forceinline__ void pss_rekey_at(Pss& P, const Cur& cu, uint64_t y) {
+  page_store(P, (int)threadIdx.x == cu.pos ? y : cu.v);
+  if (cu.pos == 0) pss_set(P, cu.i, y, cu.pid, cu.cnt);
+}
+// x enters the set at cu, its place; false when that needs a page the directory has no entry for
+__device__ __forceinline__ bool pss_insert_at(Pss& P, LMEM uint64_t* stage, const Cur& cu, uint64_t x) {
+  const int lane = threadIdx.x;
+  if (cu.cnt < kPage) {
+    page_store(P, page_ins(cu.v, cu.pos, x));
+    if (cu.pos == 0) pss_set(P, cu.i, x, cu.pid, cu.cnt + 1);
+    else pss_count(P, cu.i, cu.pid, cu.cnt + 1);
     P.nkeys += 1;
     return true;
   }
   if (P.np >= P.cap) return false;
   const int32_t pid2 = page_new(P);
-  stage[lane + (lane >= pos ? 1 : 0)] = v;  // the kPage + 1 keys in order, split 33 | 32
-  if (lane == 0) stage[pos] = x;
+  if (cu.pos == kPage && cu.i + 1 == P.np) {  // past the last key: ascending keys fill their pages
+    page_put(P, pid2, lane == 0 ? x : kNoKey);
+    pss_dir_insert(P, cu.i + 1, x, pid2, 1);
+    P.nkeys += 1;
+    return true;
+  }
+  stage[lane + (lane >= cu.pos ? 1 : 0)] = cu.v;  // the kPage + 1 keys in order, split 33 | 32
+  if (lane == 0) stage[cu.pos] = x;
   wave_order();
   const uint64_t a = lane < kPage / 2 + 1 ? stage[lane] : kNoKey;
   const uint64_t b = lane < kPage / 2 ? stage[kPage / 2 + 1 + lane] : kNoKey;
   wave_order();
-  page_put(P, en.pid, a);
+  page_put(P, cu.pid, a);
   page_put(P, pid2, b);
-  pss_set(P, i, rl64(a, 0), en.pid, kPage / 2 + 1);
-  pss_dir_insert(P, i + 1, rl64(b, 0), pid2, kPage / 2);
+  pss_set(P, cu.i, rl64(a, 0), cu.pid, kPage / 2 + 1);
+  pss_dir_insert(P, cu.i + 1, rl64(b, 0), pid2, kPage / 2);
   P.nkeys += 1;
   return true;
 }
-
-// the updates one event makes to one set (at most three), in order
-struct SetOps {
-  int k, kind0, kind1, kind2;
-  uint64_t x0, x1, x2, y0, y1, y2;
-};
-// (selects, not branches: the fields stay in registers)
-__device__ __forceinline__ void ops_add(SetOps& o, int kind, uint64_t x, uint64_t y) {
-  const bool a0 = o.k == 0, a1 = o.k == 1, a2 = o.k == 2;
-  o.kind0 = a0 ? kind : o.kind0; o.x0 = a0 ? x : o.x0; o.y0 = a0 ? y : o.y0;
-  o.kind1 = a1 ? kind : o.kind1; o.x1 = a1 ? x : o.x1; o.y1 = a1 ? y : o.y1;
-  o.kind2 = a2 ? kind : o.kind2; o.x2 = a2 ? x : o.x2; o.y2 = a2 ? y : o.y2;
-  o.k += 1;
+__device__ __forceinline__ void pss_erase(Pss& P, LMEM uint64_t* stage, uint64_t x) {
+  if (P.np > 0) pss_erase_at(P, stage, pss_seek(P, x));  // (a key erased is present)
 }
-__device__ __forceinline__ bool ops_run(Pss& P, LMEM uint64_t* stage, const SetOps& o) {
-#pragma unroll
-  for (int k = 0; k < 3; ++k) {
-    if (k >= o.k) break;
-    const int kind = k == 0 ? o.kind0 : (k == 1 ? o.kind1 : o.kind2);
-    const uint64_t x = k == 0 ? o.x0 : (k == 1 ? o.x1 : o.x2);
-    const uint64_t y = k == 0 ? o.y0 : (k == 1 ? o.y1 : o.y2);
-    if (!pss_op(P, stage, kind, x, y)) return false;
+__device__ __forceinline__ bool pss_insert(Pss& P, LMEM uint64_t* stage, uint64_t x) {
+  if (P.np > 0) return pss_insert_at(P, stage, pss_seek(P, x), x);
+  const int32_t pid = page_new(P);
+  page_put(P, pid, threadIdx.x == 0 ? x : kNoKey);
+  pss_dir_insert(P, 0, x, pid, 1);
+  P.nkeys += 1;
+  return true;
+}
+// The key at cu is replaced by a smaller one, y.  Where y belongs in the same page, one pass moves
+// the keys between the two places up.
+__device__ __forceinline__ bool pss_lower_at(Pss& P, LMEM uint64_t* stage, const Cur& cu, uint64_t y) {
+  if (cu.i > 0 && y < rl64(cu.v, 0)) {
+    pss_erase_at(P, stage, cu);
+    return pss_insert(P, stage, y);
   }
+  const int lane = threadIdx.x;
+  const int32_t to = (int32_t)__builtin_popcountll(ballot(cu.v < y));
+  const uint64_t dn = from_lower_lane(cu.v);
+  const uint64_t nv = lane > to && lane <= cu.pos ? dn : (lane == to ? y : cu.v);
+  page_store(P, nv);
+  if (to == 0) pss_set(P, cu.i, y, cu.pid, cu.cnt);
   return true;
 }
 
 struct BigPool {
   Pss sz, ad;           // free blocks by key (size, address) and by address key (address, size)
-  SetOps osz, oad;      // this event's updates of each
   uint64_t split_min;   // split_min of this pool, in units
   GMEM uint64_t* segs;  // keys of the segments created in this pool, slot k at segs[segdir * k]
   int segdir;
@@ -3389,9 +3491,9 @@ __device__ __forceinline__ uint64_t big_idle_units(BigChain<NP, CH>& c) {
   }
   return wave_sum_u64(mine);
 }
-// release every idle segment of both pools; false if a set update failed
+// release every idle segment of both pools
 template <int NP, bool CH>
-__device__ __forceinline__ bool big_release_idle(BigChain<NP, CH>& c) {
+__device__ __forceinline__ void big_release_idle(BigChain<NP, CH>& c) {
 #pragma unroll
   for (int q = 0; q < NP; ++q) {
     BigPool& ps = c.p[q];
@@ -3401,93 +3503,138 @@ __device__ __forceinline__ bool big_release_idle(BigChain<NP, CH>& c) {
       const uint64_t x = page_get(ps.sz, en.pid);
       const uint64_t m = ballot((int32_t)threadIdx.x < en.cnt && seg_key_idle(ps.segs, ps.segdir, ps.nseg, x));
       if (!m) { ++i; continue; }
-      const uint64_t k = rl64(x, __builtin_ctzll(m));
+      const int pos = __builtin_ctzll(m);
+      const uint64_t k = rl64(x, pos);
       c.reserved_u -= key_size(k);
       c.released += 1;
-      if (!pss_op(ps.sz, c.stage, kOpErase, k, 0)) return false;
-      if (!pss_op(ps.ad, c.stage, kOpErase, akey_of(key_size(k), key_addr(k)), 0)) return false;
+      pss_erase_at(ps.sz, c.stage, Cur{i, en.pid, en.cnt, pos, x});
+      pss_erase(ps.ad, c.stage, akey_of(key_size(k), key_addr(k)));
       i = i > 0 ? i - 1 : 0;  // a merge may have moved keys into the page before
     }
   }
+}
+
+// An allocation that the chain's next event frees again, where a cached block fits and the free
+// count has been as high as it is now: the state after the two is the state before them, and only
+// the choice is noted.  False: replay them.
+template <int NP, bool CH>
+__device__ __forceinline__ bool pool_pair(BigChain<NP, CH>& c, BigPool& ps, uint64_t u) {
+  if (u >= kFastLimit || ps.maxfree < ps.sz.nkeys) return false;
+  Cur cu;
+  if (!pss_first_ge(ps.sz, u << 32, &cu)) return false;
+  note_choice(c, u, key_size(rl64(cu.v, cu.pos)));
   return true;
+}
+
+// Before each event (which adds at most one page to a set): a set of at most kPage / 2 keys a
+// directory entry always has room for another page.
+template <int NP, bool CH>
+__device__ __forceinline__ void pool_room(BigChain<NP, CH>& c, BigPool& ps) {
+  if (ps.sz.np < ps.sz.cap && ps.ad.np < ps.ad.cap) return;
+  if (ps.sz.nkeys > kPage / 2 * ps.sz.cap) return;
+  pss_compact(ps.sz, c.stage);
+  pss_compact(ps.ad, c.stage);
 }
 
 template <int NP, bool CH>
 __device__ __forceinline__ int pool_alloc(BigChain<NP, CH>& c, BigPool& ps, const Derived& d, const Gw& w, uint64_t u,
                                           int64_t e, uint64_t* blk) {
   if (u >= kFastLimit) return kRetry;
-  ps.osz.k = ps.oad.k = 0;
-  const uint64_t b = pss_first_ge(ps.sz, u << 32);
   const uint64_t split_min = ps.split_min;
-  if (b != kNoKey) {
+  Cur cu;
+  if (pss_first_ge(ps.sz, u << 32, &cu)) {
+    const uint64_t b = rl64(cu.v, cu.pos);
     const uint64_t S = key_size(b), A = key_addr(b), rem = S - u;
     note_choice(c, u, S);
-    ops_add(ps.osz, kOpErase, b, 0);
-    if (rem >= split_min) {  // the remainder keeps the block's place in address order
-      ops_add(ps.oad, kOpRekey, akey_of(S, A), akey_of(rem, A + u));
-      ops_add(ps.osz, kOpInsert, key_of(rem, A + u), 0);
-      *blk = key_of(u, A);
-    } else {
-      ops_add(ps.oad, kOpErase, akey_of(S, A), 0);
+    const uint64_t ak = akey_of(S, A);
+    if (rem < split_min) {
+      pss_erase_at(ps.sz, c.stage, cu);
+      pss_erase(ps.ad, c.stage, ak);
       *blk = b;
+      return XMEM_T_OK;
     }
-  } else {
-    // nothing cached fits: a new segment (Section 3.4 (ii), (iv))
-    const uint64_t S = segment_units(d, ps.pool, u);
-    if (ps.created_u + S > d.limit_u) return XMEM_T_OVERFLOW;
-    if (ps.bump + S + 1 > kFastLimit) return kRetry;
-    if (NP == 2 && S > d.cap_u - c.reserved_u) {  // Section 3.4 (v): reclaim idle segments, else OOM
-      const uint64_t idle = big_idle_units(c);
-      if (S > d.cap_u - (c.reserved_u - idle)) return XMEM_T_OOM;
-      if (!big_release_idle(c)) return kRetry;
-    }
-    const uint64_t A = ps.bump;
-    if (!CH && threadIdx.x == 0) ps.segs[(int64_t)ps.segdir * ps.nseg] = key_of(S, A);
-    ps.nseg += 1;
-    ps.bump += S + 1;  // one-unit gap: segments are never physically adjacent
-    ps.created_u += S;
-    c.reserved_u += S;
-    c.created += 1;
-    record_reserved(c, w, e, d.shift);
-    const uint64_t rem = S - u;
-    if (rem >= split_min) {
-      ops_add(ps.osz, kOpInsert, key_of(rem, A + u), 0);
-      ops_add(ps.oad, kOpInsert, akey_of(rem, A + u), 0);
-      *blk = key_of(u, A);
-    } else {
-      *blk = key_of(S, A);
-    }
+    *blk = key_of(u, A);
+    if (!pss_lower_at(ps.sz, c.stage, cu, key_of(rem, A + u))) return kRetry;
+    // the remainder keeps the block's place in address order
+    pss_rekey_at(ps.ad, pss_seek(ps.ad, ak), akey_of(rem, A + u));
+    return XMEM_T_OK;
   }
-  return ops_run(ps.sz, c.stage, ps.osz) && ops_run(ps.ad, c.stage, ps.oad) ? XMEM_T_OK : kRetry;
+  // nothing cached fits: a new segment (Section 3.4 (ii), (iv))
+  const uint64_t S = segment_units(d, ps.pool, u);
+  if (ps.created_u + S > d.limit_u) return XMEM_T_OVERFLOW;
+  if (ps.bump + S + 1 > kFastLimit) return kRetry;
+  if (NP == 2 && S > d.cap_u - c.reserved_u) {  // Section 3.4 (v): reclaim idle segments, else OOM
+    const uint64_t idle = big_idle_units(c);
+    if (S > d.cap_u - (c.reserved_u - idle)) return XMEM_T_OOM;
+    big_release_idle(c);
+  }
+  const uint64_t A = ps.bump;
+  if (!CH && threadIdx.x == 0) ps.segs[(int64_t)ps.segdir * ps.nseg] = key_of(S, A);
+  ps.nseg += 1;
+  ps.bump += S + 1;  // one-unit gap: segments are never physically adjacent
+  ps.created_u += S;
+  c.reserved_u += S;
+  c.created += 1;
+  record_reserved(c, w, e, d.shift);
+  const uint64_t rem = S - u;
+  if (rem < split_min) {
+    *blk = key_of(S, A);
+    return XMEM_T_OK;
+  }
+  *blk = key_of(u, A);
+  return pss_insert(ps.sz, c.stage, key_of(rem, A + u)) && pss_insert(ps.ad, c.stage, akey_of(rem, A + u))
+             ? XMEM_T_OK : kRetry;
 }
 
 template <int NP, bool CH>
 __device__ __forceinline__ int pool_free(BigChain<NP, CH>& c, BigPool& ps, uint64_t b) {
   const uint64_t A = key_addr(b), S = key_size(b), E = A + S;
-  ps.osz.k = ps.oad.k = 0;
-  // the free blocks just before and just after [A, E) in address order
-  const uint64_t la = A > 0 ? pss_last_le(ps.ad, (A << 32) - 1) : kNoKey;
-  const uint64_t ra = pss_first_ge(ps.ad, E << 32);
-  const bool hl = la != kNoKey && akey_addr(la) + akey_size(la) == A;
-  const bool hr = ra != kNoKey && akey_addr(ra) == E;
   uint64_t ms = S, ma = A;
-  if (hl) { ms += akey_size(la); ma = akey_addr(la); }
-  if (hr) ms += akey_size(ra);
-  if (hr) ops_add(ps.oad, kOpErase, ra, 0);
-  if (hl) ops_add(ps.oad, kOpRekey, la, akey_of(ms, ma));  // the merged block starts where the left one did
-  else ops_add(ps.oad, kOpInsert, akey_of(ms, ma), 0);
-  if (hl) ops_add(ps.osz, kOpErase, key_of(akey_size(la), akey_addr(la)), 0);
-  if (hr) ops_add(ps.osz, kOpErase, key_of(akey_size(ra), akey_addr(ra)), 0);
-  ops_add(ps.osz, kOpInsert, key_of(ms, ma), 0);
-  return ops_run(ps.sz, c.stage, ps.osz) && ops_run(ps.ad, c.stage, ps.oad) ? XMEM_T_OK : kRetry;
+  if (ps.ad.np > 0) {
+    // the free blocks just before and just after [A, E) in address order: the keys on both sides of
+    // its place (the one after it may be the next page's first)
+    const Cur cu = pss_seek(ps.ad, A << 32);
+    const bool in = cu.pos < cu.cnt;
+    const uint64_t la = cu.pos > 0 ? rl64(cu.v, cu.pos - 1) : kNoKey;
+    uint64_t ra = kNoKey;
+    if (in) ra = rl64(cu.v, cu.pos);
+    else if (cu.i + 1 < ps.ad.np) ra = uni64(ps.ad.dkey[cu.i + 1]);
+    const bool hl = la != kNoKey && akey_addr(la) + akey_size(la) == A;
+    const bool hr = ra != kNoKey && akey_addr(ra) == E;
+    if (hl) { ms += akey_size(la); ma = akey_addr(la); }
+    if (hr) ms += akey_size(ra);
+    const uint64_t mk = akey_of(ms, ma);
+    if (!hl && !hr) {
+      if (!pss_insert_at(ps.ad, c.stage, cu, mk)) return kRetry;
+    } else {
+      // the merged block takes the left one's place, else the right one's
+      if (hl) {
+        const Cur cl{cu.i, cu.pid, cu.cnt, cu.pos - 1, cu.v};
+        pss_rekey_at(ps.ad, cl, mk);
+        if (hr) pss_erase(ps.ad, c.stage, ra);
+        pss_erase(ps.sz, c.stage, key_of(akey_size(la), akey_addr(la)));
+      } else if (in) {
+        pss_rekey_at(ps.ad, cu, mk);
+      } else {
+        const Ent en = pss_ent(ps.ad, cu.i + 1);
+        const uint64_t nv = page_get(ps.ad, en.pid);
+        pss_rekey_at(ps.ad, Cur{cu.i + 1, en.pid, en.cnt, 0, nv}, mk);
+      }
+      if (hr) pss_erase(ps.sz, c.stage, key_of(akey_size(ra), akey_addr(ra)));
+    }
+  } else if (!pss_insert(ps.ad, c.stage, akey_of(ms, ma))) {
+    return kRetry;
+  }
+  return pss_insert(ps.sz, c.stage, key_of(ms, ma)) ? XMEM_T_OK : kRetry;
 }
 
 template <int NP>
 __global__ __launch_bounds__(kWave) void k_replay_big(const int64_t* off_, int64_t nchains, Derived d, Ws ws) {
-  constexpr int32_t cap = NP == 1 ? kBigDir1 : kBigDir2;
+  constexpr int32_t cap = NP == 1 ? kBigDir1 : kBigDir2, ways = kCacheSlots / (2 * NP);
   __shared__ uint64_t s_dkey[2 * NP][cap + 2];
   __shared__ uint32_t s_dpg[2 * NP][cap + 2];
   __shared__ uint64_t s_stage[2 * kPage + 2];
+  __shared__ uint64_t s_slots[kPage * kCacheSlots];
   const Gw w = typed(ws);
   const GMEM int64_t* off = gp(off_);
   if (w.ctl[0]) return;
@@ -3507,11 +3654,10 @@ __global__ __launch_bounds__(kWave) void k_replay_big(const int64_t* off_, int64
     for (int q = 0; q < NP; ++q) {
       const int pool = NP == 1 ? pool_one : q;
       BigPool& ps = c.p[q];
-      pss_init(ps.sz, (LMEM uint64_t*)s_dkey[2 * q], (LMEM uint32_t*)s_dpg[2 * q],
-               slot + (int64_t)(2 * q) * (cap + 2) * kPage, cap);
-      pss_init(ps.ad, (LMEM uint64_t*)s_dkey[2 * q + 1], (LMEM uint32_t*)s_dpg[2 * q + 1],
-               slot + (int64_t)(2 * q + 1) * (cap + 2) * kPage, cap);
-      ps.osz.k = ps.oad.k = 0;
+#pragma unroll
+      for (int a = 2 * q; a < 2 * q + 2; ++a)
+        pss_init(a & 1 ? ps.ad : ps.sz, (LMEM uint64_t*)s_dkey[a], (LMEM uint32_t*)s_dpg[a], cap + 2,
+                 slot + (int64_t)a * (cap + 2) * kPage, (LMEM uint64_t*)s_slots + kPage * ways * a, ways, cap);
       ps.segdir = pool == 0 ? 1 : -1;
       ps.segs = pool == 0 ? sgk + c.base : sgk + c.base + c.n - 1;
       ps.nseg = 0;
@@ -3540,30 +3686,49 @@ __global__ __launch_bounds__(kWave) void k_replay_big(const int64_t* off_, int64
 // them into fresh pages.
 static_assert(kBigDir1 == kBigDirMaxHost, "the chunked paged slots match the directory size");
 
-// the set's keys in order into dst; returns their count
-__device__ __forceinline__ int32_t pss_dump(Pss& P, GMEM uint64_t* dst) {
+// the set's keys in order into dst, eight pages at once; returns their count (after cache_flush)
+__device__ __forceinline__ int32_t pss_dump(const Pss& P, GMEM uint64_t* dst) {
+  const int lane = threadIdx.x;
   int32_t pos = 0;
-  for (int32_t i = 0; i < P.np; ++i) {
-    const Ent en = pss_ent(P, i);
-    const uint64_t x = page_get(P, en.pid);
-    if ((int32_t)threadIdx.x < en.cnt) dst[pos + (int32_t)threadIdx.x] = x;
-    pos += en.cnt;
+  for (int32_t r0 = 0; r0 < P.np; r0 += kWave) {
+    const uint32_t row = r0 + lane < P.np ? P.dpg[r0 + lane] : 0u;
+    const int32_t m = P.np - r0 < kWave ? P.np - r0 : kWave;
+    for (int32_t i = 0; i < m; i += 8) {
+      uint64_t x[8];
+#pragma unroll
+      for (int q = 0; q < 8; ++q) x[q] = P.pages[(int64_t)kPage * pss_decode(P, rl(row, i + q)).pid + lane];
+#pragma unroll
+      for (int q = 0; q < 8; ++q) {
+        const int32_t cnt = pss_decode(P, rl(row, i + q)).cnt;  // (0 past the directory's end)
+        if (lane < cnt) dst[pos + lane] = x[q];
+        pos += cnt;
+      }
+    }
   }
   wave_order();
   return pos;
 }
-// an empty set (pss_init) filled with cnt ascending keys, about 48 to a page
+// an empty set (pss_init) filled with cnt ascending keys, 48 to a page, eight pages at once
 __device__ __forceinline__ void pss_load(Pss& P, const GMEM uint64_t* src, int32_t cnt) {
+  const int lane = threadIdx.x;
   const int32_t per = (int64_t)cnt > 48 * (int64_t)P.cap ? kPage : 48;
   const int32_t np = (cnt + per - 1) / per;
-  for (int32_t i = 0; i < np; ++i) {
-    const int32_t a = (int32_t)((int64_t)i * cnt / np), b = (int32_t)((int64_t)(i + 1) * cnt / np);
-    const uint64_t x = (int32_t)threadIdx.x < b - a ? src[a + (int32_t)threadIdx.x] : kNoKey;
-    P.pages[(int64_t)kPage * i + threadIdx.x] = x;
-    if (threadIdx.x == 0) {
-      P.dkey[i] = x;
-      P.dpg[i] = (uint32_t)i | ((uint32_t)(b - a) << 16);
+  for (int32_t i = lane; i < np; i += kWave) {
+    const int32_t a = i * per, in = cnt - a < per ? cnt - a : per;
+    P.dkey[i] = src[a];
+    P.dpg[i] = (uint32_t)i | ((uint32_t)in << 16);
+  }
+  for (int32_t i = 0; i < np; i += 8) {
+    uint64_t x[8];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      const int32_t a = (i + q) * per + lane;
+      x[q] = src[a < cnt ? a : 0];
+      x[q] = lane < per && a < cnt ? x[q] : kNoKey;
     }
+#pragma unroll
+    for (int q = 0; q < 8; ++q)
+      if (i + q < np) P.pages[(int64_t)kPage * (i + q) + lane] = x[q];
   }
   wave_order();
   P.np = np;
@@ -3575,12 +3740,11 @@ __device__ __forceinline__ void pss_load(Pss& P, const GMEM uint64_t* src, int32
   pss_summary(P);
 }
 
-
 // One chunk on the paged sets: events [lo, hi) of the chain from the frontier's state.
 __device__ __forceinline__ void big_chunk(const Gw& w, const GMEM int64_t* off, const Derived& d, int64_t chain, int k,
                                           int64_t lo, int64_t hi, const CCtl& ctl, LMEM uint64_t* dkey0,
                                           LMEM uint64_t* dkey1, LMEM uint32_t* dpg0, LMEM uint32_t* dpg1,
-                                          LMEM uint64_t* s_stage) {
+                                          LMEM uint64_t* s_stage, LMEM uint64_t* s_slots) {
   const int lane = threadIdx.x;
   const int K = w.chunks;
   const int64_t t = chain >> 1;
@@ -3592,9 +3756,9 @@ __device__ __forceinline__ void big_chunk(const Gw& w, const GMEM int64_t* off, 
   c.n = off[t + 1] - c.base;
   c.stage = s_stage;
   BigPool& ps = c.p[0];
-  pss_init(ps.sz, dkey0, dpg0, slot, cap);
-  pss_init(ps.ad, dkey1, dpg1, slot + (int64_t)(cap + 2) * kPage, cap);
-  ps.osz.k = ps.oad.k = 0;
+  constexpr int32_t ways = kCacheSlots / 2;
+  pss_init(ps.sz, dkey0, dpg0, kBigDir1 + 2, slot, s_slots, ways, cap);
+  pss_init(ps.ad, dkey1, dpg1, kBigDir1 + 2, slot + (int64_t)(cap + 2) * kPage, s_slots + kPage * ways, ways, cap);
   ps.segdir = 1;
   ps.segs = (GMEM uint64_t*)w.segs + c.base;  // not written in chunk mode
   ps.nseg = 0;
@@ -3604,30 +3768,29 @@ __device__ __forceinline__ void big_chunk(const Gw& w, const GMEM int64_t* off, 
   ps.n_mf = 0;
   c.g = 0;
   bool loaded = true;
+  const GMEM uint64_t* add = nullptr;
+  int32_t nadd = 0;
   ps.bump = ps.created_u = 0;
   c.reserved_u = 0;
   c.created = 0;
   if (ctl.f > 0) {  // the frontier's state: the end state of the chunk before it, plus the delta keys
     const GMEM uint64_t* src = w.bstate + (chain * K + ctl.f - 1) * w.bstate_words;
-    const uint64_t cnts = src[3];
-    ps.bump = src[0];
-    ps.created_u = src[1];
-    c.reserved_u = src[2];
-    c.created = (int32_t)src[4];
+    const uint64_t cnts = uni64(src[3]);
+    ps.bump = uni64(src[0]);
+    ps.created_u = uni64(src[1]);
+    c.reserved_u = uni64(src[2]);
+    c.created = (int32_t)uni((uint32_t)src[4]);
     pss_load(ps.sz, src + 8, (int32_t)(uint32_t)cnts);
     pss_load(ps.ad, src + 8 + w.bstate_keys, (int32_t)(cnts >> 32));
   }
   if (ctl.nd > 0) {
     const GMEM uint64_t* del = w.cdel + chain * kDeltaWords;
-    ps.bump = del[kMaxDelta];
-    ps.created_u = del[kMaxDelta + 1];
-    c.reserved_u = del[kMaxDelta + 2];
-    c.created = (int32_t)del[kMaxDelta + 3];
-    for (int i = 0; i < ctl.nd && loaded; ++i) {
-      const uint64_t x = del[i];
-      loaded = pss_op(ps.sz, c.stage, kOpInsert, x, 0) &&
-               pss_op(ps.ad, c.stage, kOpInsert, akey_of(key_size(x), key_addr(x)), 0);
-    }
+    ps.bump = uni64(del[kMaxDelta]);
+    ps.created_u = uni64(del[kMaxDelta + 1]);
+    c.reserved_u = uni64(del[kMaxDelta + 2]);
+    c.created = (int32_t)uni((uint32_t)del[kMaxDelta + 3]);
+    add = del;
+    nadd = ctl.nd;
   }
   c.released = c.n_res = 0;
   int32_t created0 = c.created;
@@ -3636,24 +3799,24 @@ __device__ __forceinline__ void big_chunk(const Gw& w, const GMEM int64_t* off, 
     // the first chunk resumes where it outgrew the LDS table: that run's state (table keys and
     // counters), records, free-count maximum and lane registers; its records stay in place
     const GMEM uint64_t* src = w.cst + (chain * K + k) * kStateWords;
-    const uint64_t cw = src[kStateKeys + 3];
-    const int32_t cnt = (int32_t)(uint32_t)cw;
-    ps.bump = src[kStateKeys];
-    ps.created_u = src[kStateKeys + 1];
-    c.reserved_u = src[kStateKeys + 2];
+    const uint64_t cw = uni64(src[kStateKeys + 3]);
+    ps.bump = uni64(src[kStateKeys]);
+    ps.created_u = uni64(src[kStateKeys + 1]);
+    c.reserved_u = uni64(src[kStateKeys + 2]);
     c.created = (int32_t)(cw >> 32);
-    for (int32_t i = 0; i < cnt && loaded; ++i) {
-      const uint64_t x = src[i];
-      loaded = pss_op(ps.sz, c.stage, kOpInsert, x, 0) &&
-               pss_op(ps.ad, c.stage, kOpInsert, akey_of(key_size(x), key_addr(x)), 0);
-    }
+    add = src;
+    nadd = (int32_t)(uint32_t)cw;
     const CHdr h = gload(&w.chdr[chain * K + k]);
-    c.n_res = h.n_res;
-    ps.n_mf = h.n_mf;
-    ps.maxfree = h.maxc;
+    c.n_res = (int32_t)uni((uint32_t)h.n_res);
+    ps.n_mf = (int32_t)uni((uint32_t)h.n_mf);
+    ps.maxfree = (int32_t)uni((uint32_t)h.maxc);
     created0 = 0;  // the chunk's start: the empty state
     const GMEM uint64_t* fw = w.bstate + (chain * K + 1) * w.bstate_words;
     rs = Resume{(int64_t)ctl.resume - 1, fw[lane], fw[kWave + lane]};
+  }
+  for (int32_t i = 0; i < nadd && loaded; ++i) {  // further free blocks, one by one
+    const uint64_t x = uni64(add[i]);
+    loaded = pss_insert(ps.sz, c.stage, x) && pss_insert(ps.ad, c.stage, akey_of(key_size(x), key_addr(x)));
   }
   const int32_t n0 = ps.sz.nkeys;
   c.back_res = false;
@@ -3666,6 +3829,8 @@ __device__ __forceinline__ void big_chunk(const Gw& w, const GMEM int64_t* off, 
   int64_t stop = lo;
   if (loaded) chain_run<1>(c, d, w, pool_one, lo, hi, &status, &stop, &rs);
   GMEM uint64_t* dst = w.bstate + (chain * K + k) * w.bstate_words;
+  cache_flush(ps.sz);
+  cache_flush(ps.ad);
   const int32_t nsz = pss_dump(ps.sz, dst + 8);
   const int32_t nad = pss_dump(ps.ad, dst + 8 + w.bstate_keys);
   if (lane == 0) {
@@ -3688,6 +3853,7 @@ __global__ __launch_bounds__(kWave) void k_replay_combo(const int64_t* off_, int
   __shared__ uint64_t s_dkey[2][kBigDir1 + 2];
   __shared__ uint32_t s_dpg[2][kBigDir1 + 2];
   __shared__ uint64_t s_stage[2 * kPage + 2];
+  __shared__ uint64_t s_slots[kPage * kCacheSlots];
   static_assert(sizeof(s_dkey[0]) >= sizeof(uint64_t) * 64 * kTabRows, "a row table's keys fit in a directory");
   const Gw w = typed(ws);
   const GMEM int64_t* off = gp(off_);
@@ -3705,7 +3871,7 @@ __global__ __launch_bounds__(kWave) void k_replay_combo(const int64_t* off_, int
   const int64_t lo = bnd[k], hi = ctl.mode == 2 ? bnd[nk] : bnd[k + 1];
   if (ctl.big)
     big_chunk(w, off, d, chain, k, lo, hi, ctl, (LMEM uint64_t*)s_dkey[0], (LMEM uint64_t*)s_dkey[1],
-              (LMEM uint32_t*)s_dpg[0], (LMEM uint32_t*)s_dpg[1], (LMEM uint64_t*)s_stage);
+              (LMEM uint32_t*)s_dpg[0], (LMEM uint32_t*)s_dpg[1], (LMEM uint64_t*)s_stage, (LMEM uint64_t*)s_slots);
   else
     fast_chunk<true>(w, off, d, chain, k, uni((int32_t)lo), uni((int32_t)hi), ctl, (LMEM uint64_t*)s_dkey[0]);
 }

@@ -1,0 +1,64 @@
+"""Parity of the paged sets (pools of more free blocks than a row table holds) with the CPU oracle,
+bit-exact: more pages than a set keeps in LDS, allocations freed at once, page splits and merges in
+the middle and at the end, and a directory that fills with half-empty pages."""
+import numpy as np
+import pytest
+
+import oracle
+from evw import A, F
+from gpu_util import check
+from spill_traces import batch
+from test_gpu_rows import around
+
+pytestmark = pytest.mark.gpu
+
+P = oracle.paper_params()
+# every request of two units or more is served by a segment of its own size: free blocks never touch
+EXACT = oracle.paper_params(small_max_bytes=512, small_segment_bytes=512, mid_segment_bytes=1024,
+                            min_large_alloc_bytes=1024, large_round_bytes=512)
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _gpu():
+    import torch
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    import paper_2510_21048_amd as xm
+    xm.load()
+    yield
+
+
+@pytest.mark.parametrize("large", [False, True])
+@pytest.mark.parametrize("chunks", [0, 1, 9])
+@pytest.mark.parametrize("capacity", [None, 1 << 38])
+def test_pages_beyond_the_kept_ones(large, chunks, capacity):
+    """Up to 150 pages a set (30 or 60 are kept), with pairs that fit, pairs that need a segment and
+    pairs at a new maximum of the free count."""
+    ev, off = batch([around(7 + h, h, large, churn=3000) for h in (767, 2500, 6000)])
+    p = P if capacity is None else dict(P, device_capacity_bytes=capacity)
+    check(ev, off, p, chunks=chunks, what=f"paged, large={large}")
+
+
+@pytest.mark.parametrize("classes,capacity", [(2048, None), (1024, 1 << 40)])
+def test_full_directory_of_small_pages(classes, capacity):
+    """A page of keys per size class (the sizes ascend, so each page fills), then a 65th free block
+    splits each page and allocations drain its lower half to a quarter: the directory (4096 entries;
+    2048 with a capacity) is full of pages that hold fewer keys than half of it.  More free blocks
+    in some classes need further pages, which merging neighbours makes room for."""
+    more, drained = 100, 17
+    ev, blocks = [], []
+    for s in range(classes):
+        n = 65 + (35 if s < more else 0)
+        blocks.append(range(len(ev), len(ev) + n))
+        ev += [A(512 * (s + 2))] * n
+    for b in blocks:
+        ev += [F(i) for i in b[:32]] + [F(i) for i in b[33:65]]
+    for s, b in enumerate(blocks):
+        ev.append(F(b[32]))
+        ev += [A(512 * (s + 2))] * drained
+    for b in blocks[:more]:
+        ev += [F(i) for i in b[65:]]
+    ev, off = batch([np.array(ev, dtype=np.uint64)])
+    p = EXACT if capacity is None else dict(EXACT, device_capacity_bytes=capacity)
+    assert oracle.validate_params(p) == 0
+    g, _ = check(ev, off, p, chunks=1, what=f"{classes} classes")
+    assert g["max_free_blocks_large"][0] >= 64 * classes
