@@ -172,7 +172,7 @@ int xmem_validate_params(const xmem_allocator_params* p);
 /* Bytes of device workspace xmem_replay_batch_ex needs for this batch:
  * about 86 bytes per event plus, for batches of 32 traces or more, a fixed
  * 268 MB of paged free-block sets for pools whose free blocks outgrow the
- * replay kernel's LDS table (less for fewer traces), plus the chunked
+ * replay kernel's row table (less for fewer traces), plus the chunked
  * replay's task queue and chunk states (at most about 810 MB); for a single
  * trace, or two averaging 2^20 events or more, the chunks' own paged sets
  * instead, up to 8.4 MB per pool and chunk (one trace of 16.8M events:

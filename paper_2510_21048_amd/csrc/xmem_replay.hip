@@ -115,7 +115,7 @@ constexpr int kMaxChunks = 63;
 // scheduler): traces x chunks at most 127, so 2 x 127 workgroups of one wavefront, one per CU;
 // the cut planner's share table has room for a single trace's 127 chunks.  Two such traces run
 // there as fast as on the scheduler when no pool spills, and about 10x faster when their pools
-// outgrow the LDS table (the scheduler hands those to the serial paged kernel); three or four
+// outgrow the row table (the scheduler hands those to the serial paged kernel); three or four
 // would get 42 or 31 chunks each, 1.4-1.9x slower than the scheduler's 63 when none spills
 constexpr int kMaxComboChunks = 127;
 constexpr int64_t kFineEvents = 1 << 20;
@@ -2322,7 +2322,7 @@ __device__ __forceinline__ void store_choices(const Gw& w, int64_t slot, uint32_
 // A round replays, per chain, in MODE 0 the frontier chunk alone; in MODE 1
 // every chunk from the frontier on, each from the frontier's state; in MODE 2
 // the frontier chunk extended to the end of the chain.
-// One chunk on the LDS table: events [lo, hi) of the chain from the frontier's state.
+// One chunk on the row table: events [lo, hi) of the chain from the frontier's state.
 // Returns kChunkGrew when the chunk created segments, kChunkStopped when it stopped.
 constexpr int kChunkGrew = 1, kChunkStopped = 2;
 template <bool KEEP = false>  // KEEP: a first chunk that spills keeps its lane registers (the paged rounds resume there)
@@ -2422,8 +2422,8 @@ __device__ __forceinline__ int fast_chunk(const Gw& w, const GMEM int64_t* off, 
 // the running maximum), and advances the frontier; a finished chain gets its
 // header.
 //
-// Certification (paged chains, and small-pool chains on the LDS table; for a
-// large pool on the LDS table the choice summary per allocation did not repay
+// Certification (paged chains, and small-pool chains on the row table; for a
+// large pool on the row table the choice summary per allocation did not repay
 // its cost).  A chunk that created segments is exact when it ran from the
 // right state, and since it frees what it allocates, its end state is the
 // frontier's state plus its new segments, each one whole free block above every
@@ -2453,7 +2453,7 @@ __device__ __forceinline__ uint64_t wave_sort_desc(uint64_t v, int n, LMEM uint6
   wave_order();
   return r;
 }
-// RENAME: small-pool chunks on the LDS table may be certified past later growers (below); only
+// RENAME: small-pool chunks on the row table may be certified past later growers (below); only
 // where every chunk of the round ran, i.e. no bound gave up the chunks past a second grower
 // (chunks on the paged sets always run).
 __device__ __forceinline__ void stitch_walk(const Gw& w, const GMEM int64_t* off, int64_t chain, const int MODE,
@@ -2465,7 +2465,7 @@ __device__ __forceinline__ void stitch_walk(const Gw& w, const GMEM int64_t* off
   const int pool_one = (int)(chain & 1);
   const int nk = uni(w.cnum[chain]);
   const int64_t base = off[t], n = off[t + 1] - base;
-  // certification: paged chunks, and small-pool chunks on the LDS table, which need no choice
+  // certification: paged chunks, and small-pool chunks on the row table, which need no choice
   // summary (a small request never prefers a whole new small segment: no small block is larger,
   // and an equal one sits at a lower address)
   const bool CERT = BIG || pool_one == 0;
@@ -3063,7 +3063,7 @@ __global__ void k_combo_adopt(int64_t nchains, Ws ws) {
 }
 
 // ------------------------------------------------------------------ paged chain: sorted key pages
-// A chain whose pool outgrows its LDS table is replayed again by k_replay_big,
+// A chain whose pool outgrows its row table is replayed again by k_replay_big,
 // with each pool's free blocks held twice, in paged sorted sets: by key (size,
 // address), where best fit (Section 3.4 (iii)) is the first key >= (u << 32),
 // and by address key (address, size), where a block's free physical neighbours
@@ -3678,7 +3678,7 @@ __global__ __launch_bounds__(kWave) void k_replay_big(const int64_t* off_, int64
 }
 
 // ------------------------------------------------------------------ chunked replay on the paged sets
-// A chain whose pool outgrew the LDS table during the chunked replay is
+// A chain whose pool outgrew the row table during the chunked replay is
 // replayed again, in the same chunks and rounds, on the paged sets -- when the
 // batch is small enough for every (chain, chunk) to have its own page slot (a
 // few long traces, the case with no parallelism across chains).  A chunk state
@@ -3796,7 +3796,7 @@ __device__ __forceinline__ void big_chunk(const Gw& w, const GMEM int64_t* off, 
   int32_t created0 = c.created;
   Resume rs{-1, 0, 0};
   if (ctl.resume > 0) {
-    // the first chunk resumes where it outgrew the LDS table: that run's state (table keys and
+    // the first chunk resumes where it outgrew the row table: that run's state (table keys and
     // counters), records, free-count maximum and lane registers; its records stay in place
     const GMEM uint64_t* src = w.cst + (chain * K + k) * kStateWords;
     const uint64_t cw = uni64(src[kStateKeys + 3]);
@@ -3848,7 +3848,7 @@ __device__ __forceinline__ void big_chunk(const Gw& w, const GMEM int64_t* off, 
 // Few traces (every (chain, chunk) has its own paged slot, one wavefront per
 // CU): one round of the chunked replay for every chain, each in its own mode
 // and on its own path, so a pool moved to the paged sets runs its rounds beside
-// the other pools' rounds on the LDS table.
+// the other pools' rounds on the row table.
 __global__ __launch_bounds__(kWave) void k_replay_combo(const int64_t* off_, int64_t nchains, Derived d, Ws ws) {
   __shared__ uint64_t s_dkey[2][kBigDir1 + 2];
   __shared__ uint32_t s_dpg[2][kBigDir1 + 2];
@@ -4646,8 +4646,8 @@ constexpr int64_t kChunkWaves = 64512;
 constexpr int kAutoChunks = 63;
 constexpr int kMinAutoChunks = 16;
 constexpr int64_t kSerialTraces = 16384;
-// a single trace this short replays serially: the chunked rounds' fixed cost (about 1.5 ms of
-// launches) is more than its serial replay (about 0.27 us per event)
+// a single trace this short replays serially: 4,096 events of an MLP take 0.06 ms so, and the chunked
+// rounds' launches alone 0.2 ms
 constexpr int64_t kShortEvents = 4096;
 inline int chunk_count(const xmem_allocator_params* p, const Derived& d, int64_t T, int64_t N) {
   if (!d.split_pools || T <= 0) return 1;
@@ -4716,7 +4716,7 @@ int replay_launch(const uint64_t* d_events, const int64_t* d_offsets, int64_t n_
       k_plan_chains<<<(unsigned)n_traces, 64, 0, st>>>(d_offsets, n_traces, target, w);
       k_plan_cuts<<<(unsigned)pblocks, kPlanThreads, 0, st>>>(d_offsets, n_traces, w);
       k_plan_final<<<(unsigned)chains, 64, 0, st>>>(d_offsets, n_traces, w);
-      if (combo_main(n_traces, total_events, K)) {  // a few traces: every chain in its own mode, on the LDS table or the paged sets
+      if (combo_main(n_traces, total_events, K)) {  // a few traces: every chain in its own mode, on the row table or the paged sets
         ok = ok && mark(3);
         for (int r = 0; r < 2 * (kSpecRounds + 2); ++r) {
           k_replay_combo<<<(unsigned)(chains * K), kWave, 0, st>>>(d_offsets, chains, d, w);
