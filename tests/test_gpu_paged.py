@@ -62,3 +62,41 @@ def test_full_directory_of_small_pages(classes, capacity):
     assert oracle.validate_params(p) == 0
     g, _ = check(ev, off, p, chunks=1, what=f"{classes} classes")
     assert g["max_free_blocks_large"][0] >= 64 * classes
+
+
+@pytest.mark.parametrize("capacity", [None, 1 << 38])
+def test_few_spilled_chains_among_many(capacity):
+    """A workgroup of the paged kernel looks at 64 chains at once: spilled ones in its first, last and
+    middle places, in either pool, in more than one of its looks, among chains that are done."""
+    rest = [around(3, 2, large, churn=4) for large in (False, True)]
+    spilled = {0, 1, 31, 32, 63, 64, 2015, 2016, 2047, 2048, 2049, 4095, 4096, 4100}
+    traces = [around(k, 800, bool(k % 3), churn=200) if k in spilled else rest[k & 1] for k in range(4101)]
+    ev, off = batch(traces)
+    p = P if capacity is None else dict(P, device_capacity_bytes=capacity)
+    g, _ = check(ev, off, p, series=False, chunks=1, what="few spilled chains among many")
+    assert (np.maximum(g["max_free_blocks_small"], g["max_free_blocks_large"]) > 767).sum() == len(spilled)
+
+
+def test_idle_fallback_time():
+    """No pool spills: looking for one among 200,000 chains takes at most a fifth of the call (a
+    twentieth measured; half, a header at a time)."""
+    import torch
+    import paper_2510_21048_amd as xm
+    from paper_2510_21048_amd import binding
+    T, n = 100000, 8
+    e = torch.full((T * n,), 4096, dtype=torch.int64, device="cuda")
+    o, p = torch.arange(T + 1, device="cuda") * n, xm.params(0)
+    ws = torch.empty(binding.xmem_workspace_bytes(T, T * n, p), dtype=torch.uint8, device="cuda")
+    out = torch.empty((T, 96), dtype=torch.uint8, device="cuda")
+    share = []
+    for _ in range(6):
+        marks = [torch.cuda.Event(enable_timing=True) for _ in range(8)]
+        for m in marks:
+            m.record()  # creates the event
+        rc = binding.xmem_replay_batch_ex_timed(e, o, T, T * n, p, out, None, ws, ws.numel(),
+                                                torch.cuda.current_stream().cuda_stream, [m.cuda_event for m in marks])
+        assert rc == 0
+        torch.cuda.synchronize()
+        share.append(marks[4].elapsed_time(marks[5]) / marks[0].elapsed_time(marks[7]))
+    print(share, flush=True)
+    assert sorted(share)[3] <= 0.2, share  # (the first call loads the kernels)
