@@ -545,8 +545,8 @@ struct PrepWs {
                      // or the attribution's parameter-size hash sets (2 u32 slots per block)
   uint32_t* apos;    // n: position of an allocation word within its trace
   int32_t* bad;      // 1
-  uint64_t* kr;      // 8: a sort key's range on the device (min, max, OR of its values XOR a reference, gate),
-                     // then the lifecycle sort's second gate and its layout (kr[5], see k_life_keys)
+  uint64_t* kr;      // 8: the orchestration's times on the device: kr[0] their minimum, kr[1] their maximum; its
+                     // sorts' gates (32 bits each, from kr[3] on); their layout (kr[5], see k_orch_keys)
 };
 
 size_t carve(void* base, int64_t T, int64_t n, PrepWs* w) {
@@ -598,7 +598,7 @@ __global__ __launch_bounds__(kScanThreads) void k_begin(Offsets a, Offsets b, Of
   if (mine) s_bad = 1;
   if (blockIdx.x == 0 && threadIdx.x == 0) {
     kr[0] = ~0ull;
-    kr[1] = kr[2] = kr[3] = 0;
+    kr[1] = 0;
   }
   __syncthreads();
   if (gridDim.x > 1) {
@@ -633,57 +633,47 @@ void finish(int64_t T, bool empty, const PrepWs& w, int32_t* status, int64_t* ou
 
 // ---------------------------------------------------------------- key ranges
 // A sort key spans fewer bits than its 64: kr receives the minimum and maximum of the keys that
-// take part, and the OR of each XOR a reference value, whose trailing zeros all differences share.
-// The key then sorts as (key - min) >> trailing zeros, over the passes its width needs.
+// take part.  The key then sorts as key - min, over the passes its width needs.
 // a thread's running part of a range
 struct RangePart {
-  uint64_t mn = ~0ull, mx = 0, ox = 0;
-  __device__ void add(bool in, uint64_t v, uint64_t ref) {
+  uint64_t mn = ~0ull, mx = 0;
+  __device__ void add(bool in, uint64_t v) {
     mn = in && v < mn ? v : mn;
     mx = in && v > mx ? v : mx;
-    ox |= in ? v ^ ref : 0;
   }
 };
-constexpr int kRangeBlocks = 1024;  // workgroups of a range kernel (grid-stride; one set of atomics each)
-constexpr int kRangeUnroll = 8;     // records a range kernel's thread loads at once
 // the workgroup's parts combined (wavefront butterflies, then LDS), then one atomic per word
 __device__ __forceinline__ void range_commit(uint64_t* kr, RangePart p) {
-  __shared__ uint64_t s[3][kRecThreads / 64];
+  __shared__ uint64_t s[2][kRecThreads / 64];
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) {
-    const uint64_t a = __shfl_xor(p.mn, o, 64), b = __shfl_xor(p.mx, o, 64), c = __shfl_xor(p.ox, o, 64);
+    const uint64_t a = __shfl_xor(p.mn, o, 64), b = __shfl_xor(p.mx, o, 64);
     p.mn = a < p.mn ? a : p.mn;
     p.mx = b > p.mx ? b : p.mx;
-    p.ox |= c;
   }
   const int wv = threadIdx.x >> 6;
-  if ((threadIdx.x & 63) == 0) { s[0][wv] = p.mn; s[1][wv] = p.mx; s[2][wv] = p.ox; }
+  if ((threadIdx.x & 63) == 0) { s[0][wv] = p.mn; s[1][wv] = p.mx; }
   __syncthreads();
   if (threadIdx.x == 0) {
     for (int k = 1; k < (int)blockDim.x / 64; ++k) {
       p.mn = s[0][k] < p.mn ? s[0][k] : p.mn;
       p.mx = s[1][k] > p.mx ? s[1][k] : p.mx;
-      p.ox |= s[2][k];
     }
     if (p.mn <= p.mx) {
       atomicMin((unsigned long long*)&kr[0], (unsigned long long)p.mn);
       atomicMax((unsigned long long*)&kr[1], (unsigned long long)p.mx);
-      atomicOr((unsigned long long*)&kr[2], (unsigned long long)p.ox);
     }
   }
 }
-// the shift and the pass gate of a range: bits of (max - min) >> shift, as an even number of
-// passes (so that a gated sort ends in the buffer it started from)
-__device__ __forceinline__ int range_shift(const uint64_t* kr, bool use_tz) {
-  return use_tz && kr[2] != 0 ? __builtin_ctzll(kr[2]) : 0;
-}
-// bits of (max - min) >> shift
-__device__ __forceinline__ int range_bits(const uint64_t* kr, int shift) {
-  const uint64_t span = kr[0] <= kr[1] ? (kr[1] - kr[0]) >> shift : 0;
+// bits of max - min
+__device__ __forceinline__ int range_bits(const uint64_t* kr) {
+  const uint64_t span = kr[0] <= kr[1] ? kr[1] - kr[0] : 0;
   return span ? 64 - __builtin_clzll(span) : 0;
 }
-__device__ __forceinline__ int32_t range_gate(const uint64_t* kr, int shift) {
-  const int passes = (range_bits(kr, shift) + kDigit - 1) / kDigit;
+// the pass gate of a range: an even number of passes, so that a gated sort ends in the buffer it
+// started from
+__device__ __forceinline__ int32_t range_gate(const uint64_t* kr) {
+  const int passes = (range_bits(kr) + kDigit - 1) / kDigit;
   return kDigit * (passes + (passes & 1));
 }
 
@@ -1101,8 +1091,8 @@ __global__ __launch_bounds__(kRecThreads) void k_orch_retime(const xmem_block* b
     }
     if (f != kPersist && f < x.t_alloc) f = x.t_alloc;
     tfr[b] = f;
-    p.add(true, (uint64_t)x.t_alloc ^ (1ull << 63), 0);
-    p.add(f != kPersist, (uint64_t)f ^ (1ull << 63), 0);
+    p.add(true, (uint64_t)x.t_alloc ^ (1ull << 63));
+    p.add(f != kPersist, (uint64_t)f ^ (1ull << 63));
     freed += f != kPersist ? 1u : 0u;
   }
   atomicAdd(&s_cnt, freed);
@@ -1127,12 +1117,12 @@ __global__ __launch_bounds__(kRecThreads) void k_orch_keys(const xmem_block* blo
   if (*bad) return;
   __shared__ TileFlags f;
   const int64_t base = (int64_t)blockIdx.x * kTileN;
-  const int tb = range_bits(kr, 0);
+  const int tb = range_bits(kr);
   const bool joint = tbits + tb + 2 <= 64;
   const uint64_t lowest = kr[0];
   if (blockIdx.x == 0 && threadIdx.x == 0) {
     const int jp = (tbits + tb + 2 + kDigit - 1) / kDigit;
-    gate[0] = joint ? kDigit * jp : range_gate(kr, 0);
+    gate[0] = joint ? kDigit * jp : range_gate(kr);
     gate[1] = joint ? 0 : 64;
     gate[2] = joint ? 0 : 64;
     // the time sort starts in the second buffer; the separate layout then takes the trace passes
