@@ -57,6 +57,7 @@ def test_issue_reader_matches_workload_and_source(tmp_path, monkeypatch):
     write_summary(tmp_path / "pmc_a.txt", ["counter  per launch", "issue_key: w1", f"source_sha256: {sha}",
                                            "salu_per_event: 55.180", "valu_per_event: 40.794"])
     assert bench.measured_issue("w1", str(src)) == 55.18
+    assert bench.measured_issue("w1", str(src), count="valu_per_event") == 40.794
     assert bench.measured_issue("w2", str(src)) is None
     src.write_text("y\n")
     assert bench.measured_issue("w1", str(src)) is None
