@@ -18,7 +18,9 @@ FLAGS = [
     # the row tables order their integer keys as doubles, none of them a NaN: min and max need no quieting
     "-fno-honor-nans",
     # the event loops branch on wave-uniform values only: left unstructured, both sides of a branch update
-    # the table's registers in place (structured, each side keeps a copy: 1.7x the registers, and spills)
+    # the table's registers in place (structured, each side keeps a copy: 1.7x the registers, and spills
+    # in the loops; as it is, k_chunk_sched<false> and k_rs_scatter spill a few registers a tile, none
+    # of them between two events, which tests/test_abi_host.py holds them to)
     "-mllvm", "-structurizecfg-skip-uniform-regions=1",
 ]
 
