@@ -105,9 +105,10 @@ def test_lifecycles_random(seed, n_traces, max_len):
 
 @pytest.mark.parametrize("span_bits,n_traces", [(63, 1), (64, 1), (20, 1000), (27, 128), (60, 300), (56, 255), (57, 256)])
 def test_lifecycles_key_layouts(span_bits, n_traces):
-    """Address spans that put the pairing sort on one key of (trace, address) bits -- up to 64 bits
-    together, in an odd or an even number of 8-bit passes -- or on the address and then the trace.
-    The pool of addresses holds 0 and 2^span_bits - 1, so the span is exact and no low bit is shared."""
+    """Addresses and trace counts on both sides of the packed key of (trace, address), which takes
+    addresses below 2^47 and traces below 2^15: all keys packed (spans of 20 and 27 bits), or mixed
+    from trace and address for nearly all of them (56 bits and more), whose equality the pairing
+    verifies.  The pool of addresses holds 0 and 2^span_bits - 1."""
     rng = np.random.default_rng(span_bits * 1000 + n_traces)
     hi = (1 << span_bits) - 1
     pool = np.concatenate([np.array([0, hi], np.uint64), rng.integers(0, hi, 62, dtype=np.uint64, endpoint=True)])
