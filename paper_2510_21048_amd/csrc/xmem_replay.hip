@@ -369,6 +369,9 @@ __device__ __forceinline__ void gstore(GMEM T* p, const T& v) {
 // What one task of the chunk scheduler writes for another (states, headers, records, control words):
 // each 8 bytes an agent-scope access, which goes past the XCD's L2 where the XCDs share memory, so
 // no task has to write a whole L2 back or invalidate it.  cst/cld: one word, ast/ald: a struct.
+// Their order is the hardware's (stores_done, loads_after below), not one of acquire and release, so
+// it holds for these accesses alone: another field handed over has to go through them too, since a
+// plain store stays in its XCD's L2 and a plain load may find an old line in its own.
 __device__ __forceinline__ void cst(GMEM uint64_t* p, uint64_t v) {
   __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
@@ -2522,7 +2525,7 @@ __device__ __forceinline__ void stitch_walk(const Gw& w, const GMEM int64_t* off
             over = kfound == kWave && cnt > kWave && akey_addr(st[8 + w.bstate_keys + cnt - 1 - kWave]) >= sf_bump;
             kgot = is_new ? key_of(akey_size(a), akey_addr(a)) : kNoKey;  // lane i < kfound: new key i, descending
             kc0 = st[0]; kc1 = st[1]; kc2 = st[2]; kc3 = st[4];
-          } else {  // the saved table, unordered: its keys at or above the bump, then sorted
+          } else {  // the saved table, in key order (size first): its keys at or above the bump, sorted by address
             const GMEM uint64_t* st = w.cst + (chain * K + k) * kStateWords;
             const uint64_t cw = cld(st + kStateKeys + 3);
             const int32_t cnt = (int32_t)(uint32_t)cw;
@@ -2689,7 +2692,7 @@ __device__ __forceinline__ void stitch_walk(const Gw& w, const GMEM int64_t* off
         over = found == kWave && cnt > kWave && akey_addr(st[8 + w.bstate_keys + cnt - 1 - kWave]) >= sf_bump;
         got = is_new ? key_of(akey_size(a), akey_addr(a)) : kNoKey;  // lane i < found: new key i
       } else {
-        // the end state's table, unordered: gather the keys at or above the bump in LDS
+        // the end state's table, in key order (size first): gather the keys at or above the bump in LDS
         const GMEM uint64_t* st = w.cst + (chain * K + k) * kStateWords;
         const uint64_t cw = cld(st + kStateKeys + 3);
         const int32_t cnt = (int32_t)(uint32_t)cw;
@@ -3023,7 +3026,7 @@ __global__ __launch_bounds__(kWave, 6) void k_chunk_sched(SchedArgs args) {
 }
 // Batches of few chunks per pool (fewer than 16): every task is a long part of its chain, and
 // the batch ends with its slowest chains.  Windowed rounds, and each chunk raises its
-// wavefront's issue priority as it ages (chain_run), so that a SIMD's oldest tasks go first.
+// wavefront's issue priority as it ages (row_run), so that a SIMD's oldest tasks go first.
 // Short tasks never reach an age check, but the loop state costs the kernels of finer batches
 // about 1-2%, so they run the instances above.
 __global__ __launch_bounds__(kWave, 6) void k_chunk_sched_aged(SchedArgs args) {
@@ -3895,7 +3898,7 @@ __global__ __launch_bounds__(kWave) void k_replay_combo(const int64_t* off_, int
 }
 
 // After each k_replay_combo round: the walk of k_chunk_stitch in each chain's
-// own mode and path, then the chain's next mode: a pool that outgrew the LDS
+// own mode and path, then the chain's next mode: a pool that outgrew the row
 // table starts over on the paged sets; after the first chunk come the
 // speculative rounds, and after kSpecRounds of them the rest in one piece.
 __global__ __launch_bounds__(kWave) void k_chunk_stitch_combo(const int64_t* off_, int64_t nchains, Ws ws) {
@@ -4664,8 +4667,11 @@ constexpr int64_t kChunkWaves = 64512;
 constexpr int kAutoChunks = 63;
 constexpr int kMinAutoChunks = 16;
 constexpr int64_t kSerialTraces = 16384;
-// a single trace this short replays serially: 4,096 events of an MLP take 0.06 ms so, and the chunked
-// rounds' launches alone 0.2 ms
+// A single trace this short replays serially: the longest that is no slower so for any shape measured
+// (us a call, serial / in 63 chunks; 4,096 events: ResNet-shaped 545 / 600, GPT-shaped 573 / 777,
+// random churn 429 / 535, MLP 100 / 272).  The ResNet-shaped one, whose iterations are short, is
+// faster in chunks from there on (6,000 events 760 / 610, 8,192 994 / 621); the others later: GPT-shaped
+// and churn at about 16,000 (8,192 events 929 / 1,175 and 784 / 873), the MLP past 32,768 (420 / 981).
 constexpr int64_t kShortEvents = 4096;
 inline int chunk_count(const xmem_allocator_params* p, const Derived& d, int64_t T, int64_t N) {
   if (!d.split_pools || T <= 0) return 1;
