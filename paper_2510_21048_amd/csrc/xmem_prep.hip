@@ -33,8 +33,8 @@
 // the passes are known on the host, whatever the addresses span.  The orchestration sorts by time,
 // rebased to its batch's minimum, over the passes its span needs.  Up to 8,192 records are sorted
 // by one workgroup in one launch, and no flags are scanned: per tile counts, added up by the
-// kernels that use them.  One profile of 4,001 events takes 15 launches instead of 148: 535 -> 211 us
-// for the three steps (with their host calls); 128 profiles of 65,536 events 2,045 -> 1,656 us.
+// kernels that use them.  One profile of 4,001 events takes 15 launches instead of 148: 535 -> 200 us
+// for the three steps (with their host calls); 128 profiles of 65,536 events 2,045 -> 1,585 us.
 #include <hip/hip_runtime.h>
 #include <algorithm>
 #include <stddef.h>
@@ -747,10 +747,12 @@ __device__ __forceinline__ bool life_same(const xmem_raw_event* raw, const int64
 // the next record of its key when that is a free; a free is unmatched unless the record of its key
 // before it is an allocation.  Few other keys may still be many records: where one address is taken
 // and freed again all the time, its records lie between those of any other that shares its hash.  So
-// a thread looks at its kNear next records only, and then its workgroup goes on through the run,
-// 2,048 records a step.  2^20 events, half of them at one address, 30 others sharing its hash: the
-// call takes 260 us, by threads alone 57 ms; 110 us either way where none shares it.  (64 records
-// a thread: 16 profiles of 20,011 events 103 -> 111 us a call; 512 or 1,024 threads 110 or 115 us.)
+// a thread looks at its kNear next records only, its wavefront at the 64 after them, and then its
+// workgroup goes on through the run, 2,048 records a step.  2^20 events, half of them at one address,
+// 30 others sharing its hash: the call takes 260 us, by threads alone 57 ms; 110 us either way where
+// none shares it.  (64 records a thread: 16 profiles of 20,011 events 103 -> 111 us a call; 512 or
+// 1,024 threads 110 or 115 us.  Without the wavefronts' part a batch whose runs are a little longer
+// than a thread's part waits for its workgroups: 40 profiles of 2,000 events 97 us a call, 88 with it.)
 constexpr int kNear = 16, kFarItems = 8;
 constexpr int64_t kNoPartner = -1, kFarPartner = -2;
 __device__ __forceinline__ uint64_t run_of(uint64_t key, int shift0) {
@@ -782,12 +784,28 @@ __device__ __forceinline__ int64_t life_near(const LifeRun& r, int64_t p, uint64
   }
   return kFarPartner;
 }
-// the same past the kNear next ones, by the whole workgroup (s_hit: one word; every thread calls it):
+__device__ __forceinline__ uint64_t lane_u64(uint64_t v, int lane) {
+  return ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(v >> 32), lane) << 32) |
+         (uint32_t)__builtin_amdgcn_readlane((int)v, lane);
+}
+// the same among the 64 after those, by one wavefront (p, x and k wave-uniform)
+__device__ __forceinline__ int64_t life_wave(const LifeRun& r, int64_t p, uint64_t x, uint32_t k) {
+  const int64_t dir = (x & 1) ? -1 : 1, from = p + dir * (kNear + 1), q = from + dir * (int64_t)(threadIdx.x & 63);
+  const uint64_t y = q >= 0 && q < r.n ? r.key[q] : x;  // (x: past the records the search ends)
+  for (uint64_t m = ballot((y | 1) == (x | 1) || run_of(y, r.shift0) != run_of(x, r.shift0)); m; m &= m - 1) {
+    const int64_t at = from + dir * (int64_t)__builtin_ctzll(m);
+    if (at < 0 || at >= r.n) return kNoPartner;
+    const int look = life_look(r, x, k, at, r.key[at]);
+    if (look >= 0) return look ? at : kNoPartner;
+  }
+  return kFarPartner;
+}
+// the same past the kNear + 64 next ones, by the whole workgroup (s_hit: one word; every thread calls it):
 // the nearest place that holds x's key or ends the run, then whether that is of x's trace and address
 __device__ int64_t life_far(const LifeRun& r, int64_t p, uint64_t x, uint32_t k, uint32_t* s_hit) {
   const int64_t dir = (x & 1) ? -1 : 1;
   const uint64_t run = run_of(x, r.shift0);
-  for (int64_t from = p + dir * (kNear + 1);;) {
+  for (int64_t from = p + dir * (kNear + 64 + 1);;) {
     uint64_t y[kFarItems];
 #pragma unroll
     for (int i = 0; i < kFarItems; ++i) {
@@ -839,12 +857,17 @@ __global__ __launch_bounds__(kThreads, 8) void k_life_pair(const xmem_raw_event*
   if (threadIdx.x == 0) s_nfar = 0;
   __syncthreads();
   const uint64_t x = p < n ? key[p] : kNone;
-  if ((x & kNone) != kNone && (!(x & 1) || unmatched)) {
-    const uint32_t k = val[p];
-    const int64_t q = life_near(r, p, x, k);
-    if (q == kFarPartner) s_far[atomicAdd(&s_nfar, 1u)] = threadIdx.x;
-    else life_settle(r, x, k, q, tfree, unmatched);
+  const bool search = (x & kNone) != kNone && (!(x & 1) || unmatched);
+  const uint32_t k = search ? val[p] : 0;
+  int64_t q = search ? life_near(r, p, x, k) : kNoPartner;
+  for (uint64_t far = ballot(q == kFarPartner); far; far &= far - 1) {
+    const int l = __builtin_ctzll(far);
+    const int64_t found = life_wave(r, base + (int)(threadIdx.x & ~63u) + l, lane_u64(x, l),
+                                    (uint32_t)__builtin_amdgcn_readlane((int)k, l));
+    if ((int)(threadIdx.x & 63) == l) q = found;
   }
+  if (q == kFarPartner) s_far[atomicAdd(&s_nfar, 1u)] = threadIdx.x;
+  else if (search) life_settle(r, x, k, q, tfree, unmatched);
   __syncthreads();
   const uint32_t nfar = s_nfar;
   for (uint32_t i = 0; i < nfar; ++i) {

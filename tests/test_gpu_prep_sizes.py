@@ -108,6 +108,35 @@ def test_lifecycles_hot_address(n, base, trace):
     check_lifecycles(raw, off, what=f"{n} events, half at one address")
 
 
+@pytest.mark.parametrize("base", [0x7F0000000000, 1 << 52], ids=["packed", "wide"])
+def test_lifecycles_partner_distance(base):
+    """A partner, or the end of the run, at the edges of what a thread (16 records), its wavefront (64
+    more) and its workgroup (2,048 a step) look at: rare addresses between the records of a hot one."""
+    hot = np.uint64(base + (5 << 21))
+    cand = (base + (np.arange(1 << 24) << 9)).astype(np.uint64)
+    rare = cand[(life_hash(cand, 0) == life_hash(np.array([hot]), 0)[0]) & (cand != hot)]
+    edges = [1, 2, 15, 16, 17, 18, 79, 80, 81, 82, 16 + 64 + 2048, 16 + 64 + 2049, 5000]
+    assert len(rare) > len(edges)
+    for end in edges:
+        rows, h = [(rare[0], -64)], 0  # a free of nothing
+        def hots(n):
+            nonlocal h
+            for _ in range(n):
+                rows.append((hot, 4096 if h % 2 == 0 else -4096))
+                h += 1
+        for d, a in zip(edges, rare[1:]):
+            rows.append((a, 512))
+            hots(d - 1)
+            rows.append((a, -512))
+        rows.append((rare[0], 64))  # never freed, the run's end `end` records on
+        hots(end - 1)
+        raw = np.zeros(len(rows), oracle.RAW_DTYPE)
+        raw["ts"] = np.arange(len(rows))
+        raw["addr"] = np.array([a for a, _ in rows], np.uint64)
+        raw["bytes"] = [b for _, b in rows]
+        check_lifecycles(raw, np.array([0, len(rows)]), what=f"distances to {edges[-1]}, the run's end after {end}")
+
+
 def test_lifecycles_hot_address_time():
     """The records between are stepped over by a workgroup: the call takes at most 4 times as long as
     where no address shares the hot one's hash (2.4 measured; over 500 by single threads)."""
