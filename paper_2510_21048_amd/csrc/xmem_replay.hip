@@ -20,7 +20,7 @@
 //               (the pools never interact), else one trace.  The chain walks
 //               the annotated stream in 64-event tiles with a one-tile
 //               prefetch.  Each free block is one packed key (size, address),
-//               held sorted in vector registers (768 per pool; paged sorted sets
+//               held sorted in vector registers (767 per pool; paged sorted sets
 //               in HBM beyond): best fit (Section 3.4 (iii)) is one comparison per
 //               row and a ballot, a split or merge moves the keys between its old
 //               and new place by one, a new segment is
@@ -1768,7 +1768,9 @@ __device__ __forceinline__ void chain_header(const C& c, const Gw& w, int np, in
 // to the shader engines of each in fixed turns, whose length is a power of two: with a trace's two
 // pools one after the other, every second engine had only small pools to run, and the others waited
 // for whichever pool took longer (20,000 GPT-shaped traces of 300 events: 820 us, so 517; with all
-// events in one pool, 1,000 each: 1,920 -> 1,230 us a call).
+// events in one pool, 1,000 each: 1,920 -> 1,230 us a call).  A single trace keeps the pools' order, in
+// which the first workgroup has the small pool (4,096 MLP events: 83.4 us a call, the large pool
+// first 84.4).
 template <int NP>
 __global__ __launch_bounds__(kWave, NP == 1 ? 6 : 3) void k_replay_fast(const int64_t* off_, Derived d, Ws ws) {
   const Gw w = typed(ws);
@@ -1776,7 +1778,7 @@ __global__ __launch_bounds__(kWave, NP == 1 ? 6 : 3) void k_replay_fast(const in
   if (w.ctl[0]) return;
   __shared__ uint64_t s_k[64 * kTabRows];
   const int64_t half = gridDim.x / 2, b = blockIdx.x;
-  const int64_t chain = NP == 1 ? (b < half ? 2 * b + 1 : 2 * (b - half)) : b;
+  const int64_t chain = NP == 1 && half > 1 ? (b < half ? 2 * b + 1 : 2 * (b - half)) : b;
   const int64_t t = NP == 1 ? (chain >> 1) : chain;
   const int pool_one = NP == 1 ? (int)(chain & 1) : 0;  // pool of a split chain
   GMEM uint64_t* sgk = (GMEM uint64_t*)w.segs;
