@@ -1,6 +1,6 @@
 """Seeded churn traces that leave thousands of blocks free at once in one pool.
 
-They drive a pool past the replay kernel's LDS table and through the paged free-block sets:
+They drive a pool past the replay kernel's row table and through the paged free-block sets:
 the live count rises to a peak, falls back almost to zero and rises again, so pages split,
 merge, even out with neighbours and empty; random sizes make blocks split and coalesce.
 Format only: event words, no allocator logic."""

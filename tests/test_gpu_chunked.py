@@ -108,7 +108,7 @@ def test_no_clean_position():
 
 
 def test_chunked_spill_to_paged_sets():
-    """A chunk whose pool outgrows the LDS table hands its whole chain to the paged kernel."""
+    """A chunk whose pool outgrows the row table hands its whole chain to the paged kernel."""
     traces = [churn(1, 60000, 3000, 512, 64 << 10), fragment(5, 12000, 20000), growing(200, 1)]
     ev, off = batch(traces)
     gres, ores = check(ev, off, P, what="chunked spill", chunks=8)
@@ -167,7 +167,7 @@ def test_chunk_counts_agree_bitwise():
 
 @pytest.mark.parametrize("chunks", [2, 8, 63])
 def test_chunked_paged_sets(chunks):
-    """A pool past the LDS table in a batch of one or two traces: its chunks are replayed again
+    """A pool past the row table in a batch of one or two traces: its chunks are replayed again
     on the paged sets, each from the packed key lists of the chunk before (the frontier)."""
     spill = churn(11, 90000, 8000, 512, 64 << 10, waves=3)
     for traces in ([spill], [fragment(12, 30000, 40000)], [growing(100, 1), spill]):
@@ -178,7 +178,7 @@ def test_chunked_paged_sets(chunks):
 
 @pytest.mark.parametrize("chunks", [2, 8, 32, 63])
 def test_paged_resume_after_spill(chunks):
-    """A first chunk that outgrows the LDS table hands over to the paged sets at the event where
+    """A first chunk that outgrows the row table hands over to the paged sets at the event where
     it did, from the state it left there; temporaries freed within 150 events, at seeded points
     of the 64-event tile, reach the resumed run through both tiles' lane registers and the
     mailbox, in either pool.  One trace per batch, and two (chunks <= 32) with the few-trace
@@ -198,7 +198,7 @@ def test_paged_resume_after_spill(chunks):
 def test_one_long_trace_fine_grain():
     """A single trace of 2^20 events or more is cut into up to 127 chunks per pool (the automatic
     grain; the cut planner takes the second group of 64 cuts), replayed in the paged-set rounds:
-    a GPT-style trace that stays on the LDS table, and a fragmented one that spills."""
+    a GPT-style trace that stays on the row table, and a fragmented one that spills."""
     for cfg, fp in ((3, -1), (5, 3000)):
         ev, off = tracegen.generate(cfg, 1, 1 << 20, frag_pairs=fp)
         gres, ores = check(ev, off, P, what=f"C{cfg} 1 x 2^20, automatic grain")
@@ -219,7 +219,7 @@ def test_two_long_traces_paged_rounds():
 
 def test_long_traces_spill_after_scheduler():
     """Three traces averaging 2^20 events or more run the chunk scheduler; the pool that outgrows
-    the LDS table there is replayed by the paged-set rounds afterwards (not the serial paged
+    the row table there is replayed by the paged-set rounds afterwards (not the serial paged
     kernel), beside two that finish under the scheduler."""
     ev3, off3 = tracegen.generate(3, 2, 1 << 20)
     ev5, off5 = tracegen.generate(5, 1, (1 << 20) + 4097, frag_pairs=3000)
@@ -294,8 +294,9 @@ def test_paged_chunks_past_later_growers(chunks):
 
 
 # 1 KiB blocks freed every other: the oracle's largest small-pool free count is 766 (766 - 2 on the
-# chunk's speculative run, without the two new segments) -- certified within the 768-slot table;
-# with 8 more blocks it is 769, so that chunk is not certified and its true run spills
+# chunk's speculative run, without the two new segments) -- certified within the row table, which
+# holds 767; with 2 more blocks it is 767, with 4 more 768 and with 8 more 769, and a chunk that
+# would pass 767 is not certified and its true run spills
 FRAG_NEAR = 1528
 
 
@@ -304,16 +305,17 @@ def test_small_pool_certification(chunks):
     """Small-pool chunks after one that created segments are certified instead of replayed again:
     the new segments join the next frontier's table, later maxima shift by their count, a later
     segment-creating chunk ends the certified run, and a chunk whose free count with the delta
-    would pass the LDS table is not certified (the last trace: the true run spills)."""
+    would pass the row table is not certified (the traces of 768 and 769: the true runs spill)."""
     traces = [small_growth(120, (30,), frag_at=(60, 100)),
               small_growth(120, (10, 50, 90), frag_at=(20, 70, 110)),
               small_growth(60, (20,), frag_at=(40,), m=100, size=KiB, frag_m=FRAG_NEAR, gstep=8),
               growing(150, 2, steady_after=40),
-              small_growth(60, (20,), frag_at=(40,), m=100, size=KiB, frag_m=FRAG_NEAR + 8, gstep=8)]
+              *[small_growth(60, (20,), frag_at=(40,), m=100, size=KiB, frag_m=FRAG_NEAR + more, gstep=8)
+                for more in (8, 2, 4)]]
     ev, off = batch(traces)
     gres, ores = check(ev, off, P, what=f"small-pool certification chunks={chunks}", chunks=chunks)
     mf = ores["max_free_blocks_small"]
-    assert int(mf[2]) <= 768 < int(mf[4]) and int(ores["segments_created"][1]) >= 5
+    assert [int(mf[t]) for t in (2, 5, 6, 4)] == [766, 767, 768, 769] and int(ores["segments_created"][1]) >= 5
     for t in range(2):  # a batch of one trace: the rounds of the few-traces kernels
         ev1, off1 = batch([traces[t]])
         check(ev1, off1, P, what=f"small-pool certification, one trace, chunks={chunks}", chunks=chunks)

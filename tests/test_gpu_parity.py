@@ -71,7 +71,7 @@ def test_configs_reduced(cfg):
     ev, off = tracegen.generate(cfg, nt, ne, frag_pairs=fp)
     gres, ores = check(ev, off, P, what=f"C{cfg} reduced")
     if cfg == 5:
-        assert ores["max_free_blocks_small"][0] > 2000  # the LDS table spills to HBM
+        assert ores["max_free_blocks_small"][0] > 2000  # the row table spills to the paged sets
 
 
 def test_ragged_batch_with_empty_traces():
@@ -380,7 +380,7 @@ def _spill_traces():
 
 
 def test_paged_sets():
-    """Pools with more free blocks than the LDS table holds are replayed with the paged sets:
+    """Pools with more free blocks than the row table holds are replayed with the paged sets:
     pages split, merge, even out and empty as the free set rises and falls (up to ~15K free
     blocks, several summary rows of the directory), in both pools."""
     ev, off = batch(_spill_traces())

@@ -74,7 +74,7 @@ def test_noalloc_matches_ex_two_calls():
 
 
 def test_noalloc_serial_fallback_and_capacity():
-    """A long trace whose small pool outgrows the LDS table (the paged-set kernel runs): its
+    """A long trace whose small pool outgrows the row table (the paged-set kernel runs): its
     chunked workspace does not fit the area, so the serial replay with fewer paged slots runs;
     then a smaller batch under a finite capacity (reclaim and OOM), again after a larger call."""
     P = oracle.paper_params()
