@@ -117,7 +117,7 @@ def test_stable_per_seed():
 
 
 def test_spill_mix_passes_the_table_early():
-    """The resume traces pass 768 free blocks (a row table holds 767) of their pool in their
+    """The resume traces pass 768 free blocks (as many as a row table holds) of their pool in their
     fragmentation phase, with every temporary freed and no free of a free."""
     import oracle
     from spill_traces import spill_mix, batch

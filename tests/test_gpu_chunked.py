@@ -295,8 +295,8 @@ def test_paged_chunks_past_later_growers(chunks):
 
 # 1 KiB blocks freed every other: the oracle's largest small-pool free count is 766 (766 - 2 on the
 # chunk's speculative run, without the two new segments) -- certified within the row table, which
-# holds 767; with 2 more blocks it is 767, with 4 more 768 and with 8 more 769, and a chunk that
-# would pass 767 is not certified and its true run spills
+# holds 768; with 2 more blocks it is 767, with 4 more 768 and with 8 more 769, where the chunk is not
+# certified and its true run spills
 FRAG_NEAR = 1528
 
 
@@ -305,7 +305,7 @@ def test_small_pool_certification(chunks):
     """Small-pool chunks after one that created segments are certified instead of replayed again:
     the new segments join the next frontier's table, later maxima shift by their count, a later
     segment-creating chunk ends the certified run, and a chunk whose free count with the delta
-    would pass the row table is not certified (the traces of 768 and 769: the true runs spill)."""
+    would pass the row table is not certified (the trace of 769: the true run spills)."""
     traces = [small_growth(120, (30,), frag_at=(60, 100)),
               small_growth(120, (10, 50, 90), frag_at=(20, 70, 110)),
               small_growth(60, (20,), frag_at=(40,), m=100, size=KiB, frag_m=FRAG_NEAR, gstep=8),
